@@ -75,6 +75,7 @@ struct AttnPlan {
   AttnPath path;
   bool kv_fp8, br_fp8;
   int shape, tile_m, n_row_tiles, chunk_len, last_short, s_max, total_units;
+  // (general path: shape = row blocks of 16 per workgroup; the workspace is optional there)
   size_t part_o_bytes, part_ml_bytes;
 };
 
@@ -99,6 +100,61 @@ la_status validate_desc(const la_attn_desc *d) {
   return LA_OK;
 }
 
+// Partial slots, workspace sizes and the number of (request, chunk) units, once chunk_len is chosen.
+void size_partials(const la_attn_desc *d, const int32_t *prefix_lens_host, AttnPlan *plan) {
+  const size_t n_rows = (size_t)d->gamma * d->branch_len * d->num_q_heads;
+  int s_max = 1, total = 0;
+  for (int b = 0; b < d->num_requests; ++b) {
+    const int nc = attn_num_chunks(prefix_lens_host[b], plan->chunk_len);
+    s_max = nc > s_max ? nc : s_max;
+    total += nc;
+  }
+  plan->s_max = s_max;
+  plan->total_units = total;
+  plan->part_o_bytes = align_up((size_t)d->num_requests * s_max * n_rows * d->head_dim * sizeof(float));
+  plan->part_ml_bytes = align_up((size_t)d->num_requests * s_max * n_rows * 2 * sizeof(float));
+}
+
+constexpr int kWholePrefix = 1 << 30;   // chunk length of an unsplit plan (no prefix is longer)
+
+// The general path: one workgroup per (row block, kv head) and request, and, for bf16 / fp8 storage, chunks of the
+// prefix where that leaves the chip idle.  fp32 calls have no workspace (their sizes are small, and the query says so).
+void make_general_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, int64_t max_p, bool f32, AttnPlan *plan) {
+  const int R = d->gamma * d->branch_len * (d->num_q_heads / d->num_kv_heads);
+  plan->path = PATH_F32;
+  // two row blocks share every operand of a key where the registers allow it (measured figures: attn_f32.hip)
+  plan->shape = !f32 && d->head_dim == 64 && R > 16 ? 2 : 1;
+  plan->tile_m = 16 * plan->shape;
+  plan->n_row_tiles = (R + plan->tile_m - 1) / plan->tile_m;
+  plan->chunk_len = kWholePrefix;
+  const int priv = plan->tile_m + d->branch_len < d->gamma * d->branch_len ? plan->tile_m + d->branch_len : d->gamma * d->branch_len;
+  plan->last_short = (priv + 63) / 64;
+  if (!f32 && d->kv_split_tokens) {
+    plan->chunk_len = d->kv_split_tokens;
+  } else if (!f32) {
+    // microseconds: rounds of workgroups over the slots x (blocks a wavefront walks + start and fold) + the merge; block
+    // times fitted to the figures in attn_f32.hip (head dimension 64, two row blocks: 41 us for 32 blocks)
+    const double t_block = d->head_dim == 64 ? (plan->shape == 2 ? 1.3 : 0.9) : 3.0, t_fixed = 5.0;
+    const int64_t base = (int64_t)d->num_kv_heads * plan->n_row_tiles, slots = (int64_t)num_cus() * (d->head_dim == 64 && plan->shape == 1 ? 2 : 1);
+    const size_t n_rows = (size_t)d->gamma * d->branch_len * d->num_q_heads;
+    double best = 0.0;
+    for (int n = 1; n <= 64; ++n) {
+      const int64_t len = ((max_p + n - 1) / n + 63) / 64 * 64;
+      if (n > 1 && len < 256) break;   // less than a block per wavefront
+      int64_t units = 0;
+      for (int b = 0; b < d->num_requests; ++b) units += n == 1 ? 1 : attn_num_chunks(prefix_lens_host[b], (int)len);
+      const int64_t rounds = (base * units + slots - 1) / slots;
+      const int64_t steps = ((n == 1 ? max_p : len) + 64 * plan->last_short / n + 255) / 256;
+      const double cost = (double)rounds * ((double)steps * t_block + t_fixed) +
+                          (n == 1 ? 0.0 : 4.0 + (double)units * n_rows * (d->head_dim + 2) * 4.0 / 3.0e6);
+      if (n == 1 || cost < best) best = cost, plan->chunk_len = n == 1 ? kWholePrefix : (int)len;
+      if (n > 1 && base * units > 2 * slots) break;
+    }
+  }
+  size_partials(d, prefix_lens_host, plan);
+  if (plan->s_max == 1) plan->part_o_bytes = plan->part_ml_bytes = 0;   // the kernel writes the output itself
+}
+
 // extra: the call carries a drafted chain or pool (nested / tree form)
 la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, bool extra, AttnPlan *plan) {
   la_status st = validate_desc(d);
@@ -115,7 +171,7 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, bool
       d->q_dtype == LA_F32 && d->kv_dtype == LA_F32 && d->branch_kv_dtype == LA_F32 && d->out_dtype == LA_F32;
   if (all_f32) {
     if (d->head_dim != 64 && d->head_dim != 128 && d->head_dim != 256) return LA_ERR_UNSUPPORTED;
-    plan->path = PATH_F32;
+    make_general_plan(d, prefix_lens_host, max_p, true, plan);
     return LA_OK;
   }
   const bool out_ok = d->out_dtype == LA_BF16 || d->out_dtype == LA_F32;
@@ -125,10 +181,10 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, bool
   if (!out_ok || !(bf16_all || fp8_kv)) return LA_ERR_UNSUPPORTED;
   if (d->head_dim != 128) {
     // the MFMA and streaming kernels are written for head dimension 128; 64 and 256 run on the general kernel
-    // (fp32 arithmetic on exactly widened inputs, one wavefront per query row)
+    // (exactly widened inputs, fp32-accurate)
     if (d->head_dim != 64 && d->head_dim != 256) return LA_ERR_UNSUPPORTED;
     if (d->kernel_shape > 0) return LA_ERR_UNSUPPORTED;
-    plan->path = PATH_F32;
+    make_general_plan(d, prefix_lens_host, max_p, false, plan);
     return LA_OK;
   }
   plan->path = PATH_MFMA;
@@ -260,19 +316,9 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, bool
   plan->shape = best_shape;
   plan->tile_m = si.tile_m;
   plan->n_row_tiles = (R + plan->tile_m - 1) / plan->tile_m;
-  const int chunk = best_len;
-  plan->chunk_len = chunk;
+  plan->chunk_len = best_len;
   plan->last_short = best_short;
-  int s_max = 1, total = 0;
-  for (int b = 0; b < d->num_requests; ++b) {
-    const int nc = attn_num_chunks(prefix_lens_host[b], chunk);
-    s_max = nc > s_max ? nc : s_max;
-    total += nc;
-  }
-  plan->s_max = s_max;
-  plan->total_units = total;
-  plan->part_o_bytes = align_up((size_t)d->num_requests * s_max * n_rows * d->head_dim * sizeof(float));
-  plan->part_ml_bytes = align_up((size_t)d->num_requests * s_max * n_rows * 2 * sizeof(float));
+  size_partials(d, prefix_lens_host, plan);
   return LA_OK;
 }
 
@@ -305,7 +351,7 @@ la_status la_verify_attention_workspace(const la_attn_desc *desc, const int32_t 
     la_status st = make_plan(desc, prefix_lens_host, extra != 0, &plan);
     if (extra && st == LA_ERR_UNSUPPORTED) continue;  // a forced shape that only runs flat calls
     if (st != LA_OK) return st;
-    const size_t need = plan.path == PATH_MFMA ? plan.part_o_bytes + plan.part_ml_bytes : 0;
+    const size_t need = plan.part_o_bytes + plan.part_ml_bytes;
     bytes = need > bytes ? need : bytes;
   }
   *bytes_out = bytes;
@@ -365,8 +411,14 @@ static la_status verify_attention(const la_attn_desc *desc, const void *q, const
         if (chain_vis_host[t] < 0 || chain_vis_host[t] > chain_len) return LA_ERR_INVALID_ARG;
     }
   }
-  const size_t need = plan.path == PATH_MFMA ? plan.part_o_bytes + plan.part_ml_bytes : 0;
-  if (need > 0 && (!workspace || workspace_bytes < need)) return LA_ERR_WORKSPACE_TOO_SMALL;
+  const size_t need = plan.part_o_bytes + plan.part_ml_bytes;
+  bool partials = need > 0;
+  if (need > 0 && (!workspace || workspace_bytes < need)) {
+    if (plan.path == PATH_MFMA) return LA_ERR_WORKSPACE_TOO_SMALL;
+    partials = false;   // the general path does without, unsplit
+    plan.chunk_len = kWholePrefix;
+    size_partials(desc, prefix_lens_host, &plan);
+  }
 
   AttnParams p;
   memset(&p, 0, sizeof p);
@@ -387,13 +439,13 @@ static la_status verify_attention(const la_attn_desc *desc, const void *q, const
   p.scale_log2 = desc->softmax_scale * 1.44269504088896340736f;
   hipStream_t stream = (hipStream_t)hip_stream;
 
-  if (plan.path == PATH_F32) return launch_attn_f32(p, stream) == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
-
   p.n_row_tiles = plan.n_row_tiles, p.chunk_len = plan.chunk_len, p.s_max = plan.s_max;
   p.last_short = plan.last_short;
   p.total_units = plan.total_units;
-  p.part_o = (float *)workspace;
-  p.part_ml = (float *)((uint8_t *)workspace + plan.part_o_bytes);
+  if (partials) {
+    p.part_o = (float *)workspace;
+    p.part_ml = (float *)((uint8_t *)workspace + plan.part_o_bytes);
+  }
   if (p.B <= kMaxInlineLens) {
     p.n_inline = p.B;
     for (int b = 0; b < p.B; ++b) {
@@ -407,6 +459,10 @@ static la_status verify_attention(const la_attn_desc *desc, const void *q, const
       rq.inv = rq.n > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint64_t)rq.n) + 1u : 0u;
       if (rq.n > 1024) p.n_inline = 0;
     }
+  }
+  if (plan.path == PATH_F32) {
+    if (launch_attn_f32(p, plan.shape, stream) != hipSuccess) return LA_ERR_LAUNCH;
+    return !partials || launch_attn_merge(p, stream) == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
   }
   const ShapeInfo si = shape_info(plan.shape);
   const hipError_t e =

@@ -7,7 +7,7 @@
 //     lse = ln2 * (M + log2 sum_s w_s l_s).
 // One wavefront owns one output row: lane s < n_s loads (m_s, l_s), the maximum
 // and the denominator are wavefront shuffle reductions, the weights are then
-// broadcast lane by lane while each lane accumulates its two output columns.
+// broadcast lane by lane while each lane accumulates its D / 64 output columns.
 #include "la_internal.hpp"
 
 namespace la {
@@ -16,10 +16,13 @@ namespace {
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
-constexpr int kD = 128;
 constexpr int kWaves = 4;
 
+template <int D>
 __global__ __launch_bounds__(64 * kWaves) void attn_merge_kernel(const AttnParams p) {
+  constexpr int E = D / 64;
+  typedef __attribute__((ext_vector_type(E))) float fvec;
+  typedef __attribute__((ext_vector_type(E))) __bf16 bvec;
   const int lane = threadIdx.x & 63;
   const size_t grow = (size_t)blockIdx.x * kWaves + (threadIdx.x >> 6);  // row over all requests
   if (grow >= (size_t)p.B * p.n_rows) return;
@@ -28,7 +31,8 @@ __global__ __launch_bounds__(64 * kWaves) void attn_merge_kernel(const AttnParam
   const int n_s = attn_num_chunks(p.prefix_lens[b], p.chunk_len);
   const size_t slot0 = (size_t)b * p.s_max;
 
-  float acc0 = 0.f, acc1 = 0.f, m_all = -INFINITY, denom = 0.f;
+  fvec acc = 0.f;
+  float m_all = -INFINITY, denom = 0.f;
   // more than 64 chunks are folded 64 at a time with the usual running rescale
   for (int s0 = 0; s0 < n_s; s0 += 64) {
     const int cnt = min(64, n_s - s0);
@@ -47,61 +51,58 @@ __global__ __launch_bounds__(64 * kWaves) void attn_merge_kernel(const AttnParam
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) wl += __shfl_xor(wl, off);
     const float rescale = __builtin_amdgcn_exp2f(m_all - m_new);  // 0 on the first pass (m_all = -inf)
-    acc0 *= rescale;
-    acc1 *= rescale;
+    acc *= rescale;
     denom = denom * rescale + wl;
     m_all = m_new;
-    const float *po = p.part_o + ((slot0 + s0) * p.n_rows + r) * kD + 2 * lane;
-    const size_t stride = (size_t)p.n_rows * kD;  // between the partials of consecutive chunks
+    const float *po = p.part_o + ((slot0 + s0) * p.n_rows + r) * D + E * lane;
+    const size_t stride = (size_t)p.n_rows * D;  // between the partials of consecutive chunks
     // with many chunks this loop is bound by the latency of its loads, so a whole group of 32 partial rows is
-    // requested before the first is used (64 registers)
+    // requested before the first is used (64 registers; 16 rows at head dimension 256)
+    constexpr int kGroup = E > 2 ? 16 : 32;
 #pragma unroll 1
-    for (int g = 0; g < cnt; g += 32) {
-      f32x2 o[32];
+    for (int g = 0; g < cnt; g += kGroup) {
+      fvec o[kGroup];
 #pragma unroll
-      for (int j = 0; j < 32; ++j) {
+      for (int j = 0; j < kGroup; ++j) {
         const int sj = g + j < cnt ? g + j : cnt - 1;   // surplus slots repeat the last chunk with weight zero
-        o[j] = *(const f32x2 *)(po + (size_t)sj * stride);
+        o[j] = *(const fvec *)(po + (size_t)sj * stride);
       }
 #pragma unroll
-      for (int j = 0; j < 32; ++j) {
+      for (int j = 0; j < kGroup; ++j) {
         const float ws = g + j < cnt ? __shfl(w, g + j) : 0.f;
-        acc0 = __builtin_fmaf(ws, o[j].x, acc0);
-        acc1 = __builtin_fmaf(ws, o[j].y, acc1);
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] = __builtin_fmaf(ws, o[j][e], acc[e]);
       }
     }
   }
-  const float inv = 1.0f / denom;
-  acc0 *= inv;
-  acc1 *= inv;
-  const size_t orow = grow * kD + 2 * lane;
-  if (p.out_f32) {
-    f32x2 v = {acc0, acc1};
-    *(f32x2 *)((float *)p.out + orow) = v;
-  } else {
-    f32x2 v = {acc0, acc1};
-    *(bf16x2 *)((__bf16 *)p.out + orow) = __builtin_convertvector(v, bf16x2);
-  }
+  acc *= 1.0f / denom;
+  const size_t orow = grow * D + E * lane;
+  if (p.out_f32)
+    *(fvec *)((float *)p.out + orow) = acc;
+  else
+    *(bvec *)((__bf16 *)p.out + orow) = __builtin_convertvector(acc, bvec);
   if (p.lse && lane == 0) p.lse[grow] = 0.69314718055994530942f * (m_all + __builtin_log2f(denom));
 }
 
-// Few chunks (at most kFew per request), the usual case with many query rows: 32 threads own one row, four output
+// Few chunks (at most kFew per request), the usual case with many query rows: D / 4 threads own one row, four output
 // columns each.  Every thread forms the weights of its row itself (the (m, l) pairs are one broadcast load each) and
 // has all its 16-byte partial loads in flight at once; nothing is exchanged between lanes.
 constexpr int kFew = 8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 
+template <int D>
 __global__ __launch_bounds__(256) void attn_merge_few_kernel(const AttnParams p) {
-  const size_t grow = (size_t)blockIdx.x * 8 + (threadIdx.x >> 5);  // row over all requests
+  constexpr int kPerRow = D / 4;
+  const size_t grow = (size_t)blockIdx.x * (256 / kPerRow) + threadIdx.x / kPerRow;  // row over all requests
   if (grow >= (size_t)p.B * p.n_rows) return;
-  const int col = (threadIdx.x & 31) * 4;
+  const int col = (threadIdx.x % kPerRow) * 4;
   const int b = (int)(grow / p.n_rows);
   const int r = (int)(grow % p.n_rows);
   const int n_s = attn_num_chunks(p.prefix_lens[b], p.chunk_len);  // <= kFew (checked by the host)
   const size_t slot0 = (size_t)b * p.s_max;
-  const size_t stride = (size_t)p.n_rows * kD;
-  const float *po = p.part_o + (slot0 * p.n_rows + r) * kD + col;
+  const size_t stride = (size_t)p.n_rows * D;
+  const float *po = p.part_o + (slot0 * p.n_rows + r) * D + col;
   const float *pml = p.part_ml + (slot0 * p.n_rows + r) * 2;
 
   f32x4 o[kFew];
@@ -127,7 +128,7 @@ __global__ __launch_bounds__(256) void attn_merge_few_kernel(const AttnParams p)
   }
   const float inv = 1.0f / denom;
   acc *= inv;
-  const size_t orow = grow * kD + col;
+  const size_t orow = grow * D + col;
   if (p.out_f32)
     *(f32x4 *)((float *)p.out + orow) = acc;
   else
@@ -135,18 +136,28 @@ __global__ __launch_bounds__(256) void attn_merge_few_kernel(const AttnParams p)
   if (p.lse && col == 0) p.lse[grow] = 0.69314718055994530942f * (m_all + __builtin_log2f(denom));
 }
 
+template <int D>
+hipError_t launch_merge(const AttnParams &p, hipStream_t stream) {
+  const size_t rows = (size_t)p.B * p.n_rows;
+  if (p.s_max <= kFew) {
+    constexpr int kRows = 256 / (D / 4);
+    hipLaunchKernelGGL(attn_merge_few_kernel<D>, dim3((unsigned)((rows + kRows - 1) / kRows)), dim3(256), 0, stream, p);
+  } else {
+    hipLaunchKernelGGL(attn_merge_kernel<D>, dim3((unsigned)((rows + kWaves - 1) / kWaves)), dim3(64 * kWaves), 0, stream, p);
+  }
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_attn_merge(const AttnParams &p, hipStream_t stream) {
   ProfileScope scope(SLOT_ATTN_MERGE, stream);
-  const size_t rows = (size_t)p.B * p.n_rows;
-  if (p.s_max <= kFew) {
-    hipLaunchKernelGGL(attn_merge_few_kernel, dim3((unsigned)((rows + 7) / 8)), dim3(256), 0, stream, p);
-    return hipGetLastError();
+  switch (p.D) {
+    case 64: return launch_merge<64>(p, stream);
+    case 128: return launch_merge<128>(p, stream);
+    case 256: return launch_merge<256>(p, stream);
   }
-  const int grid = (int)((rows + kWaves - 1) / kWaves);
-  hipLaunchKernelGGL(attn_merge_kernel, dim3(grid), dim3(64 * kWaves), 0, stream, p);
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 }  // namespace la

@@ -119,7 +119,8 @@ int attn_stream_max_chunk_blocks();
 bool attn_stream_shape_is_fp8(int shape);  // else: bf16 cache and branch K/V
 hipError_t launch_attn_stream(const AttnParams &p, int shape, hipStream_t stream);
 hipError_t launch_attn_merge(const AttnParams &p, hipStream_t stream);
-hipError_t launch_attn_f32(const AttnParams &p, hipStream_t stream);
+// row_blocks: blocks of 16 query rows per workgroup (p.n_row_tiles counts those workgroups)
+hipError_t launch_attn_f32(const AttnParams &p, int row_blocks, hipStream_t stream);
 
 // ----------------------------------------------------------------------------
 // Speculative accept / resample.

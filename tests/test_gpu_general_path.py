@@ -1,0 +1,58 @@
+"""The general attention path (fp32 tensors; bf16 / fp8 storage at head dimensions 64 and 256) at the edges of its tiles:
+row blocks of 16 and 32, key blocks of 16 and 32, chunks, with and without the optional workspace."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import attn_desc, row_errors, upload_attention
+from paper_2506_19830_amd import binding as B
+from paper_2506_19830_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+BF16, FP8 = ("bf16", "bf16", "bf16"), ("bf16", "fp8_e4m3", "fp8_e4m3")
+MIXED, F32 = ("bf16", "fp8_e4m3", "bf16"), ("f32", "f32", "f32")
+
+
+def _case(name, prefix, gamma, L, hq, hkv, d, storage, out="f32", **kw):
+    return W.AttnCase(name, prefix, gamma, L, hq, hkv, d, *storage, out, seed=len(name) + d, **kw)
+
+
+CASES = [
+    _case("rows_16", (31,), 2, 8, 2, 2, 64, BF16),                        # one full row block, a partial key block
+    _case("rows_17", (32,), 1, 17, 1, 1, 64, BF16),                       # two row blocks, the second nearly empty
+    _case("rows_33_chunks", (700, 0, 65), 3, 11, 2, 2, 64, BF16, paged=True),
+    _case("split_small_block", (2049,), 1, 1, 4, 1, 64, FP8, paged=True),
+    _case("split_large_block", (1537, 300), 2, 3, 4, 2, 64, FP8, paged=True, block_size=64),
+    _case("mixed_chunks", (1100,), 2, 9, 5, 1, 64, MIXED, paged=True),
+    _case("wide_chunks", (1025,), 1, 3, 4, 2, 256, BF16, paged=True, block_size=32),
+    _case("wide_fp8", (900, 16), 2, 9, 2, 1, 256, FP8),
+    _case("wide_mixed", (513,), 1, 33, 1, 1, 256, MIXED, paged=True),
+    _case("f32_15", (15,), 1, 15, 1, 1, 64, F32),
+    _case("f32_d128", (257, 16), 2, 5, 4, 2, 128, F32, paged=True),
+    _case("f32_d256", (33,), 2, 17, 2, 1, 256, F32),
+]
+
+
+@pytest.mark.parametrize("split", [0, 64, 320])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: c.name)
+def test_general_path_edges(oracle, case, split):
+    """Against the fp64 oracle at the fp32 bar of the path (1e-5 of a row's largest element): operands are exact, sums
+    fp32 over at most 2100 keys.  The unsplit result (no workspace) and the split one are both checked."""
+    inp = W.make_attention_inputs(case)
+    dev = upload_attention(case, inp)
+    desc = attn_desc(case, split)
+    lens = [int(x) for x in inp["prefix_lens"]]
+    ref, ref_lse = oracle.verify_attention(**inp, q_dtype=case.q_dtype, kv_dtype=case.kv_dtype,
+                                           branch_kv_dtype=case.branch_kv_dtype, block_size=case.block_size,
+                                           scale=case.scale)
+    size = B.la_verify_attention_workspace(desc, lens)
+    assert size == 0 or case.kv_dtype != "f32"
+    for ws in ([None] if size == 0 else [None, torch.empty(size, dtype=torch.uint8, device="cuda")]):
+        out = B.empty_out(ref.shape, case.out_dtype).fill_(float("nan"))
+        lse = torch.full(ref.shape[:-1], float("nan"), device="cuda")
+        B.la_verify_attention(desc, dev["q"], dev["k_cache"], dev["v_cache"], dev["block_tables"], dev["prefix_lens"], lens,
+                              dev["k_branch"], dev["v_branch"], dev["k_scale"], dev["v_scale"], out, lse, ws)
+        torch.cuda.synchronize()
+        assert row_errors(out.double().cpu().numpy(), ref).max() <= 1e-5
+        assert np.abs(lse.double().cpu().numpy() - ref_lse).max() <= 1e-5
