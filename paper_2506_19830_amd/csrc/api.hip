@@ -194,14 +194,14 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, bool
   const int G = d->num_q_heads / d->num_kv_heads;
   const int R = d->gamma * d->branch_len * G;
   const size_t n_rows = (size_t)d->gamma * d->branch_len * d->num_q_heads;
-  // the streaming shapes exist for flat calls with cache and branch K/V of one storage type
+  // the streaming shapes exist for cache and branch K/V of one storage type
   auto stream_ok = [&](const ShapeInfo &si) {
-    return !extra && plan->kv_fp8 == si.fp8 && plan->br_fp8 == si.fp8 &&
+    return plan->kv_fp8 == si.fp8 && plan->br_fp8 == si.fp8 &&
            (int64_t)d->num_kv_heads * d->block_size * d->head_dim * (si.fp8 ? 1 : 2) < ((int64_t)1 << 32);
   };
   if (d->kernel_shape > 0) {
     const ShapeInfo forced = shape_info(d->kernel_shape - 1);
-    if (forced.stream && !stream_ok(forced)) return LA_ERR_UNSUPPORTED;
+    if (forced.stream && (extra || !stream_ok(forced))) return LA_ERR_UNSUPPORTED;  // (forcing one: flat calls only)
   }
 
   // Choose the kernel shape and the number of chunks that minimise a simple cost model (microseconds, constants
@@ -322,6 +322,22 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, bool
   return LA_OK;
 }
 
+// A chain or pool of drafted tokens is reduced by the last chunk's workgroups too: deal them that many tiles less of
+// the prefix.  The number of chunks, and with it the workspace, does not depend on this (the workspace query does not
+// know the chain's length).  tokens: the longest part any branch sees.  A forced shape keeps the flat call's chunk
+// ranges, so that forms compared under it sum in the same order.
+void count_extra_tiles(const la_attn_desc *d, int64_t tokens, AttnPlan *plan) {
+  if (plan->path != PATH_MFMA || tokens <= 0 || d->kernel_shape > 0) return;
+  const ShapeInfo si = shape_info(plan->shape);
+  const int64_t tiles = (tokens + 63) / 64, step_tiles = si.step_keys / 64;
+  // the block ids of the longest chunk have to fit the kernel's table (make_plan's bound, with the tiles added here)
+  const int64_t cap = si.stream ? attn_stream_max_chunk_blocks() : attn_mfma_max_chunk_blocks();
+  const int64_t most = ((cap - 2) * d->block_size - plan->chunk_len) / 64 - 2;
+  int64_t ls = plan->last_short + (si.stream ? step_tiles * ((tiles + step_tiles - 1) / step_tiles) : 3 * tiles);
+  ls = ls < most ? ls : most;
+  if (ls > plan->last_short) plan->last_short = (int)ls;
+}
+
 }  // namespace
 
 }  // namespace la
@@ -411,6 +427,11 @@ static la_status verify_attention(const la_attn_desc *desc, const void *q, const
         if (chain_vis_host[t] < 0 || chain_vis_host[t] > chain_len) return LA_ERR_INVALID_ARG;
     }
   }
+  int64_t seen = tree ? chain_len : 0;
+  if (chain_len > 0 && !tree)
+    for (int64_t t = 0; t < (int64_t)desc->num_requests * desc->gamma; ++t)
+      seen = chain_vis_host[t] > seen ? chain_vis_host[t] : seen;
+  count_extra_tiles(desc, seen, &plan);
   const size_t need = plan.part_o_bytes + plan.part_ml_bytes;
   bool partials = need > 0;
   if (need > 0 && (!workspace || workspace_bytes < need)) {

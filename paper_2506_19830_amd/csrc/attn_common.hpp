@@ -69,7 +69,7 @@ struct RowState {
   int tile_seg;
 };
 
-enum MaskMode { MASK_NONE = 0, MASK_TAIL = 1, MASK_BRANCH = 2, MASK_TREE = 3 };
+enum MaskMode { MASK_NONE = 0, MASK_TAIL = 1, MASK_BRANCH = 2, MASK_TREE = 3, MASK_BITS = 4 };
 
 // sched_group_barrier masks
 constexpr int kSgMfma = 0x008, kSgValu = 0x002, kSgSalu = 0x004, kSgVmemRead = 0x020, kSgDsRead = 0x100;
@@ -106,7 +106,36 @@ __device__ __forceinline__ void mask_block(f32x16 (&s)[RB], const RowState<RB> &
       for (int rb = 0; rb < RB; ++rb)
         if (past || !((st.row_mask[rb] >> seg) & 1)) s[rb][j] = -INFINITY;
     }
+  } else if constexpr (MASK == MASK_BITS) {  // row_mask holds one bit per key of the tile (visible_keys)
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const uint32_t w = (uint32_t)(st.row_mask[rb] >> (kb * 32)) >> (lh * 4);
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+        if (!((w >> ((j >> 2) * 8 + (j & 3))) & 1)) s[rb][j] = -INFINITY;
+    }
   }
+}
+
+// Bits lo .. hi - 1 of a tile's 64 keys.
+__device__ __forceinline__ uint64_t key_range(int lo, int hi) {
+  auto upto = [](int n) { return n <= 0 ? 0ull : n >= 64 ? ~0ull : (1ull << n) - 1; };
+  return upto(hi) & ~upto(lo);
+}
+
+// Which keys of a 64-token pool tile a row sees, one bit per key.  seg: lane k's is the segment of key k (valid: the
+// token exists); seen: the segments of the row's branch.  One round per segment that occurs in the tile -- a node of
+// the draft tree usually fills a good part of one --, so the masks of a tile cost a few dozen instructions instead of
+// two lane reads and a 64-bit shift per score register.
+__device__ __forceinline__ uint64_t visible_keys(int seg, bool valid, uint64_t seen) {
+  uint64_t left = __builtin_amdgcn_ballot_w64(valid), keys = 0;
+  while (left) {
+    const int s = __builtin_amdgcn_readlane(seg, __builtin_ctzll(left));
+    const uint64_t same = __builtin_amdgcn_ballot_w64(seg == s) & left;
+    if ((seen >> s) & 1) keys |= same;
+    left &= ~same;
+  }
+  return keys;
 }
 
 // Absolute maximum (log2 units) of one 32-key block per row.  The scores arrive as x with absolute value

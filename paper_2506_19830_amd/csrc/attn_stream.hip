@@ -438,6 +438,7 @@ struct StreamLoader {
   int first_lb, ident, shift, bs_mask;
   uint32_t blk_stride, br_stride;  // bytes between cache blocks / between branch tokens
   const uint8_t *k_pre, *v_pre, *k_br, *v_br;
+  const uint8_t *k_ex, *v_ex;    // drafted chain / pool (nested and tree forms), laid out like the branch tokens
   int key[IPW], goff[IPW];       // per lane: key inside the tile, byte offset inside the key row
   const int32_t *table;          // global: the request's block table (paged), or null
   uint32_t row_off;              // per lane: byte offset of its key row inside the G::kRows rows of a load
@@ -500,7 +501,44 @@ struct StreamLoader {
       load_lds16(src, stage + tile * G::kTile + half * G::kHalf + r * 1024);
     }
   }
+  // A step behind the prefix of the nested and tree forms: tiles t0 .. of the sequence (n_priv branch-private tiles,
+  // then those of the chain / pool), so that a step of several tiles may hold both kinds.  Tokens past a segment's end
+  // repeat its last one, also in the tile slots behind the sequence.
+  __device__ __forceinline__ void issue_post(int slot, int t0, int n_priv, int ext_last, int tk0, int t_hi) const {
+    const uint32_t stage = ring + slot * (KSL * G::kTile);
+#pragma unroll
+    for (int j = 0; j < IPW; ++j) {
+      const int ii = wave * IPW + j;
+      const int tile = ii / (2 * G::kLoadsPerHalf), half = (ii / G::kLoadsPerHalf) & 1, r = ii % G::kLoadsPerHalf;
+      const int t = t0 + tile;
+      const bool ext = t >= n_priv && ext_last >= 0;
+      const int tok = min((ext ? (t - n_priv) * kTileN : tk0 + t * kTileN) + key[j], ext ? ext_last : t_hi);
+      // (wavefront-uniform selections between values, not between the members' addresses)
+      const uint64_t ex = half ? (uint64_t)v_ex : (uint64_t)k_ex, br = half ? (uint64_t)v_br : (uint64_t)k_br;
+      const uint8_t *src = (const uint8_t *)((ext ? ex : br) + ((uint64_t)(uint32_t)tok * br_stride + (uint32_t)goff[j]));
+      load_lds16(src, stage + tile * G::kTile + half * G::kHalf + r * 1024);
+    }
+  }
 };
+
+// The chain / pool tiles a workgroup reduces after its branch-private tiles (nested and tree forms, last chunk only):
+// how many, and the last token a load may touch (-1: none).  Wavefront-uniform, from scalar loads.
+struct ExtraTiles {
+  int n, last;
+};
+template <int EXTRA>
+__device__ __forceinline__ ExtraTiles extra_tiles(const AttnParams &p, int b, int t_lo, int t_hi, bool last_chunk) {
+  int tokens = 0;
+  if (EXTRA == 1 && last_chunk) {  // the longest visible part among the branches of this row tile
+    typedef const __attribute__((address_space(4))) int32_t *cint_ptr;
+    const cint_ptr vis = (cint_ptr)(uintptr_t)(p.chain_vis + (size_t)b * p.gamma);
+    const int g1 = t_hi / p.L;
+    for (int g = t_lo / p.L; g <= g1; ++g) tokens = max(tokens, (int)vis[__builtin_amdgcn_readfirstlane(g)]);
+  }
+  if (EXTRA == 2 && last_chunk) tokens = p.C;
+  tokens = __builtin_amdgcn_readfirstlane(tokens);
+  return {(tokens + kTileN - 1) / kTileN, tokens - 1};
+}
 
 // NRB row blocks of 32 rows per workgroup; KSL = 8/NRB tiles per pipeline step; a ring of kSlots tile slots behind
 // the Q fragments.
@@ -524,7 +562,8 @@ struct StreamShape {
 
 // The work of one workgroup.  GENERAL: every tile in the general form (the second attempt; see stream_tile_fast).
 // Returns false if this attempt gave up (nothing has been written then).
-template <int NRB, bool GENERAL>
+// EXTRA: 0 = flat call, 1 = nested form (drafted chain), 2 = tree form (pool of drafted tokens, segment masks).
+template <int NRB, int EXTRA, bool GENERAL>
 __device__ __forceinline__ bool stream_chunk(const AttnParams &p, uint8_t *lds, int thread_id, int block_id) {
   using S = StreamShape<NRB>;
   constexpr int KSL = S::KSL, NST = S::NST, IPW = S::IPW;
@@ -558,7 +597,8 @@ __device__ __forceinline__ bool stream_chunk(const AttnParams &p, uint8_t *lds, 
   const int t_lo = __builtin_amdgcn_readfirstlane(r0 / p.G), t_hi = __builtin_amdgcn_readfirstlane((r1 - 1) / p.G);
   const int tk0 = __builtin_amdgcn_readfirstlane((t_lo / p.L) * p.L);
   const int n_priv = (c == n_chunks - 1) ? (t_hi - tk0 + 1 + kTileN - 1) / kTileN : 0;
-  const int n_steps = n_pre_steps + (n_priv + KSL - 1) / KSL;
+  const ExtraTiles ext = extra_tiles<EXTRA>(p, b, t_lo, t_hi, c == n_chunks - 1);
+  const int n_steps = n_pre_steps + (ext.n + n_priv + KSL - 1) / KSL;
 
   // ---- physical block ids of this chunk -> LDS (paged caches only) ------------------------------
   int32_t *blk_lds = (int32_t *)(lds + S::kBlkOff);
@@ -600,6 +640,11 @@ __device__ __forceinline__ bool stream_chunk(const AttnParams &p, uint8_t *lds, 
   ld.v_pre = (const uint8_t *)p.v_cache + ((size_t)kvh << p.block_shift) * kRowBytes;
   ld.k_br = (const uint8_t *)p.k_branch + br_off;
   ld.v_br = (const uint8_t *)p.v_branch + br_off;
+  if constexpr (EXTRA != 0) {
+    const size_t ex_off = ((size_t)b * p.C * p.Hkv + kvh) * kRowBytes;
+    ld.k_ex = (const uint8_t *)p.k_chain + ex_off;
+    ld.v_ex = (const uint8_t *)p.v_chain + ex_off;
+  }
   ld.init_lane(lane);
   auto issue = [&](int step) __attribute__((always_inline)) {
     const int slot = step % NST;
@@ -607,6 +652,8 @@ __device__ __forceinline__ bool stream_chunk(const AttnParams &p, uint8_t *lds, 
       ld.template issue<true, false>(slot, k_begin + step * (KSL * kTileN), 0);
     else if (step < n_pre_steps)
       ld.template issue<true, true>(slot, k_begin + step * (KSL * kTileN), k_end - 1);
+    else if constexpr (EXTRA != 0)
+      ld.issue_post(slot, (step - n_pre_steps) * KSL, n_priv, ext.last, tk0, t_hi);
     else
       ld.template issue<false, true>(slot, tk0 + (step - n_pre_steps) * (KSL * kTileN), t_hi);
   };
@@ -731,6 +778,10 @@ __device__ __forceinline__ bool stream_chunk(const AttnParams &p, uint8_t *lds, 
                          give_up);
     }
   }
+  int row_vis = 0;  // nested form: chain tokens the row's branch sees
+  if (EXTRA == 1 && ext.n > 0) row_vis = p.chain_vis[b * p.gamma + row_tok / p.L];
+  uint64_t row_seen = 0;  // tree form: segments the row's branch sees
+  if (EXTRA == 2 && ext.n > 0) row_seen = p.seg_mask[b * p.gamma + row_tok / p.L];
   for (; step < n_steps; ++step) {
     // own loads of this step have landed (the steps issued after it may still be in flight) ...
     wait_later<IPW, NST - 2>(min(n_steps - 1, step + NST - 2) - step);
@@ -739,25 +790,35 @@ __device__ __forceinline__ bool stream_chunk(const AttnParams &p, uint8_t *lds, 
     if (step + NST - 1 < n_steps) issue(step + NST - 1);
     if (!active) continue;
     const uint8_t *kt = lds + S::kRingOff + (step % NST) * kStepBytes + ks * kTileBytes;
+    // Every masked tile -- the prefix's tail, the branch's own tokens, the chain / pool -- as a bit per key, through
+    // one instance of the tile: with an instance per kind the bf16 shapes spill hundreds of registers.
+    const int t = (step - n_pre_steps) * KSL + ks;
+    uint64_t keys = 0;
     if (step < n_pre_steps) {
-      const int first = k_begin + (step * KSL + ks) * kTileN;
-      if constexpr (GENERAL) {
-        if (first < k_end) stream_tile_lean<MASK_TAIL>(kt, qfrag, qscale, st, koff, voff, lh, first, k_end);
-      } else {
-        if (first + kTileN <= k_end)
-          stream_tile_fast(kt, qfrag, qscale, st, koff, voff, give_up);
-        else if (first < k_end)
-          stream_tile<MASK_TAIL>(kt, qfrag, qscale, st, koff, voff, lh, first, k_end);
+      const int left = k_end - (k_begin + (step * KSL + ks) * kTileN);
+      if (!GENERAL && KSL > 1 && left >= kTileN) {  // a full tile of a step that is not full
+        stream_tile_fast(kt, qfrag, qscale, st, koff, voff, give_up);
+        continue;
       }
-    } else {
-      const int first = tk0 + ((step - n_pre_steps) * KSL + ks) * kTileN;
-      if (first <= t_hi) {
-        if constexpr (GENERAL)
-          stream_tile_lean<MASK_BRANCH>(kt, qfrag, qscale, st, koff, voff, lh, first, 0);
-        else
-          stream_tile<MASK_BRANCH>(kt, qfrag, qscale, st, koff, voff, lh, first, 0);
+      keys = key_range(0, left);
+    } else if (t < n_priv) {
+      const int first = tk0 + t * kTileN;
+      keys = key_range((row_tok / p.L) * p.L - first, row_tok + 1 - first);
+    } else if (t < n_priv + ext.n) {
+      const int first = (t - n_priv) * kTileN;
+      if constexpr (EXTRA < 2) {  // branch g sees chain tokens 0 .. vis - 1
+        keys = key_range(0, row_vis - first);
+      } else {
+        const int seg = p.pool_seg[(size_t)b * p.C + min(first + lane, ext.last)];
+        keys = visible_keys(seg, first + lane <= ext.last, row_seen);
       }
     }
+    if (__builtin_amdgcn_ballot_w64(keys != 0) == 0) continue;  // no row of the wavefront sees anything of the tile
+    st.row_mask[0] = keys;
+    if constexpr (GENERAL)
+      stream_tile_lean<MASK_BITS>(kt, qfrag, qscale, st, koff, voff, lh, 0, 0);
+    else
+      stream_tile<MASK_BITS>(kt, qfrag, qscale, st, koff, voff, lh, 0, 0);
   }
   wait_vmcnt<0>();  // no direct load may still be on its way to LDS when the workgroup gives its LDS back
   if constexpr (!GENERAL) {
@@ -842,16 +903,16 @@ __device__ __forceinline__ bool stream_chunk(const AttnParams &p, uint8_t *lds, 
   return true;
 }
 
-template <int NRB>
+template <int NRB, int EXTRA>
 __global__ __launch_bounds__(64 * kWaves) void attn_stream_kernel(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  if (__builtin_expect(!stream_chunk<NRB, false>(p, lds, threadIdx.x, blockIdx.x), 0)) {
+  if (__builtin_expect(!stream_chunk<NRB, EXTRA, false>(p, lds, threadIdx.x, blockIdx.x), 0)) {
     // The second attempt starts from the kernel's arguments again, and from thread and workgroup ids the compiler
     // cannot see through: whatever it shared between the two attempts stayed alive across the first one, in private
     // memory (a kernel that uses private memory at all streams a tenth slower at few rows).
     int thread_id = threadIdx.x, block_id = blockIdx.x;
     asm volatile("" : "+v"(thread_id), "+s"(block_id));
-    stream_chunk<NRB, true>(p, lds, thread_id, block_id);
+    stream_chunk<NRB, EXTRA, true>(p, lds, thread_id, block_id);
   }
 }
 
@@ -1020,7 +1081,7 @@ struct Stream16Shape {
 };
 
 // The work of one workgroup; GENERAL: the second attempt, every tile in the general form (see stream_chunk).
-template <int NRB, bool GENERAL>
+template <int NRB, int EXTRA, bool GENERAL>
 __device__ __forceinline__ bool stream16_chunk(const AttnParams &p, uint8_t *lds, int thread_id, int block_id) {
   using S = Stream16Shape<NRB>;
   using G = Geo<false>;
@@ -1049,18 +1110,19 @@ __device__ __forceinline__ bool stream16_chunk(const AttnParams &p, uint8_t *lds
   const int t_lo = __builtin_amdgcn_readfirstlane(r0 / p.G), t_hi = __builtin_amdgcn_readfirstlane((r1 - 1) / p.G);
   const int tk0 = __builtin_amdgcn_readfirstlane((t_lo / p.L) * p.L);
   const int n_priv = (c == n_chunks - 1) ? (t_hi - tk0 + 1 + kTileN - 1) / kTileN : 0;
-  const int n_steps = n_pre_steps + (n_priv + KSL - 1) / KSL;
+  const ExtraTiles ext = extra_tiles<EXTRA>(p, b, t_lo, t_hi, c == n_chunks - 1);
+  const int n_steps = n_pre_steps + (ext.n + n_priv + KSL - 1) / KSL;
 
   // ---- Q -> registers (before the stream starts, so that the only vector memory operations in flight later are
   //      the direct loads the kernel counts itself), times the score scale in log2 units, rounded to bf16 again
   RowState<1> st;
   const int row = r0 + rb * 32 + ln;
+  const int rr = min(row, p.R - 1), row_tok = rr / p.G;
   {
-    const int rr = min(row, p.R - 1);
-    st.row_tok[0] = rr / p.G;
-    st.row_bstart[0] = (st.row_tok[0] / p.L) * p.L;
+    st.row_tok[0] = row_tok;
+    st.row_bstart[0] = (row_tok / p.L) * p.L;
     const uint8_t *qrow =
-        (const uint8_t *)p.q + (((size_t)b * gl + st.row_tok[0]) * p.Hq + kvh * p.G + (rr % p.G)) * (size_t)(kD * 2);
+        (const uint8_t *)p.q + (((size_t)b * gl + row_tok) * p.Hq + kvh * p.G + (rr % p.G)) * (size_t)(kD * 2);
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       u32x4 v = *(const u32x4 *)(qrow + (16 * t + 8 * lh) * 2);
@@ -1103,6 +1165,11 @@ __device__ __forceinline__ bool stream16_chunk(const AttnParams &p, uint8_t *lds
   ld.v_pre = (const uint8_t *)p.v_cache + ((size_t)kvh << p.block_shift) * G::kRow;
   ld.k_br = (const uint8_t *)p.k_branch + br_off;
   ld.v_br = (const uint8_t *)p.v_branch + br_off;
+  if constexpr (EXTRA != 0) {
+    const size_t ex_off = ((size_t)b * p.C * p.Hkv + kvh) * G::kRow;
+    ld.k_ex = (const uint8_t *)p.k_chain + ex_off;
+    ld.v_ex = (const uint8_t *)p.v_chain + ex_off;
+  }
   ld.init_lane(lane);
   auto issue = [&](int step) __attribute__((always_inline)) {
     const int slot = step % NST;
@@ -1110,6 +1177,8 @@ __device__ __forceinline__ bool stream16_chunk(const AttnParams &p, uint8_t *lds
       ld.template issue<true, false>(slot, k_begin + step * (KSL * kTileN), 0);
     else if (step < n_pre_steps)
       ld.template issue<true, true>(slot, k_begin + step * (KSL * kTileN), k_end - 1);
+    else if constexpr (EXTRA != 0)
+      ld.issue_post(slot, (step - n_pre_steps) * KSL, n_priv, ext.last, tk0, t_hi);
     else
       ld.template issue<false, true>(slot, tk0 + (step - n_pre_steps) * (KSL * kTileN), t_hi);
   };
@@ -1143,31 +1212,45 @@ __device__ __forceinline__ bool stream16_chunk(const AttnParams &p, uint8_t *lds
         stream_tile16<MASK_NONE, true>(lds + (step % NST) * kStepBytes + ks * G::kTile, st, koff0, voff, lh, 0, 0, give_up);
     }
   }
+  int row_vis = 0;  // nested form: chain tokens the row's branch sees
+  if (EXTRA == 1 && ext.n > 0) row_vis = p.chain_vis[b * p.gamma + row_tok / p.L];
+  uint64_t row_seen = 0;  // tree form: segments the row's branch sees
+  if (EXTRA == 2 && ext.n > 0) row_seen = p.seg_mask[b * p.gamma + row_tok / p.L];
   for (; step < n_steps; ++step) {
     wait_later<IPW, NST - 2>(min(n_steps - 1, step + NST - 2) - step);
     __builtin_amdgcn_s_barrier();
     if (step + NST - 1 < n_steps) issue(step + NST - 1);
     if (!active) continue;
     const uint8_t *kt = lds + (step % NST) * kStepBytes + ks * G::kTile;
+    // Every masked tile -- the prefix's tail, the branch's own tokens, the chain / pool -- as a bit per key, through
+    // one instance of the tile: with an instance per kind the bf16 shapes spill hundreds of registers.
+    const int t = (step - n_pre_steps) * KSL + ks;
+    uint64_t keys = 0;
     if (step < n_pre_steps) {
-      const int first = k_begin + (step * KSL + ks) * kTileN;
-      if constexpr (GENERAL) {
-        if (first < k_end) stream_tile16_lean<MASK_TAIL>(kt, st, koff0, voff, lh, first, k_end);
-      } else {
-        if (first + kTileN <= k_end)
-          stream_tile16<MASK_NONE, true>(kt, st, koff0, voff, lh, 0, 0, give_up);
-        else if (first < k_end)
-          stream_tile16<MASK_TAIL>(kt, st, koff0, voff, lh, first, k_end);
+      const int left = k_end - (k_begin + (step * KSL + ks) * kTileN);
+      if (!GENERAL && KSL > 1 && left >= kTileN) {  // a full tile of a step that is not full
+        stream_tile16<MASK_NONE, true>(kt, st, koff0, voff, lh, 0, 0, give_up);
+        continue;
       }
-    } else {
-      const int first = tk0 + ((step - n_pre_steps) * KSL + ks) * kTileN;
-      if (first <= t_hi) {
-        if constexpr (GENERAL)
-          stream_tile16_lean<MASK_BRANCH>(kt, st, koff0, voff, lh, first, 0);
-        else
-          stream_tile16<MASK_BRANCH>(kt, st, koff0, voff, lh, first, 0);
+      keys = key_range(0, left);
+    } else if (t < n_priv) {
+      const int first = tk0 + t * kTileN;
+      keys = key_range((row_tok / p.L) * p.L - first, row_tok + 1 - first);
+    } else if (t < n_priv + ext.n) {
+      const int first = (t - n_priv) * kTileN;
+      if constexpr (EXTRA < 2) {  // branch g sees chain tokens 0 .. vis - 1
+        keys = key_range(0, row_vis - first);
+      } else {
+        const int seg = p.pool_seg[(size_t)b * p.C + min(first + lane, ext.last)];
+        keys = visible_keys(seg, first + lane <= ext.last, row_seen);
       }
     }
+    if (__builtin_amdgcn_ballot_w64(keys != 0) == 0) continue;  // no row of the wavefront sees anything of the tile
+    st.row_mask[0] = keys;
+    if constexpr (GENERAL)
+      stream_tile16_lean<MASK_BITS>(kt, st, koff0, voff, lh, 0, 0);
+    else
+      stream_tile16<MASK_BITS>(kt, st, koff0, voff, lh, 0, 0);
   }
   wait_vmcnt<0>();  // no direct load may still be on its way to LDS when the workgroup gives its LDS back
   if constexpr (!GENERAL) {
@@ -1177,7 +1260,7 @@ __device__ __forceinline__ bool stream16_chunk(const AttnParams &p, uint8_t *lds
 
   // ---- the partial: one key slice per row block writes its registers, two are folded through LDS first ---------
   const size_t slot = (size_t)b * p.s_max + c;
-  const size_t out_row = slot * p.n_rows + (size_t)st.row_tok[0] * p.Hq + kvh * p.G + (row % p.G);
+  const size_t out_row = slot * p.n_rows + (size_t)row_tok * p.Hq + kvh * p.G + (row % p.G);
   float *po = p.part_o + out_row * kD;
   if constexpr (KSL > 1) {
     __builtin_amdgcn_s_barrier();
@@ -1227,21 +1310,21 @@ __device__ __forceinline__ bool stream16_chunk(const AttnParams &p, uint8_t *lds
   return true;
 }
 
-template <int NRB>
+template <int NRB, int EXTRA>
 __global__ __launch_bounds__(64 * kWaves) void attn_stream16_kernel(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  if (__builtin_expect(!stream16_chunk<NRB, false>(p, lds, threadIdx.x, blockIdx.x), 0)) {
+  if (__builtin_expect(!stream16_chunk<NRB, EXTRA, false>(p, lds, threadIdx.x, blockIdx.x), 0)) {
     int thread_id = threadIdx.x, block_id = blockIdx.x;  // (opaque to the compiler: see attn_stream_kernel)
     asm volatile("" : "+v"(thread_id), "+s"(block_id));
-    stream16_chunk<NRB, true>(p, lds, thread_id, block_id);
+    stream16_chunk<NRB, EXTRA, true>(p, lds, thread_id, block_id);
   }
 }
 
-template <int NRB>
+template <int NRB, int EXTRA>
 hipError_t launch_stream16_variant(const AttnParams &p, hipStream_t stream) {
   using S = Stream16Shape<NRB>;
   const int grid = p.Hkv * p.n_row_tiles * p.total_units;
-  auto kern = attn_stream16_kernel<NRB>;
+  auto kern = attn_stream16_kernel<NRB, EXTRA>;
   const int blk_entries =
       p.block_tables ? (attn_max_chunk_tokens(p.chunk_len, p.last_short) >> p.block_shift) + 2 : 0;
   if (blk_entries > kMaxBlkLds) return hipErrorInvalidValue;
@@ -1258,11 +1341,11 @@ hipError_t launch_stream16_variant(const AttnParams &p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int NRB>
+template <int NRB, int EXTRA>
 hipError_t launch_stream_variant(const AttnParams &p, hipStream_t stream) {
   using S = StreamShape<NRB>;
   const int grid = p.Hkv * p.n_row_tiles * p.total_units;
-  auto kern = attn_stream_kernel<NRB>;
+  auto kern = attn_stream_kernel<NRB, EXTRA>;
   const int blk_entries =
       p.block_tables ? (attn_max_chunk_tokens(p.chunk_len, p.last_short) >> p.block_shift) + 2 : 0;
   if (blk_entries > kMaxBlkLds) return hipErrorInvalidValue;
@@ -1291,16 +1374,24 @@ int attn_stream_step_keys(int shape) { return kTileN * kWaves / kStreamNrb[shape
 int attn_stream_max_chunk_blocks() { return kMaxBlkLds; }
 bool attn_stream_shape_is_fp8(int shape) { return shape < 3; }
 
-hipError_t launch_attn_stream(const AttnParams &p, int shape, hipStream_t stream) {
-  ProfileScope scope(SLOT_ATTN_MFMA, stream);
+namespace {
+template <int EXTRA>
+hipError_t launch_stream_form(const AttnParams &p, int shape, hipStream_t stream) {
   switch (shape) {
-    case 0: return launch_stream_variant<2>(p, stream);
-    case 1: return launch_stream_variant<4>(p, stream);
-    case 2: return launch_stream_variant<8>(p, stream);
-    case 3: return launch_stream16_variant<8>(p, stream);
-    case 4: return launch_stream16_variant<4>(p, stream);
+    case 0: return launch_stream_variant<2, EXTRA>(p, stream);
+    case 1: return launch_stream_variant<4, EXTRA>(p, stream);
+    case 2: return launch_stream_variant<8, EXTRA>(p, stream);
+    case 3: return launch_stream16_variant<8, EXTRA>(p, stream);
+    case 4: return launch_stream16_variant<4, EXTRA>(p, stream);
   }
   return hipErrorInvalidValue;
+}
+}  // namespace
+
+hipError_t launch_attn_stream(const AttnParams &p, int shape, hipStream_t stream) {
+  ProfileScope scope(SLOT_ATTN_MFMA, stream);
+  if (p.C > 0) return p.pool_seg ? launch_stream_form<2>(p, shape, stream) : launch_stream_form<1>(p, shape, stream);
+  return launch_stream_form<0>(p, shape, stream);
 }
 
 }  // namespace la
