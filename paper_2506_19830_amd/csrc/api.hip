@@ -212,13 +212,18 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, bool
   // A request's key tiles are dealt out evenly over its chunks (attn_chunk_range); the workgroup of the last chunk
   // also runs the branch-private tiles (masked, general form: about three prefix tiles each in the row-tile
   // shapes, whole pipeline steps in the streaming shapes), which count as `last_short` tiles of its share.
+  // With a bf16 cache the row-tile shapes are left to calls that force them (and to block strides the streaming shapes
+  // cannot address): over 45 calls of all forms, 24 to 1400 rows and 300 to 32768 keys, the better of the two bf16
+  // streaming shapes took 0.60 to 1.0 of the better row-tile shape's time (27434 + 12924 + 3678 + 3540 keys, 32 rows:
+  // 41 against 59 us; 8475 + 546 keys, 728 rows: 49 against 66 us).
+  const bool skip_row_tiles = d->kernel_shape == 0 && !plan->kv_fp8 && stream_ok(shape_info(num_shapes() - 1));
   double best_cost = 0.0;
   int best_len = 0, best_shape = -1, best_short = 0;
   const int64_t T = (max_p + 63) / 64;
   for (int shape = 0; shape < num_shapes(); ++shape) {
     if (d->kernel_shape > 0 && shape != d->kernel_shape - 1) continue;
     const ShapeInfo si = shape_info(shape);
-    if (si.stream && !stream_ok(si)) continue;
+    if (si.stream ? !stream_ok(si) : skip_row_tiles) continue;
     const int64_t base_wgs = (int64_t)d->num_kv_heads * ((R + si.tile_m - 1) / si.tile_m);
     const int priv_tokens = si.tile_m / G + d->branch_len < d->gamma * d->branch_len ? si.tile_m / G + d->branch_len
                                                                                      : d->gamma * d->branch_len;
