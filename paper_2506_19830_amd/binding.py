@@ -7,6 +7,7 @@ fallback -- if the library has not been built, loading raises.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 from pathlib import Path
 from typing import Optional, Sequence
@@ -199,6 +200,22 @@ def _host_lens(prefix_lens_host: Sequence[int]):
     return arr
 
 
+def _host_rows(rows):
+    """Nested sequence of ints -> C array of int32, one row after the other.  A tree call passes one label per pool
+    token, so plain ints are converted in C (378 labels: 49 us through a list and a ctypes constructor, 16 us this way);
+    whatever the array type does not take goes the general way."""
+    flat = array.array("i")
+    try:
+        for row in rows:
+            flat.extend(row)
+    except (TypeError, OverflowError):
+        vals = [int(x) for row in rows for x in row]
+        return (ctypes.c_int32 * max(1, len(vals)))(*vals)
+    if not flat:
+        return (ctypes.c_int32 * 1)()
+    return (ctypes.c_int32 * len(flat)).from_buffer(flat)
+
+
 def la_verify_attention_workspace(desc: la_attn_desc, prefix_lens_host: Sequence[int]) -> int:
     out = ctypes.c_size_t(0)
     st = load().la_verify_attention_workspace(ctypes.byref(desc), _host_lens(prefix_lens_host), ctypes.byref(out))
@@ -237,8 +254,7 @@ def la_verify_attention_nested(desc: la_attn_desc, q, k_cache, v_cache, block_ta
     [B, gamma] (device int32) / ``chain_vis_host`` (nested sequence of ints, same values)."""
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     C = 0 if k_chain is None else int(k_chain.shape[1])
-    flat = [int(x) for row in chain_vis_host for x in row] if C else []
-    vis_host = (ctypes.c_int32 * max(1, len(flat)))(*flat)
+    vis_host = _host_rows(chain_vis_host if C else [])
     st = load().la_verify_attention_nested(ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache),
                                            _ptr(block_tables), _ptr(prefix_lens), _host_lens(prefix_lens_host),
                                            _ptr(k_branch), _ptr(v_branch), _ptr(k_chain), _ptr(v_chain),
@@ -256,8 +272,7 @@ def la_verify_attention_tree(desc: la_attn_desc, q, k_cache, v_cache, block_tabl
     (device, 64-bit: torch.int64 holding the bit pattern)."""
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     C = 0 if k_pool is None else int(k_pool.shape[1])
-    flat = [int(x) for row in pool_seg_host for x in row] if C else []
-    seg_host = (ctypes.c_int32 * max(1, len(flat)))(*flat)
+    seg_host = _host_rows(pool_seg_host if C else [])
     st = load().la_verify_attention_tree(ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache),
                                          _ptr(block_tables), _ptr(prefix_lens), _host_lens(prefix_lens_host),
                                          _ptr(k_branch), _ptr(v_branch), _ptr(k_pool), _ptr(v_pool),
