@@ -1,0 +1,69 @@
+"""Nested and tree calls on the streaming shapes (fp8 and bf16 caches): chain and pool lengths around a key tile, row
+tiles that straddle branches, prefixes that are empty, shorter than a tile, ragged; both attempts of the kernels."""
+import numpy as np
+import pytest
+
+from paper_2506_19830_amd import workloads as W
+from test_gpu_attention import TOL_LOWP, check_nested, check_tree
+
+pytestmark = pytest.mark.gpu
+
+
+def make_case(kv, prefix, gamma, L, hq, hkv, paged, seed, out="bf16"):
+    return W.AttnCase(f"forms_{kv}_{len(prefix)}", prefix, gamma, L, hq, hkv, 128, "bf16", kv, kv, out, paged=paged,
+                      seed=seed)
+
+
+# (prefixes, gamma, L, Hq, Hkv, paged): 45 rows, 135 rows over two requests, 384 rows (several row tiles of every shape)
+SHAPES = [((700,), 3, 3, 10, 2, True), ((0, 333), 3, 9, 10, 2, False), ((1100,), 4, 12, 16, 2, True),
+          ((5,), 6, 1, 8, 2, False)]
+
+
+def streams(case):
+    from paper_2506_19830_amd import binding as B
+    desc = B.make_attn_desc(num_requests=case.B, num_q_heads=case.Hq, num_kv_heads=case.Hkv, head_dim=case.D,
+                            gamma=case.gamma, branch_len=case.L, block_size=case.block_size,
+                            max_blocks_per_request=case.max_blocks, q_dtype=case.q_dtype, kv_dtype=case.kv_dtype,
+                            branch_kv_dtype=case.branch_kv_dtype, out_dtype=case.out_dtype, softmax_scale=case.scale)
+    return B.la_verify_attention_plan(desc, [int(x) for x in case.prefix_lens], 1)["kernel_shape"] >= 3
+
+
+@pytest.mark.parametrize("kv", ["fp8_e4m3", "bf16"])
+@pytest.mark.parametrize("chain_len", [1, 63, 64, 65, 300])
+@pytest.mark.parametrize("shape", range(len(SHAPES)))
+def test_nested(oracle, kv, chain_len, shape):
+    case = make_case(kv, *SHAPES[shape], seed=300 + shape)
+    assert streams(case)
+    rng = np.random.default_rng(chain_len + shape)
+    vis = rng.integers(0, chain_len + 1, size=(case.B, case.gamma)).astype(np.int32)
+    vis[0, 0], vis[-1, -1] = 0, chain_len                     # one branch sees nothing, one everything
+    for split in (0, 128):
+        check_nested(oracle, case, chain_len, TOL_LOWP, vis, split)
+
+
+@pytest.mark.parametrize("kv", ["fp8_e4m3", "bf16"])
+@pytest.mark.parametrize("width,depth,step_len", [(2, 1, 1), (2, 2, 21), (3, 2, 16), (1, 3, 64)])
+@pytest.mark.parametrize("shape", range(len(SHAPES)))
+def test_tree(oracle, kv, width, depth, step_len, shape):
+    case = make_case(kv, *SHAPES[shape], seed=340 + shape, out="f32" if shape == 1 else "bf16")
+    assert streams(case)
+    for split in (0, 128):
+        check_tree(oracle, case, width, depth, step_len, TOL_LOWP, split)
+
+
+@pytest.mark.parametrize("kv", ["fp8_e4m3", "bf16"])
+@pytest.mark.parametrize("shape", [1, 2])
+def test_second_attempt(oracle, kv, shape):
+    """Every workgroup reduces its chunk again in the general form (a hook of the benchmark library)."""
+    from paper_2506_19830_amd import binding as B
+    case = make_case(kv, *SHAPES[shape], seed=380 + shape)
+    B.select_library("bench")
+    try:
+        B.la_selftest_second_attempt(True)
+        try:
+            check_nested(oracle, case, 130, TOL_LOWP)
+            check_tree(oracle, case, 2, 2, 21, TOL_LOWP)
+        finally:
+            B.la_selftest_second_attempt(False)
+    finally:
+        B.select_library("product")
