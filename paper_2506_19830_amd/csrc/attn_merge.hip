@@ -18,17 +18,27 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
 constexpr int kWaves = 4;
 
-template <int D>
+// The grid is (row groups of a request, requests, batches of kMaxGridY requests), so that no division by the number of
+// rows is needed; the number of partials comes from the kernel arguments where the host has put it there, so that the
+// first loads of a wavefront are the partials themselves.
+constexpr int kMaxGridY = 65535;
+__device__ __forceinline__ int merge_request(const AttnParams &p) { return (int)(blockIdx.y + blockIdx.z * kMaxGridY); }
+__device__ __forceinline__ int merge_chunks(const AttnParams &p, int b) {
+  return p.n_inline ? p.req[b].n : attn_num_chunks(p.prefix_lens[b], p.chunk_len);
+}
+
+// kGroup: partial rows requested before the first is used
+template <int D, int kGroup>
 __global__ __launch_bounds__(64 * kWaves) void attn_merge_kernel(const AttnParams p) {
   constexpr int E = D / 64;
   typedef __attribute__((ext_vector_type(E))) float fvec;
   typedef __attribute__((ext_vector_type(E))) __bf16 bvec;
   const int lane = threadIdx.x & 63;
-  const size_t grow = (size_t)blockIdx.x * kWaves + (threadIdx.x >> 6);  // row over all requests
-  if (grow >= (size_t)p.B * p.n_rows) return;
-  const int b = (int)(grow / p.n_rows);
-  const int r = (int)(grow % p.n_rows);
-  const int n_s = attn_num_chunks(p.prefix_lens[b], p.chunk_len);
+  const int b = merge_request(p);
+  const int r = (int)(blockIdx.x * kWaves + (threadIdx.x >> 6));
+  if (b >= p.B || r >= p.n_rows) return;
+  const size_t grow = (size_t)b * p.n_rows + r;   // row over all requests
+  const int n_s = merge_chunks(p, b);
   const size_t slot0 = (size_t)b * p.s_max;
 
   fvec acc = 0.f;
@@ -56,9 +66,8 @@ __global__ __launch_bounds__(64 * kWaves) void attn_merge_kernel(const AttnParam
     m_all = m_new;
     const float *po = p.part_o + ((slot0 + s0) * p.n_rows + r) * D + E * lane;
     const size_t stride = (size_t)p.n_rows * D;  // between the partials of consecutive chunks
-    // with many chunks this loop is bound by the latency of its loads, so a whole group of 32 partial rows is
-    // requested before the first is used (64 registers; 16 rows at head dimension 256)
-    constexpr int kGroup = E > 2 ? 16 : 32;
+    // with many chunks this loop is bound by the latency of its loads, so a whole group of partial rows is requested
+    // before the first is used (32 rows: 64 registers)
 #pragma unroll 1
     for (int g = 0; g < cnt; g += kGroup) {
       fvec o[kGroup];
@@ -86,20 +95,21 @@ __global__ __launch_bounds__(64 * kWaves) void attn_merge_kernel(const AttnParam
 
 // Few chunks (at most kFew per request), the usual case with many query rows: D / 4 threads own one row, four output
 // columns each.  Every thread forms the weights of its row itself (the (m, l) pairs are one broadcast load each) and
-// has all its 16-byte partial loads in flight at once; nothing is exchanged between lanes.
-constexpr int kFew = 8;
+// has all its 16-byte partial loads in flight at once; nothing is exchanged between lanes.  Bound by the read of the
+// partials: kFew is the next power of two, since a surplus load costs its issue slots and cache bandwidth although it
+// hits (24576 rows x 10 chunks over 4 requests: 38.7 us with eight loads per row, 28.1 us with four; 5.2 TB/s).
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 
-template <int D>
+template <int D, int kFew>
 __global__ __launch_bounds__(256) void attn_merge_few_kernel(const AttnParams p) {
   constexpr int kPerRow = D / 4;
-  const size_t grow = (size_t)blockIdx.x * (256 / kPerRow) + threadIdx.x / kPerRow;  // row over all requests
-  if (grow >= (size_t)p.B * p.n_rows) return;
+  const int b = merge_request(p);
+  const int r = (int)(blockIdx.x * (256 / kPerRow) + threadIdx.x / kPerRow);
+  if (b >= p.B || r >= p.n_rows) return;
+  const size_t grow = (size_t)b * p.n_rows + r;   // row over all requests
   const int col = (threadIdx.x % kPerRow) * 4;
-  const int b = (int)(grow / p.n_rows);
-  const int r = (int)(grow % p.n_rows);
-  const int n_s = attn_num_chunks(p.prefix_lens[b], p.chunk_len);  // <= kFew (checked by the host)
+  const int n_s = merge_chunks(p, b);  // <= kFew (checked by the host)
   const size_t slot0 = (size_t)b * p.s_max;
   const size_t stride = (size_t)p.n_rows * D;
   const float *po = p.part_o + (slot0 * p.n_rows + r) * D + col;
@@ -138,13 +148,21 @@ __global__ __launch_bounds__(256) void attn_merge_few_kernel(const AttnParams p)
 
 template <int D>
 hipError_t launch_merge(const AttnParams &p, hipStream_t stream) {
-  const size_t rows = (size_t)p.B * p.n_rows;
-  if (p.s_max <= kFew) {
-    constexpr int kRows = 256 / (D / 4);
-    hipLaunchKernelGGL(attn_merge_few_kernel<D>, dim3((unsigned)((rows + kRows - 1) / kRows)), dim3(256), 0, stream, p);
-  } else {
-    hipLaunchKernelGGL(attn_merge_kernel<D>, dim3((unsigned)((rows + kWaves - 1) / kWaves)), dim3(64 * kWaves), 0, stream, p);
-  }
+  auto grid = [&](int rows) {
+    return dim3((unsigned)((p.n_rows + rows - 1) / rows), (unsigned)(p.B < kMaxGridY ? p.B : kMaxGridY),
+                (unsigned)((p.B + kMaxGridY - 1) / kMaxGridY));
+  };
+  constexpr int kRows = 256 / (D / 4), kLong = D > 128 ? 16 : 32;
+  if (p.s_max <= 2)
+    hipLaunchKernelGGL((attn_merge_few_kernel<D, 2>), grid(kRows), dim3(256), 0, stream, p);
+  else if (p.s_max <= 4)
+    hipLaunchKernelGGL((attn_merge_few_kernel<D, 4>), grid(kRows), dim3(256), 0, stream, p);
+  else if (p.s_max <= 8)
+    hipLaunchKernelGGL((attn_merge_few_kernel<D, 8>), grid(kRows), dim3(256), 0, stream, p);
+  else if (p.s_max <= 16)
+    hipLaunchKernelGGL((attn_merge_kernel<D, 16>), grid(kWaves), dim3(64 * kWaves), 0, stream, p);
+  else
+    hipLaunchKernelGGL((attn_merge_kernel<D, kLong>), grid(kWaves), dim3(64 * kWaves), 0, stream, p);
   return hipGetLastError();
 }
 
