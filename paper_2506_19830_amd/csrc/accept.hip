@@ -23,14 +23,15 @@
 //   warp    (only with top-k / top-p) one workgroup per target row: the smallest logit the row keeps and the
 //           mass of the kept tokens.  Both filters are predicates on a token's value (keep v iff fewer than k
 //           tokens are larger; keep v iff the mass of the larger kept tokens is below top_p * Z_k), so equal
-//           logits are never split.  With a small k, or with top-p alone, a bound taken from the lanes' largest
-//           logits leaves a short list of candidate tokens, which is sorted and walked in descending order;
-//           otherwise (and whenever such a list overflows or falls short) two radix selections over an
+//           logits are never split.  With top-p alone the threshold is searched among the candidates rowz listed.
+//           With a small k, or where those fall short, a bound taken from the lanes' largest logits leaves a short
+//           list of candidate tokens, which is sorted and walked in descending order; otherwise (and whenever such a list overflows or falls short) two radix selections over an
 //           order-preserving key of the logit: the k-th largest by count, then among those the value at which
 //           the descending cumulative mass reaches top_p of the kept mass.  decide / resid / pick then use
 //           p(v) = [key(v) >= key_min] * exp((x_v - max)/T) / Z_kept for the target rows.
 //   rowz    (only with top-p alone) grid (fine-slice groups, target rows): the fp64 mass of every target row in
-//           fine slices, which warp folds: top-p's threshold is a share of the whole row's mass.
+//           fine slices, which warp folds: top-p's threshold is a share of the whole row's mass; and the tokens
+//           heavy enough to be kept, for warp.
 // The two resampling rows are re-read twice (2 of the 2K+1 rows of a branch; cache hits).
 // fp64 there makes the blocked running sum agree with a sequential one to ~1e-16, so the
 // drawn token does not depend on the summation order.
@@ -47,6 +48,7 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 constexpr int kThreads = 256;
 constexpr int kFinePer = 8;                 // tokens per lane in the fp64 kernels (load_fine reads eight)
 constexpr int kFine = kThreads * kFinePer;  // 2048 tokens per fine slice
+constexpr int kMaxFine = 1024;   // fine slices per row the fp64 kernels can stage in LDS (vocab <= 2M)
 
 // (bit-casting a vector element in place, __builtin_bit_cast(float, w[k]), reads element 0 with this compiler;
 // pass the element by value instead)
@@ -70,10 +72,54 @@ __device__ __forceinline__ float wave_sum(float v) {
   for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
   return v;
 }
+// Maximum and sum over a wavefront on the vector ALU, for values whose order of summation does not matter.
+template <int ROT>
+__device__ __forceinline__ float row_rotate(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + ROT, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+__device__ __forceinline__ float wave_max_dpp(float v) {
+  v = fmaxf(v, row_rotate<8>(v));
+  v = fmaxf(v, row_rotate<4>(v));
+  v = fmaxf(v, row_rotate<2>(v));
+  v = fmaxf(v, row_rotate<1>(v));
+  return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
+}
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  v += row_rotate<1>(v);
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
+// Sum over the 16 lanes of a DPP row, on the vector ALU (a shuffle goes through the LDS pipeline, two accesses per
+// double and step, which the workgroups of the fp64 kernels were queueing for).  The lanes of a row hold the same sum
+// in different orders: take it from one lane.
+template <int ROT>
+__device__ __forceinline__ double row_rotate(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + ROT, 0xf, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + ROT, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double row_sum(double v) {
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  return v + row_rotate<1>(v);
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+  v = row_sum(v);
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
 // row rw of the stacked [target rows ; draft rows] list
@@ -832,38 +878,246 @@ __device__ __forceinline__ bool warp_top_p_list(const AcceptParams &p, const voi
 // takes several slices so that its start-up (the row maximum from the slice statistics) is shared and all its loads
 // are in flight together.
 constexpr int kRowzGroup = 4;
+//
+// It also lists the tokens top-p can keep.  With Z the row's mass, tokens whose own mass is below (1 - top_p) Z / V
+// weigh less than (1 - top_p) Z together, so none of them is kept, and of a row that is peaked enough for a short list
+// the same holds for eight times that mass (normal logits, V = 152064, 31 to 8600 tokens kept: from 24 times on).  The
+// bound taken is that of eight times the mass, from the fp32 statistics; whether the listed tokens hold top_p Z is
+// checked exactly by the warp kernel.  (Normal logits of deviation 3, T = 0.6, top_p = 0.95: 2900 listed, 350 kept.)
+// A workgroup writes its tokens' keys in token order to a segment of p.cand, whose space the per-lane sums of the
+// resampling path use later; the warp kernel finds the threshold among them without reading the row.  A segment that
+// does not fit says so by its count, and the row takes the long way.
+struct CandHeader {
+  uint32_t n, pad[3];   // tokens at or above the bound (more than fit: the segment is not complete)
+};
+template <bool BF16>
+__device__ __forceinline__ uint8_t *cand_segment(const AcceptParams &p, int rw, int group) {
+  return p.cand + ((size_t)rw * ((p.n_fine + kRowzGroup - 1) / kRowzGroup) + group) * p.cand_bytes;
+}
+constexpr int kCandLds = 1024;   // most keys of a segment
+template <bool BF16>
+__device__ __forceinline__ int cand_capacity(const AcceptParams &p) {
+  return min(kCandLds, (p.cand_bytes - (int)sizeof(CandHeader)) / (BF16 ? 2 : 4));
+}
 
 template <bool BF16>
 __global__ __launch_bounds__(kThreads) void accept_rowz_kernel(const AcceptParams p) {
-  __shared__ float s_wm[kThreads / 64];
   __shared__ double red[kRowzGroup][kThreads / 64];
+  __shared__ int s_cnt[kThreads / 64];
+  __shared__ uint32_t s_list[kCandLds + 64];
   const int c0 = blockIdx.x * kRowzGroup, rw = blockIdx.y, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  // the row maximum from the slice statistics (exact, so the same value in every workgroup and in the warp kernel)
-  const float *st = p.stats + (size_t)rw * p.n_chunks * 2;
-  float m = -INFINITY;
-  for (int ch = tid; ch < p.n_chunks; ch += kThreads) m = fmaxf(m, st[2 * ch]);
-  m = wave_max(m);
-  if (lane == 0) s_wm[wave] = m;
   const bool vec = ((size_t)p.V * (BF16 ? 2 : 4)) % 16 == 0;
+  // the row maximum from the slice statistics (exact, so the same value in every workgroup and in the warp kernel) and
+  // its fp32 mass; requested before the logits, so that the fold runs while those are on their way
+  const bool one_round = p.n_chunks <= 64;
+  f32x2 st = {-INFINITY, 0.f};
+  if (one_round && lane < p.n_chunks) st = *(const f32x2 *)(p.stats + ((size_t)rw * p.n_chunks + lane) * 2);
   float x[kRowzGroup][kFinePer];
 #pragma unroll
   for (int g = 0; g < kRowzGroup; ++g)   // (slices past the row read as -inf)
     load_fine<BF16>(p.target, (size_t)rw * p.V, (c0 + g) * kFine + tid * kFinePer, p.V, vec, x[g]);
-  __syncthreads();
-  m = fmaxf(fmaxf(s_wm[0], s_wm[1]), fmaxf(s_wm[2], s_wm[3]));
+  float m, z32;
+  if (one_round) {
+    m = wave_max_dpp(st.x);
+    z32 = wave_sum_dpp(lane < p.n_chunks ? st.y * __builtin_amdgcn_exp2f((st.x - m) * p.inv_temp_log2) : 0.f);
+  } else {
+    wave_fold_row(p, rw, lane, m, z32);
+  }
   const double mx_over_t = (double)m * p.inv_temp;
+  // (a token without mass -- a masked one, or a place past V -- is never listed)
+  const float bound =
+      fmaxf(m + __builtin_amdgcn_logf(8.0f * (1.0f - p.top_p) * z32 / (float)p.V) / p.inv_temp_log2, -3.402823466e38f);
+  uint32_t marks = 0;   // bit g*8 + e: token e of slice g is listed
 #pragma unroll
   for (int g = 0; g < kRowzGroup; ++g) {
     double acc = 0.0;
 #pragma unroll
-    for (int e = 0; e < kFinePer; ++e) acc += mass64(x[g][e], mx_over_t, p.inv_temp);   // (past V: -inf, mass 0)
+    for (int e = 0; e < kFinePer; ++e) {
+      acc += mass64(x[g][e], mx_over_t, p.inv_temp);   // (past V: -inf, mass 0)
+      if (x[g][e] >= bound) marks |= 1u << (g * kFinePer + e);
+    }
     acc = wave_sum(acc);
     if (lane == 0) red[g][wave] = acc;
   }
+  const int own = __popc(marks);
+  int incl = own;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int up = __shfl_up(incl, off);
+    if (lane >= off) incl += up;
+  }
+  if (lane == 63) s_cnt[wave] = incl;
   __syncthreads();
   if (tid < kRowzGroup && c0 + tid < p.n_fine)
     p.warp_zs[(size_t)rw * p.n_fine + c0 + tid] = (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
+  if (p.cand_bytes) {   // (uniform)
+    // through LDS, every lane storing every token -- the unlisted ones to a place of their own behind the list --, so
+    // that no token costs a branch; then in whole words to the segment
+    uint8_t *seg = cand_segment<BF16>(p, rw, blockIdx.x);
+    const int cap = cand_capacity<BF16>(p);
+    const int total = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+    int at = incl - own;
+    for (int w = 0; w < wave; ++w) at += s_cnt[w];
+#pragma unroll
+    for (int g = 0; g < kRowzGroup; ++g)
+#pragma unroll
+      for (int e = 0; e < kFinePer; ++e) {
+        const uint32_t bit = marks >> (g * kFinePer + e) & 1;
+        const uint32_t key = order_key(x[g][e]);
+        s_list[bit && at < kCandLds ? at : kCandLds + lane] = BF16 ? key >> 16 : key;
+        at += bit;
+      }
+    __syncthreads();
+    if (tid == 0) ((CandHeader *)seg)->n = (uint32_t)total;
+    const int n = total <= cap ? total : 0;
+    if constexpr (BF16) {
+      uint32_t *to = (uint32_t *)(seg + sizeof(CandHeader));   // (the segment ends on a multiple of 16 bytes)
+      for (int i = tid; 2 * i < n; i += kThreads) to[i] = s_list[2 * i] | s_list[2 * i + 1] << 16;
+    } else {
+      uint32_t *to = (uint32_t *)(seg + sizeof(CandHeader));
+      for (int i = tid; i < n; i += kThreads) to[i] = s_list[i];
+    }
+  }
+}
+
+// top-p without top-k from the segments accept_rowz_kernel wrote.  The threshold is the largest c with
+// mass{key >= c} >= top_p * zk: the tokens at or above it stay -- the mass above each of them is below the target --
+// and no other does.  It is found from the top bits down, two bits per round, the fp64 masses of a lane's keys in
+// registers and three sums per round; every sum runs in a fixed order.  Bound by its chain of loads, barriers and
+// rounds, 54 workgroups on the chip: 44.3 -> 14.6 us at 54 rows of 152064 (T 0.6, top_p 0.95) against two passes of a
+// workgroup over its row and a sort; with the sums through LDS shuffles it was 21.4 us.  false: a segment is incomplete, the list is
+// longer than the workgroup holds, or it falls short of the target (the same decision in every lane).
+constexpr int kCandPer = 8;                        // keys per lane
+constexpr int kCandMax = kCandPer * kWarpThreads;  // (the LDS list holds as many)
+
+template <bool BF16>
+__device__ __forceinline__ bool warp_top_p_segments(const AcceptParams &p, int rw, double *red, uint32_t *list, float *row_max_out,
+                                                    uint32_t *key_min_out, double *z_out) {
+  constexpr int kW = kWarpThreads / 64;
+  constexpr int kMaxGroups = kMaxFine / kRowzGroup;
+  __shared__ int s_off[kMaxGroups + 1], s_wave[kW], s_bad;
+  __shared__ uint32_t s_low[kW];
+  __shared__ double s_sum[2][3][kW];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_g = (p.n_fine + kRowzGroup - 1) / kRowzGroup, cap = cand_capacity<BF16>(p);
+  // zk from the row's fine-slice sums, in a fixed order: slice t in lane t, a butterfly per wavefront, the wavefronts
+  // in order
+  double acc = 0.0;
+  for (int t = tid; t < p.n_fine; t += kWarpThreads) acc += p.warp_zs[(size_t)rw * p.n_fine + t];
+  // where each segment's keys go in the list (n_g <= kMaxGroups <= the workgroup)
+  const int own = tid < n_g ? (int)((const CandHeader *)cand_segment<BF16>(p, rw, tid))->n : 0;
+  float m = -INFINITY;   // the row maximum
+  for (int c = lane; c < p.n_chunks; c += 64) m = fmaxf(m, p.stats[((size_t)rw * p.n_chunks + c) * 2]);
+  acc = wave_sum(acc);
+  if (lane == 0) red[wave] = acc;
+  m = wave_max_dpp(m);
+  *row_max_out = m;
+  const double mx_over_t = (double)m * p.inv_temp;
+  const bool bad = own > cap;
+  int incl = own;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int up = __shfl_up(incl, off);
+    if (lane >= off) incl += up;
+  }
+  if (lane == 63) s_wave[wave] = incl;
+  if (tid == 0) s_bad = 0;
+  __syncthreads();
+  if (bad) s_bad = 1;
+  int base = 0, n = 0;
+#pragma unroll
+  for (int w = 0; w < kW; ++w) {
+    base += w < wave ? s_wave[w] : 0;
+    n += s_wave[w];
+  }
+  if (tid < n_g) s_off[tid] = base + incl - own;
+  if (tid == n_g) s_off[n_g] = n;
+  double zk = 0.0;
+#pragma unroll
+  for (int w = 0; w < kW; ++w) zk += red[w];
+  __syncthreads();
+  if (s_bad || n > kCandMax || n < 1) return false;
+  for (int g = wave; g < n_g; g += kW) {
+    const uint8_t *keys = cand_segment<BF16>(p, rw, g) + sizeof(CandHeader);
+    const int off = s_off[g], cnt = s_off[g + 1] - off;
+    for (int i = lane; i < cnt; i += 64) {
+      if constexpr (BF16) {   // (the sixteen low bits of a widened bf16 value's key)
+        const uint32_t k = (uint32_t)((const uint16_t *)keys)[i] << 16;
+        list[off + i] = k | ((k >> 31) ? 0u : 0xFFFFu);
+      } else {
+        list[off + i] = ((const uint32_t *)keys)[i];
+      }
+    }
+  }
+  __syncthreads();
+  uint32_t key[kCandPer], low = 0xFFFFFFFFu;
+  double mass[kCandPer], total = 0.0;
+#pragma unroll
+  for (int j = 0; j < kCandPer; ++j) {
+    const int i = tid + j * kWarpThreads;
+    key[j] = 0u, mass[j] = 0.0;
+    if (j * kWarpThreads < n) {   // (uniform)
+      if (i < n) {
+        key[j] = list[i];
+        low = min(low, key[j]);
+        mass[j] = mass64(key_value(key[j]), mx_over_t, p.inv_temp);
+      }
+      total += mass[j];
+    }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) low = min(low, (uint32_t)__shfl_xor((int)low, off));
+  total = wave_sum(total);
+  if (lane == 0) s_low[wave] = low, red[wave] = total;
+  __syncthreads();
+  total = 0.0;
+#pragma unroll
+  for (int w = 0; w < kW; ++w) {
+    total += red[w];
+    low = min(low, s_low[w]);
+  }
+  const double target = (double)p.top_p * zk;
+  if (!(total >= target)) return false;
+  // the bits all listed keys share stay as they are
+  const uint32_t top = order_key(m), diff = top ^ low;
+  int bit = diff ? 31 - __clz((int)diff) : -1;   // the highest bit that differs
+  const int last = BF16 ? 16 : 0;
+  uint32_t lo = bit < 31 ? low & ~((2u << bit) - 1) : 0u;
+  if (bit < 0) lo = low;
+  double z = total;
+  for (int round = 0; bit >= last; ++round) {
+    const int sh = max(last, bit - 1);             // this round decides bits bit .. sh (two, or the last one alone)
+    const int ways = bit == sh ? 1 : 3;
+    double s[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < kCandPer; ++j)
+      if (j * kWarpThreads < n) {
+#pragma unroll
+        for (int w = 0; w < 3; ++w) s[w] += key[j] >= (lo | ((uint32_t)(w + 1) << sh)) ? mass[j] : 0.0;
+      }
+#pragma unroll
+    for (int w = 0; w < 3; ++w) s[w] = wave_sum(s[w]);
+    if (lane == 0) {
+#pragma unroll
+      for (int w = 0; w < 3; ++w) s_sum[round & 1][w][wave] = s[w];
+    }
+    __syncthreads();   // (one barrier per round: the next round writes the other half)
+    // row w of a wavefront adds up the wavefronts' shares of sum w
+    static_assert(kW == 16, "a DPP row holds one share per wavefront");
+    const double share = row_sum(lane < 3 * kW ? s_sum[round & 1][lane >> 4][lane & 15] : 0.0);
+    int take = 0;
+#pragma unroll
+    for (int w = 0; w < 3; ++w) {
+      const double t = lane_value(share, 16 * w);
+      if (w < ways && t >= target) take = w + 1, z = t;   // (falls with w)
+    }
+    lo |= (uint32_t)take << sh;
+    bit = sh - 1;
+  }
+  *key_min_out = lo;
+  *z_out = z;
+  return true;
 }
 
 template <bool BF16>
@@ -884,6 +1138,11 @@ __global__ __launch_bounds__(kWarpThreads) void accept_warp_kernel(const AcceptP
   bool done = false;
   if (p.top_k > 0 && p.top_k < p.V && p.top_k <= kSmallK)   // the candidate list lives in the histogram's storage
     done = warp_small_k<BF16>(p, row, cnt, cnt + kCand, mass + kCand, &m, &key_min, &zw);
+  const bool use_k = p.top_k > 0 && p.top_k < p.V;
+  if (!done && !use_k && p.top_p < 1.0f && p.cand_bytes) {   // (the candidate lists live in the histogram's storage)
+    done = warp_top_p_segments<BF16>(p, rw, red, cnt, &m, &key_min, &zw);
+    __syncthreads();
+  }
   if (!done) {
     if (tid < 64) {
       float z;
@@ -894,13 +1153,12 @@ __global__ __launch_bounds__(kWarpThreads) void accept_warp_kernel(const AcceptP
     m = s_m;
     const double mx_over_t = (double)m * p.inv_temp;
     key_min = 0;
-    const bool use_k = p.top_k > 0 && p.top_k < p.V;
     if (use_k)
       key_min = radix_select<BF16, false>(each_of_row, 0.0, 0.0, 0u, p.top_k, 0.0, cnt, mass, &s_pick, &s_above);
     bool listed = false;
     if (p.top_p < 1.0f) {
       double zk = 0.0;
-      if (!use_k)   // (the candidate list lives in the histogram's storage)
+      if (!use_k)
         listed = warp_top_p_list<BF16>(p, row, p.warp_zs + (size_t)rw * p.n_fine, mx_over_t, red, cnt, mass + kCand,
                                        &zk, &key_min, &zw);
       else
@@ -1063,8 +1321,6 @@ __global__ __launch_bounds__(kThreads) void accept_decide_kernel(const AcceptPar
     p.zsum[((size_t)nb * 2 + 1) * p.n_fine + c] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
   }
 }
-
-constexpr int kMaxFine = 1024;   // fine slices per row the fp64 kernels can stage in LDS (vocab <= 2M)
 
 // Two rows of n <= kMaxFine doubles each, folded together so that their loads are one round trip.  load: a lane's
 // terms (index tid + kThreads*j) into registers.  sum: the two sums, the same values in every lane of the workgroup
@@ -1382,6 +1638,13 @@ void accept_carve_workspace(AcceptParams &p, void *ws) {
   p.rowmax = (float *)at;
   at += align_up((size_t)p.NB * 2 * sizeof(float));
   p.lane_sums = (double *)at;
+  // the candidate segments of a call with top-p alone share the space: equal parts, 16-byte aligned, none if too small
+  {
+    const size_t groups = (size_t)(p.K + 1) * ((p.n_fine + kRowzGroup - 1) / kRowzGroup);
+    const size_t bytes = ((size_t)p.n_fine * kThreads * 2 * sizeof(double) / groups) & ~(size_t)15;
+    p.cand = at;
+    p.cand_bytes = bytes >= 64 ? (int)bytes : 0;
+  }
   at += align_up((size_t)p.NB * p.n_fine * kThreads * 2 * sizeof(double));
   const bool warp = (p.top_k > 0 && p.top_k < p.V) || p.top_p < 1.0f;
   p.warp_key = warp ? (uint32_t *)at : nullptr;

@@ -111,7 +111,7 @@ int attn_mfma_tile_m(int shape);   // rows per workgroup of a shape
 int attn_mfma_wgs_per_cu(int shape);  // workgroups of a shape that fit on one CU (LDS)
 int attn_mfma_max_chunk_blocks();  // a chunk may span at most this many cache blocks
 hipError_t launch_attn_mfma(const AttnParams &p, int shape, bool kv_fp8, bool br_fp8, hipStream_t stream);
-// The streaming shapes (few rows per KV head; fp8 cache and fp8 branch K/V, flat calls): row blocks x key slices.
+// The streaming shapes (few rows per KV head; cache and branch K/V of one storage type): row blocks x key slices.
 int attn_stream_num_shapes();
 int attn_stream_tile_m(int shape);
 int attn_stream_step_keys(int shape);  // keys a workgroup advances per pipeline step
@@ -143,6 +143,8 @@ struct AcceptParams {
   double *rsum;                // [NB, 2, n_fine]  fp64 slice sums of the residual and of p
   float *rowmax;               // [NB, 2] exact row maxima (raw logits) of the resampling rows
   double *lane_sums;           // [NB, n_fine, 256, 2] per-lane sums of the residual and of p
+  uint8_t *cand;               // top-p alone: candidate segments of every target row, in the space of lane_sums
+  int cand_bytes;              // size of one segment (0: none)
   // top-k / top-p warping of the target rows (off: top_k == 0 and top_p >= 1)
   int top_k;
   float top_p;
