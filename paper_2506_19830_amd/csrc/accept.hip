@@ -904,7 +904,7 @@ template <bool BF16>
 __global__ __launch_bounds__(kThreads) void accept_rowz_kernel(const AcceptParams p) {
   __shared__ double red[kRowzGroup][kThreads / 64];
   __shared__ int s_cnt[kThreads / 64];
-  __shared__ uint32_t s_list[kCandLds + 64];
+  __shared__ uint32_t s_list[kCandLds + 1];   // (one more: the second half of the last word)
   const int c0 = blockIdx.x * kRowzGroup, rw = blockIdx.y, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const bool vec = ((size_t)p.V * (BF16 ? 2 : 4)) % 16 == 0;
@@ -952,31 +952,26 @@ __global__ __launch_bounds__(kThreads) void accept_rowz_kernel(const AcceptParam
   if (tid < kRowzGroup && c0 + tid < p.n_fine)
     p.warp_zs[(size_t)rw * p.n_fine + c0 + tid] = (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
   if (p.cand_bytes) {   // (uniform)
-    // through LDS, every lane storing every token -- the unlisted ones to a place of their own behind the list --, so
-    // that no token costs a branch; then in whole words to the segment
+    // in rounds, one listed token per lane and round, its logit read once more (few, and just loaded: a test per token in
+    // straight code took 4 us of the kernel's 18); through LDS, then in whole words to the segment
     uint8_t *seg = cand_segment<BF16>(p, rw, blockIdx.x);
-    const int cap = cand_capacity<BF16>(p);
     const int total = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+    if (tid == 0) ((CandHeader *)seg)->n = (uint32_t)total;
+    if (total > cand_capacity<BF16>(p)) return;   // (uniform)
     int at = incl - own;
     for (int w = 0; w < wave; ++w) at += s_cnt[w];
-#pragma unroll
-    for (int g = 0; g < kRowzGroup; ++g)
-#pragma unroll
-      for (int e = 0; e < kFinePer; ++e) {
-        const uint32_t bit = marks >> (g * kFinePer + e) & 1;
-        const uint32_t key = order_key(x[g][e]);
-        s_list[bit && at < kCandLds ? at : kCandLds + lane] = BF16 ? key >> 16 : key;
-        at += bit;
-      }
+    for (; marks; marks &= marks - 1, ++at) {
+      const int bit = __ffs((int)marks) - 1;
+      const int v = (c0 + bit / kFinePer) * kFine + tid * kFinePer + bit % kFinePer;
+      const uint32_t key = order_key(load_logit<BF16>(p.target, (size_t)rw * p.V + v));
+      s_list[at] = BF16 ? key >> 16 : key;
+    }
     __syncthreads();
-    if (tid == 0) ((CandHeader *)seg)->n = (uint32_t)total;
-    const int n = total <= cap ? total : 0;
+    uint32_t *to = (uint32_t *)(seg + sizeof(CandHeader));   // (the segment ends on a multiple of 16 bytes)
     if constexpr (BF16) {
-      uint32_t *to = (uint32_t *)(seg + sizeof(CandHeader));   // (the segment ends on a multiple of 16 bytes)
-      for (int i = tid; 2 * i < n; i += kThreads) to[i] = s_list[2 * i] | s_list[2 * i + 1] << 16;
+      for (int i = tid; 2 * i < total; i += kThreads) to[i] = s_list[2 * i] | s_list[2 * i + 1] << 16;
     } else {
-      uint32_t *to = (uint32_t *)(seg + sizeof(CandHeader));
-      for (int i = tid; i < n; i += kThreads) to[i] = s_list[i];
+      for (int i = tid; i < total; i += kThreads) to[i] = s_list[i];
     }
   }
 }

@@ -19,7 +19,8 @@
 //   * the unmasked tiles keep the base their probabilities are formed against and never rescale O; they run in a
 //     loop of their own, and a workgroup that meets a score far above its base reduces its chunk a second time in a
 //     general form (stream_tile_fast says why).
-// The last chunk's workgroup also reduces the branch-private keys (causal inside the branch), as further steps
+// The last chunk's workgroup also reduces the branch-private keys (causal inside the branch) and, in the nested and
+// tree forms, the visible part of the drafted chain or pool, as further steps
 // of the same pipeline.
 //
 // LDS layout of a tile half (K or V, 64 key rows of 128 bytes): a wavefront-wide load lands as 1 KiB in lane
