@@ -109,8 +109,16 @@ __device__ __forceinline__ void load_lds16(const uint8_t *src, uint32_t lds_addr
 }
 // the compiler keeps LDS accesses on their side of this; no instruction
 __device__ __forceinline__ void order_lds() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+// Direct loads are ordered with LDS reads by nothing but counters: before a load may overwrite a stage, the reads of
+// what it held have to have returned.  (Free where a result that depends on all of them is needed first anyway.)
+__device__ __forceinline__ void wait_reads() {
+  order_lds();
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0), the other counters left at their maxima
+}
+// The direct loads have landed, and the LDS reads before them have returned.
 __device__ __forceinline__ void wait_loads() {
-  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0), the other counters left at their maxima
+  order_lds();
+  __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
   order_lds();
 }
 
@@ -213,7 +221,7 @@ struct General {
     constexpr int es = kBytes<T>;
     const uint8_t *kp = (const uint8_t *)(SEG == SEG_PREFIX ? p.k_cache : SEG == SEG_CHAIN ? p.k_chain : p.k_branch);
     const uint8_t *vp = (const uint8_t *)(SEG == SEG_PREFIX ? p.v_cache : SEG == SEG_CHAIN ? p.v_chain : p.v_branch);
-    order_lds();
+    wait_reads();
 #pragma unroll
     for (int j = 0; j < S::kLoads; ++j) {
       const int k = j * (1024 / S::kRow) + lane / S::kPieces;
@@ -523,7 +531,7 @@ __global__ __launch_bounds__(64 * NW) void attn_general_kernel(const AttnParams 
       f32x4 s[RB][G::kTiles];
       g.template scores<KV>(stage, s);
       if (G::kStages == 1 && more) {
-        order_lds();
+        wait_reads();
         g.load_k_full(next, 0);
       }
       if (G::kStages > 1) stage ^= 1;

@@ -7,6 +7,7 @@ import torch
 from gpu_util import attn_desc, row_errors, upload_attention
 from paper_2506_19830_amd import binding as B
 from paper_2506_19830_amd import workloads as W
+from test_gpu_attention import check_full
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +57,10 @@ def test_general_path_edges(oracle, case, split):
         torch.cuda.synchronize()
         assert row_errors(out.double().cpu().numpy(), ref).max() <= 1e-5
         assert np.abs(lse.double().cpu().numpy() - ref_lse).max() <= 1e-5
+
+
+@pytest.mark.parametrize("storage", [BF16, FP8, MIXED, F32], ids=["bf16", "fp8", "mixed", "f32"])
+def test_single_stage_over_many_blocks(oracle, storage):
+    """Head dimension 256 keeps one K stage per wavefront, which every block overwrites: unsplit, 17 to 33 blocks each."""
+    case = _case("wide_long", (4130,), 1, 5, 3, 1, 256, storage, paged=True)
+    check_full(oracle, case, 1e-5, 0 if storage is F32 else 8192, lse_tol=1e-5)
