@@ -508,8 +508,11 @@ __global__ __launch_bounds__(64 * NW) void attn_general_kernel(const AttnParams 
 
   // ---- full prefix blocks: wave, wave + NW, ...
   constexpr int kKeys = G::kKeys;
-  const int n_full = sel.k_end / kKeys;   // (chunks start at multiples of 64 keys)
-  int blk = sel.k_begin / kKeys + g.wave;
+  // A chunk may hold no prefix key at all (a short prefix beside long branches, attn_chunk_range): its range then starts
+  // behind its end, and the blocks are counted from zero.
+  const bool any_prefix = sel.k_end > sel.k_begin;
+  const int n_full = any_prefix ? sel.k_end / kKeys : 0;   // (chunks start at multiples of 64 keys)
+  int blk = (any_prefix ? sel.k_begin / kKeys : 0) + g.wave;
   {
     size_t base[G::kTiles], next[G::kTiles];
     auto bases = [&](int at, size_t (&out)[G::kTiles]) __attribute__((always_inline)) {
@@ -543,7 +546,7 @@ __global__ __launch_bounds__(64 * NW) void attn_general_kernel(const AttnParams 
     }
   }
   // ---- the rest, dealt out in the same round: the prefix's last, partial block, chain / pool blocks, branch blocks
-  const int n_tail = sel.k_end % kKeys ? 1 : 0, n_chain = last_chunk ? (vis_max + kKeys - 1) / kKeys : 0;
+  const int n_tail = any_prefix && sel.k_end % kKeys ? 1 : 0, n_chain = last_chunk ? (vis_max + kKeys - 1) / kKeys : 0;
   const int n_own = last_chunk ? (t_hi - tk0 + 1 + kKeys - 1) / kKeys : 0;
   int i = blk - n_full;
   if (n_tail) {

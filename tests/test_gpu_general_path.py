@@ -7,7 +7,7 @@ import torch
 from gpu_util import attn_desc, row_errors, upload_attention
 from paper_2506_19830_amd import binding as B
 from paper_2506_19830_amd import workloads as W
-from test_gpu_attention import check_full
+from test_gpu_attention import check_full, check_nested, check_tree
 
 pytestmark = pytest.mark.gpu
 
@@ -64,3 +64,45 @@ def test_single_stage_over_many_blocks(oracle, storage):
     """Head dimension 256 keeps one K stage per wavefront, which every block overwrites: unsplit, 17 to 33 blocks each."""
     case = _case("wide_long", (4130,), 1, 5, 3, 1, 256, storage, paged=True)
     check_full(oracle, case, 1e-5, 0 if storage is F32 else 8192, lse_tol=1e-5)
+def _empty_last_chunk(case, split):
+    """Does some request's last chunk hold no prefix key?  (The tiles of 64 keys are dealt out evenly, the last chunk
+    counted as carrying the branch-private ones.)"""
+    rows = case.gamma * case.L * case.Hq
+    r = rows // case.Hkv
+    size = B.la_verify_attention_workspace(attn_desc(case, split), list(case.prefix_lens))
+    s_max = round(size / (case.B * rows * (case.D + 2) * 4))
+    tile = 32 if case.D == 64 and r > 16 else 16
+    last_short = -(-min(tile + case.L, case.gamma * case.L) // 64)
+    longest = max(case.prefix_lens)
+    chunk = split or min(-(-longest // n) + 63 & ~63 for n in range(1, 65) if -(-longest // (-(-longest // n) + 63 & ~63)) == s_max)
+    for p in case.prefix_lens:
+        n, tiles = max(1, -(-p // chunk)), -(-p // 64)
+        if n > 1 and (n - 1) * (tiles + last_short) // n >= tiles:
+            return True
+    return False
+
+
+EMPTY_LAST = [
+    # (case, kv_split_tokens): prefixes that end 1 .. 32 tokens into a key tile, beside branches of several tiles
+    (_case("empty_p70", (70,), 2, 48, 8, 1, 64, BF16), 64),
+    (_case("empty_p96_paged", (96, 0, 640), 2, 64, 2, 1, 64, BF16, paged=True), 64),
+    (_case("empty_p80_fp8", (80,), 4, 40, 8, 2, 64, FP8), 64),
+    (_case("empty_p65_mixed", (65,), 3, 70, 2, 1, 64, MIXED, paged=True), 64),
+    (_case("empty_auto", (1055,), 1, 512, 4, 1, 64, BF16), 0),
+    (_case("empty_wide", (70,), 2, 64, 2, 1, 256, BF16, paged=True), 64),
+    (_case("empty_wide_auto", (450,), 1, 512, 4, 1, 256, BF16), 0),
+    (_case("empty_wide_auto_fp8", (715,), 2, 320, 2, 1, 256, FP8), 0),
+]
+
+
+@pytest.mark.parametrize("form", ["flat", "nested", "tree"])
+@pytest.mark.parametrize("case,split", EMPTY_LAST, ids=lambda v: getattr(v, "name", str(v)))
+def test_last_chunk_without_prefix_keys(oracle, case, split, form):
+    """Its workgroups start with the chain / pool or the branches' own tokens; every one of those keys counts."""
+    assert _empty_last_chunk(case, split)
+    if form == "flat":
+        check_full(oracle, case, 1e-5, split, lse_tol=1e-5)
+    elif form == "nested":
+        check_nested(oracle, case, 75, 1e-5, None, split)
+    else:
+        check_tree(oracle, case, 2, 2, 11, 1e-5, split)
