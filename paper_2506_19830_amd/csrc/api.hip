@@ -199,6 +199,21 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, bool
     return plan->kv_fp8 == si.fp8 && plan->br_fp8 == si.fp8 &&
            (int64_t)d->num_kv_heads * d->block_size * d->head_dim * (si.fp8 ? 1 : 2) < ((int64_t)1 << 32);
   };
+  // Tiles of other work that the last chunk's workgroup carries.  (A streaming shape advances whole steps: the private
+  // tiles are steps of their own, so the last chunk gets as many prefix steps fewer, or its workgroup would finish a step
+  // after all the others.)
+  auto last_short_tiles = [&](const ShapeInfo &si) -> int {
+    const int priv_tokens = si.tile_m / G + d->branch_len < d->gamma * d->branch_len ? si.tile_m / G + d->branch_len
+                                                                                     : d->gamma * d->branch_len;
+    const int priv_tiles = (priv_tokens + 63) / 64, step_tiles = si.step_keys / 64;
+    return si.stream ? step_tiles * ((priv_tiles + step_tiles - 1) / step_tiles) : 3 * priv_tiles;
+  };
+  // The longest chunk a shape can take: its block ids live in LDS (-2: a chunk need not start on a block boundary).
+  auto max_chunk = [&](const ShapeInfo &si, int last_short) -> int64_t {
+    const int blk_cap = si.stream ? attn_stream_max_chunk_blocks() : attn_mfma_max_chunk_blocks();
+    return ((int64_t)(blk_cap - 2) * d->block_size - 64 * (last_short + 2)) / 64 * 64;
+  };
+  auto chunk_fits = [&](int64_t longest) { return longest >= 64 && d->kv_split_tokens <= longest; };
   if (d->kernel_shape > 0) {
     const ShapeInfo forced = shape_info(d->kernel_shape - 1);
     if (forced.stream && (extra || !stream_ok(forced))) return LA_ERR_UNSUPPORTED;  // (forcing one: flat calls only)
@@ -215,8 +230,14 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, bool
   // With a bf16 cache the row-tile shapes are left to calls that force them (and to block strides the streaming shapes
   // cannot address): over 45 calls of all forms, 24 to 1400 rows and 300 to 32768 keys, the better of the two bf16
   // streaming shapes took 0.60 to 1.0 of the better row-tile shape's time (27434 + 12924 + 3678 + 3540 keys, 32 rows:
-  // 41 against 59 us; 8475 + 546 keys, 728 rows: 49 against 66 us).
-  const bool skip_row_tiles = d->kernel_shape == 0 && !plan->kv_fp8 && stream_ok(shape_info(num_shapes() - 1));
+  // 41 against 59 us; 8475 + 546 keys, 728 rows: 49 against 66 us).  A chunk length asked for (kv_split_tokens) that only
+  // the row tiles can hold, with twice the streaming shapes' table of block ids, leaves the call to them as well.
+  bool skip_row_tiles = false;
+  if (d->kernel_shape == 0 && !plan->kv_fp8)
+    for (int shape = attn_mfma_num_shapes(); shape < num_shapes(); ++shape) {
+      const ShapeInfo si = shape_info(shape);
+      skip_row_tiles |= stream_ok(si) && chunk_fits(max_chunk(si, last_short_tiles(si)));
+    }
   double best_cost = 0.0;
   int best_len = 0, best_shape = -1, best_short = 0;
   const int64_t T = (max_p + 63) / 64;
@@ -225,22 +246,15 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, bool
     const ShapeInfo si = shape_info(shape);
     if (si.stream ? !stream_ok(si) : skip_row_tiles) continue;
     const int64_t base_wgs = (int64_t)d->num_kv_heads * ((R + si.tile_m - 1) / si.tile_m);
-    const int priv_tokens = si.tile_m / G + d->branch_len < d->gamma * d->branch_len ? si.tile_m / G + d->branch_len
-                                                                                     : d->gamma * d->branch_len;
-    // (a streaming shape advances whole steps: the private tiles are steps of their own, so the last chunk gets as
-    // many prefix steps fewer, or its workgroup would finish a step after all the others)
-    const int priv_tiles = (priv_tokens + 63) / 64, step_tiles = si.step_keys / 64;
-    const int last_short = si.stream ? step_tiles * ((priv_tiles + step_tiles - 1) / step_tiles) : 3 * priv_tiles;
+    const int last_short = last_short_tiles(si);
     const int64_t slots = (int64_t)num_cus() * si.per_cu;
-    // the block ids of one chunk live in LDS (-2: a chunk need not start on a block boundary)
-    const int blk_cap = si.stream ? attn_stream_max_chunk_blocks() : attn_mfma_max_chunk_blocks();
-    const int64_t max_chunk = ((int64_t)(blk_cap - 2) * d->block_size - 64 * (last_short + 2)) / 64 * 64;
-    if (max_chunk < 64 || d->kv_split_tokens > max_chunk) continue;
+    const int64_t longest = max_chunk(si, last_short);
+    if (!chunk_fits(longest)) continue;
     double prev_cost = 0.0;
     for (int n = 1; n <= 512; ++n) {
       int64_t len = max_p > 0 ? (max_p + n - 1) / n : 64;
       len = ((len + 63) / 64) * 64;
-      if (len > max_chunk) len = max_chunk;
+      if (len > longest) len = longest;
       if (d->kv_split_tokens) len = d->kv_split_tokens;
       int64_t units = 0;
       for (int b = 0; b < d->num_requests; ++b) units += attn_num_chunks(prefix_lens_host[b], (int)len);

@@ -89,6 +89,53 @@ def test_planner_deals_unequal_requests_as_the_hardware_does():
     assert (time.perf_counter() - t0) / 50 < 5e-4          # observed 13 us; an allocating version of the model took 3 ms
 
 
+def _plan_status(desc, lens, chain_len=0):
+    try:
+        return 0, B.la_verify_attention_plan(desc, lens, chain_len)
+    except B.LaError as e:
+        return e.status, None
+
+
+def test_split_that_only_the_row_tiles_hold():
+    """The streaming shapes keep 2048 block ids of a chunk, the row tiles 4096: a bf16 call that asks for a chunk length
+    between the two runs on the row tiles, whatever its prefixes are."""
+    bf16 = dict(kv_dtype="bf16", branch_kv_dtype="bf16", num_q_heads=64, branch_len=48, max_blocks_per_request=4096)
+    for block, split, streams in ((16, 32448, True), (16, 32512, False), (16, 65024, False), (32, 65536, False)):
+        desc = good_desc(**bf16, block_size=block, kv_split_tokens=split)
+        for lens in ([100], [32000]):
+            plan = B.la_verify_attention_plan(desc, lens)
+            assert (plan["kernel_shape"] >= 3) == streams
+            assert B.la_verify_attention_workspace(desc, lens) > 0
+
+
+@pytest.mark.parametrize("seed", range(8))
+def test_the_planner_refuses_only_what_no_shape_runs(seed):
+    """Left to itself the library runs a call exactly where some kernel shape, forced, runs it (random descriptors)."""
+    import random
+    rng = random.Random(seed)
+    seen = set()
+    for _ in range(250):
+        kv, br = rng.choice((("bf16", "bf16"), ("fp8_e4m3", "fp8_e4m3"), ("fp8_e4m3", "bf16")))
+        hkv = rng.choice((1, 2, 8, 64))
+        block = 1 << rng.randint(4, 18)
+        n_req = rng.randint(1, 10)
+        blocks = rng.randint(1, 4096)
+        lens = [int(min(blocks * block, 400000) * rng.random() ** 3) for _ in range(n_req)]
+        if blocks * block > 1 << 30:
+            continue
+        kw = dict(num_requests=n_req, num_kv_heads=hkv, num_q_heads=hkv * rng.choice((1, 5, 8)), gamma=rng.randint(1, 16),
+                  branch_len=rng.choice((1, 9, 64, 700, 30000)), block_size=block, max_blocks_per_request=blocks,
+                  kv_dtype=kv, branch_kv_dtype=br, kv_split_tokens=64 * rng.choice((0, 0, 1, 100, 500, 520, 900, 1024, 3000)))
+        if kw["gamma"] * kw["branch_len"] * kw["num_q_heads"] * n_req > 1 << 30:
+            continue
+        status, plan = _plan_status(good_desc(**kw), lens)
+        forced = [_plan_status(good_desc(**kw, kernel_shape=k), lens)[0] for k in range(1, 8)]
+        assert status == (0 if 0 in forced else 2), (kw, lens, forced)
+        assert status or forced[plan["kernel_shape"] - 1] == 0
+        seen.add(status)
+    assert seen == {0, 2}
+
+
 @pytest.mark.parametrize("kw,lens,status", [
     (dict(num_q_heads=41), [100], 1),
     (dict(block_size=8), [100], 1),

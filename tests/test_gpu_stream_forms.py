@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2506_19830_amd import workloads as W
-from test_gpu_attention import TOL_LOWP, check_nested, check_tree
+from test_gpu_attention import TOL_LOWP, check_full, check_nested, check_tree
 
 pytestmark = pytest.mark.gpu
 
@@ -67,3 +67,11 @@ def test_second_attempt(oracle, kv, shape):
             B.la_selftest_second_attempt(False)
     finally:
         B.select_library("product")
+
+
+@pytest.mark.parametrize("split", [32448, 32512, 65024])
+def test_split_around_the_streaming_limit(oracle, split):
+    """Chunk lengths asked for that the streaming shapes' table of block ids can just, and can no longer hold."""
+    case = make_case("bf16", (700, 0, 130), 3, 20, 16, 2, True, seed=395)
+    check_full(oracle, case, TOL_LOWP, split)
+    check_nested(oracle, case, 60, TOL_LOWP, None, split)
