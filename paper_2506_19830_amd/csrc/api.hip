@@ -155,8 +155,8 @@ void make_general_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, i
   if (plan->s_max == 1) plan->part_o_bytes = plan->part_ml_bytes = 0;   // the kernel writes the output itself
 }
 
-// extra: the call carries a drafted chain or pool (nested / tree form)
-la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, bool extra, AttnPlan *plan) {
+// The same plan serves the flat, nested and tree forms of a call (count_extra_tiles shifts its chunk ranges for a chain).
+la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, AttnPlan *plan) {
   la_status st = validate_desc(d);
   if (st != LA_OK) return st;
   if (!prefix_lens_host) return LA_ERR_INVALID_ARG;
@@ -216,7 +216,7 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, bool
   auto chunk_fits = [&](int64_t longest) { return longest >= 64 && d->kv_split_tokens <= longest; };
   if (d->kernel_shape > 0) {
     const ShapeInfo forced = shape_info(d->kernel_shape - 1);
-    if (forced.stream && (extra || !stream_ok(forced))) return LA_ERR_UNSUPPORTED;  // (forcing one: flat calls only)
+    if (forced.stream && !stream_ok(forced)) return LA_ERR_UNSUPPORTED;
   }
 
   // Choose the kernel shape and the number of chunks that minimise a simple cost model (microseconds, constants
@@ -379,17 +379,10 @@ const char *la_status_string(int32_t status) {
 la_status la_verify_attention_workspace(const la_attn_desc *desc, const int32_t *prefix_lens_host,
                                         size_t *bytes_out) {
   if (!bytes_out) return LA_ERR_INVALID_ARG;
-  // one size serves the flat, nested and tree calls (their plans may differ)
-  size_t bytes = 0;
-  for (int extra = 0; extra < 2; ++extra) {
-    AttnPlan plan;
-    la_status st = make_plan(desc, prefix_lens_host, extra != 0, &plan);
-    if (extra && st == LA_ERR_UNSUPPORTED) continue;  // a forced shape that only runs flat calls
-    if (st != LA_OK) return st;
-    const size_t need = plan.part_o_bytes + plan.part_ml_bytes;
-    bytes = need > bytes ? need : bytes;
-  }
-  *bytes_out = bytes;
+  AttnPlan plan;
+  la_status st = make_plan(desc, prefix_lens_host, &plan);
+  if (st != LA_OK) return st;
+  *bytes_out = plan.part_o_bytes + plan.part_ml_bytes;
   return LA_OK;
 }
 
@@ -397,7 +390,7 @@ la_status la_verify_attention_plan(const la_attn_desc *desc, const int32_t *pref
                                    la_attn_plan *out) {
   if (!out || chain_len < 0) return LA_ERR_INVALID_ARG;
   AttnPlan plan;
-  la_status st = make_plan(desc, prefix_lens_host, chain_len > 0, &plan);
+  la_status st = make_plan(desc, prefix_lens_host, &plan);
   if (st != LA_OK) return st;
   memset(out, 0, sizeof *out);
   out->path = (int32_t)plan.path;
@@ -423,7 +416,7 @@ static la_status verify_attention(const la_attn_desc *desc, const void *q, const
                                   const float *v_scale, void *out, float *lse, void *workspace,
                                   size_t workspace_bytes, void *hip_stream) {
   AttnPlan plan;
-  la_status st = make_plan(desc, prefix_lens_host, chain_len > 0, &plan);
+  la_status st = make_plan(desc, prefix_lens_host, &plan);
   if (st != LA_OK) return st;
   if (!q || !prefix_lens || !k_branch || !v_branch || !out) return LA_ERR_INVALID_ARG;
   bool any_prefix = false;

@@ -108,6 +108,28 @@ def test_split_that_only_the_row_tiles_hold():
             assert B.la_verify_attention_workspace(desc, lens) > 0
 
 
+@pytest.mark.parametrize("kw,lens,shape", [
+    (dict(gamma=6, branch_len=9), [20011], 3),                                                      # fp8, few rows
+    (dict(gamma=15, branch_len=9, kv_dtype="bf16", branch_kv_dtype="bf16"), [12345], 6),
+    (dict(kv_dtype="fp8_e4m3", branch_kv_dtype="bf16"), [900], 1),
+])
+def test_what_the_plan_of_a_nested_call_names_can_be_forced(kw, lens, shape):
+    """The shape la_verify_attention_plan reports, given back as kernel_shape, is the same plan again, for flat calls and
+    for calls with a chain, and the call itself gets as far as its workspace."""
+    plan = B.la_verify_attention_plan(good_desc(**kw), lens, 135)
+    assert plan["kernel_shape"] == shape
+    pinned = good_desc(**kw, kernel_shape=shape)
+    assert B.la_verify_attention_plan(pinned, lens, 135) == plan == B.la_verify_attention_plan(pinned, lens, 0)
+    assert B.la_verify_attention_workspace(pinned, lens) == B.la_verify_attention_workspace(good_desc(**kw), lens)
+    vp, vis = ctypes.c_void_p, (ctypes.c_int32 * pinned.gamma)()
+    call = lambda desc: B.load().la_verify_attention_nested(
+        ctypes.byref(desc), vp(256), vp(256), vp(256), vp(0), vp(256), (ctypes.c_int32 * 1)(*lens), vp(256), vp(256), vp(256),
+        vp(256), ctypes.c_int32(135), vp(256), vis, vp(0), vp(0), vp(256), vp(0), vp(256), ctypes.c_size_t(1024), vp(0))
+    assert call(pinned) == 3
+    wrong = 6 if kw.get("kv_dtype") != "bf16" else 3                    # the other storage type's shape
+    assert call(good_desc(**kw, kernel_shape=wrong)) == 2
+
+
 @pytest.mark.parametrize("seed", range(8))
 def test_the_planner_refuses_only_what_no_shape_runs(seed):
     """Left to itself the library runs a call exactly where some kernel shape, forced, runs it (random descriptors)."""

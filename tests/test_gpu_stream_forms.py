@@ -75,3 +75,26 @@ def test_split_around_the_streaming_limit(oracle, split):
     case = make_case("bf16", (700, 0, 130), 3, 20, 16, 2, True, seed=395)
     check_full(oracle, case, TOL_LOWP, split)
     check_nested(oracle, case, 60, TOL_LOWP, None, split)
+
+
+FORCED = [("fp8_e4m3", 3), ("fp8_e4m3", 4), ("fp8_e4m3", 5), ("bf16", 6), ("bf16", 7)]
+
+
+@pytest.mark.parametrize("kv,kernel_shape", FORCED)
+def test_forced_shape(oracle, kv, kernel_shape, monkeypatch):
+    """Every streaming shape forced on nested and tree calls, and a chain or pool that no branch sees: the flat call's
+    bits."""
+    from gpu_util import run_attention, run_attention_nested, run_attention_tree
+    monkeypatch.setattr("gpu_util.KERNEL_SHAPE", kernel_shape)
+    for i, shape in enumerate(SHAPES):
+        case = make_case(kv, *shape, seed=400 + i)
+        for split in (0, 192):
+            check_nested(oracle, case, 130, TOL_LOWP, None, split)
+            check_tree(oracle, case, 2, 2, 21, TOL_LOWP, split)
+            inp = W.make_attention_inputs(case)
+            flat, flat_lse = run_attention(case, inp, split)
+            chain = W.make_chain_inputs(case, 70, inp, np.zeros((case.B, case.gamma), dtype=np.int32))
+            tree = W.make_tree_inputs(case, 2, 2, 17, inp)
+            tree["seg_mask"][:] = 0
+            for got, lse in (run_attention_nested(case, inp, chain, split), run_attention_tree(case, inp, tree, split)):
+                assert np.array_equal(got, flat) and np.array_equal(lse, flat_lse)
