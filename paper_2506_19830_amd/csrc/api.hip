@@ -394,14 +394,13 @@ la_status la_verify_attention_plan(const la_attn_desc *desc, const int32_t *pref
   if (st != LA_OK) return st;
   memset(out, 0, sizeof *out);
   out->path = (int32_t)plan.path;
-  if (plan.path == PATH_MFMA) {
-    out->kernel_shape = plan.shape + 1;
-    out->rows_per_workgroup = plan.tile_m;
-    out->row_tiles = plan.n_row_tiles;
-    out->chunk_tokens = plan.chunk_len;
-    out->chunks_total = plan.total_units;
-    out->workgroups = desc->num_kv_heads * plan.n_row_tiles * plan.total_units;
-  }
+  if (plan.path == PATH_MFMA) out->kernel_shape = plan.shape + 1;
+  out->rows_per_workgroup = plan.tile_m;
+  out->row_tiles = plan.n_row_tiles;
+  out->chunk_tokens = plan.s_max > 1 || plan.path == PATH_MFMA ? plan.chunk_len : 0;
+  out->chunks_total = plan.total_units;
+  const int64_t workgroups = (int64_t)desc->num_kv_heads * plan.n_row_tiles * plan.total_units;
+  out->workgroups = workgroups < INT32_MAX ? (int32_t)workgroups : INT32_MAX;
   return LA_OK;
 }
 

@@ -130,6 +130,27 @@ def test_what_the_plan_of_a_nested_call_names_can_be_forced(kw, lens, shape):
     assert call(good_desc(**kw, kernel_shape=wrong)) == 2
 
 
+def test_plan_of_the_general_path():
+    """What the general kernel would launch (head dimensions 64 and 256, fp32), as with the workspace of the query."""
+    kw = dict(num_q_heads=64, num_kv_heads=8, head_dim=64, gamma=4, branch_len=16, kv_dtype="bf16", branch_kv_dtype="bf16")
+    plan = B.la_verify_attention_plan(good_desc(**kw), [8190])
+    assert plan["path"] == 1 and plan["kernel_shape"] == 0
+    assert plan["rows_per_workgroup"] == 32 and plan["row_tiles"] == 16             # 512 rows per KV head
+    n = -(-8190 // plan["chunk_tokens"])
+    assert n > 1 and plan["chunks_total"] == n and plan["workgroups"] == 8 * 16 * n
+    rows = 4 * 16 * 64
+    assert B.la_verify_attention_workspace(good_desc(**kw), [8190]) == n * rows * (64 + 2) * 4
+    assert B.la_verify_attention_plan(good_desc(**kw), [8190], 40) == plan
+    short = B.la_verify_attention_plan(good_desc(**kw, num_requests=2), [100, 0])
+    assert short["chunk_tokens"] == 0 and short["chunks_total"] == 2 and short["workgroups"] == 2 * 8 * 16
+    split = B.la_verify_attention_plan(good_desc(**kw, num_requests=2, kv_split_tokens=64), [100, 0])
+    assert split["chunk_tokens"] == 64 and split["chunks_total"] == 3
+    f32 = dict(q_dtype="f32", kv_dtype="f32", branch_kv_dtype="f32", out_dtype="f32", num_q_heads=4, num_kv_heads=2)
+    plan = B.la_verify_attention_plan(good_desc(**f32, gamma=2, branch_len=9), [256])
+    assert plan == dict(path=1, kernel_shape=0, rows_per_workgroup=16, row_tiles=3, chunk_tokens=0, chunks_total=1,
+                        workgroups=6)
+
+
 @pytest.mark.parametrize("seed", range(8))
 def test_the_planner_refuses_only_what_no_shape_runs(seed):
     """Left to itself the library runs a call exactly where some kernel shape, forced, runs it (random descriptors)."""
