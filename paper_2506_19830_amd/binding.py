@@ -203,14 +203,17 @@ def _host_lens(prefix_lens_host: Sequence[int]):
 def _host_rows(rows):
     """Nested sequence of ints -> C array of int32, one row after the other.  A tree call passes one label per pool
     token, so plain ints are converted in C (378 labels: 49 us through a list and a ctypes constructor, 16 us this way);
-    whatever the array type does not take goes the general way."""
+    a row the array type does not take goes element by element.  Every row is iterated once only."""
     flat = array.array("i")
-    try:
-        for row in rows:
+    for row in rows:
+        if not isinstance(row, (list, tuple)):
+            row = list(row)
+        done = len(flat)
+        try:
             flat.extend(row)
-    except (TypeError, OverflowError):
-        vals = [int(x) for row in rows for x in row]
-        return (ctypes.c_int32 * max(1, len(vals)))(*vals)
+        except (TypeError, OverflowError):
+            del flat[done:]
+            flat.extend(ctypes.c_int32(int(x)).value for x in row)
     if not flat:
         return (ctypes.c_int32 * 1)()
     return (ctypes.c_int32 * len(flat)).from_buffer(flat)

@@ -317,6 +317,28 @@ def test_accept_rejects_bad_arguments():
     assert lib.la_spec_accept(ctypes.byref(d), *args, vp(256), ctypes.c_size_t(1 << 30), vp(0)) == 1
 
 
+@pytest.mark.parametrize("make", [
+    lambda rows: rows, lambda rows: tuple(map(tuple, rows)), lambda rows: (r for r in rows),
+    lambda rows: (iter(r) for r in rows), lambda rows: (map(float, r) for r in rows),
+    lambda rows: iter([rows[0], iter(map(float, rows[1])), tuple(rows[2])]),
+    lambda rows: iter([rows[0], iter([rows[1][0], float(rows[1][1]), rows[1][2]]), rows[2]]),
+])
+def test_host_rows_takes_what_iterates_once(make):
+    """Labels and visible lengths on the host: any nesting of iterables of numbers, also ones that can be walked once
+    only and whose later rows are not plain ints; what does not fit 32 bits wraps as a C conversion does."""
+    rows = [[1, 2, 3], [4, 5, 6], [7, 8, 9]]
+    assert list(B._host_rows(make(rows))) == list(range(1, 10))
+
+
+def test_host_rows_odd_values():
+    import numpy as np
+    import torch
+    assert list(B._host_rows(np.arange(6, dtype=np.int64).reshape(2, 3))) == list(range(6))
+    assert list(B._host_rows(torch.arange(6).reshape(2, 3))) == list(range(6))
+    assert list(B._host_rows([[2 ** 32 + 5, -1], [2 ** 31]])) == [5, -1, -2 ** 31]
+    assert list(B._host_rows([])) == [0] == list(B._host_rows([[], []]))
+
+
 def test_product_package_does_not_import_the_oracle():
     for f in (ROOT / "paper_2506_19830_amd").rglob("*"):
         if f.suffix in (".py", ".hip", ".hpp", ".h", ".cpp"):
