@@ -106,3 +106,17 @@ def test_last_chunk_without_prefix_keys(oracle, case, split, form):
         check_nested(oracle, case, 75, 1e-5, None, split)
     else:
         check_tree(oracle, case, 2, 2, 11, 1e-5, split)
+
+
+@pytest.mark.parametrize("d,storage", [(64, BF16), (64, FP8), (256, BF16)], ids=["d64_bf16", "d64_fp8", "d256_bf16"])
+@pytest.mark.parametrize("requests", [9, 64, 65, 130])
+def test_many_requests(oracle, requests, d, storage):
+    """More requests than the kernel arguments hold (8): each workgroup finds its own, 64 at a time.  Ragged prefixes, some
+    empty, cut into chunks and uncut; the last request's are the longest in the batch."""
+    rng = np.random.default_rng(requests + d)
+    prefix = [int(x) for x in rng.choice([0, 1, 40, 64, 65, 129, 300], size=requests)]
+    prefix[-1], prefix[0] = 391, 0
+    case = _case("many", tuple(prefix), 1, 2, 2, 1, d, storage, paged=True)
+    for split in (0, 64, 192):
+        check_full(oracle, case, 1e-5, split, lse_tol=1e-5)
+    check_nested(oracle, case, 40, 1e-5, None, 128)
