@@ -138,7 +138,8 @@ typedef struct {
                                  bf16 cache and branch K/V: 6 = 8 x 1, 7 = 4 x 2); general
                                  kernel: 0                                                       */
   int32_t rows_per_workgroup; /* query rows (of one KV head) a workgroup owns                    */
-  int32_t row_tiles;          /* workgroups per (KV head, chunk)                                 */
+  int32_t row_tiles;          /* workgroups per (KV head, chunk); 0 = general kernel, one
+                                 wavefront per query row (many requests of a few keys)           */
   int32_t chunk_tokens;       /* prefix tokens per independently reduced chunk; general kernel: as
                                  with the workspace the query asks for, 0 = no prefix is cut     */
   int32_t chunks_total;       /* chunks summed over the requests                                 */

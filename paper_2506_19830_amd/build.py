@@ -18,8 +18,8 @@ CSRC = HERE / "csrc"
 OBJ = HERE / "_build"
 LIB = HERE / "libla_verify.so"
 
-SOURCES = ["api.hip", "attn_mfma.hip", "attn_stream.hip", "attn_merge.hip", "attn_f32.hip", "accept.hip",
-           "accept_static.hip", "kv_commit.hip", "controller.hip"]
+SOURCES = ["api.hip", "attn_mfma.hip", "attn_stream.hip", "attn_merge.hip", "attn_f32.hip", "attn_rows.hip",
+           "accept.hip", "accept_static.hip", "kv_commit.hip", "controller.hip"]
 # benchmark aids (per-kernel event timing, calibration kernels, a self-test hook): only in libla_verify_bench.so,
 # which is the product library's objects linked together with these
 BENCH_SOURCES = ["bench_aids.hip", "calibrate.hip"]

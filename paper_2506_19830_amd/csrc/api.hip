@@ -75,7 +75,7 @@ struct AttnPlan {
   AttnPath path;
   bool kv_fp8, br_fp8;
   int shape, tile_m, n_row_tiles, chunk_len, last_short, s_max, total_units;
-  // (general path: shape = row blocks of 16 per workgroup; the workspace is optional there)
+  // (general path: shape = row blocks of 16 per workgroup, 0 = a wavefront per row; the workspace is optional there)
   size_t part_o_bytes, part_ml_bytes;
 };
 
@@ -153,6 +153,31 @@ void make_general_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, i
   }
   size_partials(d, prefix_lens_host, plan);
   if (plan->s_max == 1) plan->part_o_bytes = plan->part_ml_bytes = 0;   // the kernel writes the output itself
+}
+
+// Does a general-path call run one wavefront per query row (attn_rows.hip) instead of matrix tiles?  Both times are
+// estimated in microseconds for `units` (request, KV head) pairs of R rows that see at most `keys` keys: the matrix kernel
+// takes a time per unit whatever it holds, the other one per key and row, and at least the latency of its walk.
+// (Fitted to 512 to 16384 units of 1 to 8 rows and 1 to 63 keys; with 8 rows and one key, 4096 units take 23 against 63 us
+// at head dimension 64, fp32; with 16 rows the matrix kernel is the faster one at any length: 88 against 74 us.  What the
+// fit gets wrong, over 252 such points, is 13 us at most and more than 6 us at five of them.)
+// chain_len: tokens of the drafted chain or pool.
+bool general_by_rows(const la_attn_desc *d, const int32_t *prefix_lens_host, int chain_len) {
+  const int R = d->gamma * d->branch_len * (d->num_q_heads / d->num_kv_heads);
+  if (R > 8 || (int64_t)d->num_requests * d->num_kv_heads * R > attn_rows_max()) return false;
+  int64_t longest = 0;
+  for (int b = 0; b < d->num_requests; ++b) longest = prefix_lens_host[b] > longest ? prefix_lens_host[b] : longest;
+  const int64_t keys = longest + chain_len + d->branch_len;
+  if (keys > (d->head_dim == 64 ? 48 : 64)) return false;   // (64: one round of the walk)
+  const bool f32 = d->kv_dtype == LA_F32, fp8 = d->kv_dtype == LA_FP8_E4M3;
+  // per_unit: matrix kernel; even: the keys of one row at which many units take the same time either way
+  const double per_unit = d->head_dim == 64 ? (f32 ? 0.015 : 0.0085) : d->head_dim == 128 ? 0.016 : fp8 ? 0.024 : 0.028;
+  const double even = d->head_dim == 64 ? (f32 ? 77.0 : fp8 ? 52.0 : 48.0) : d->head_dim == 128 || fp8 ? 77.0 : 100.0;
+  // rows of a unit share their keys through the caches; a workgroup's four rows fall into one unit only if R divides
+  const double shared = (0.55 + 0.45 * R) * ((R & (R - 1)) ? 1.25 : 1.0);
+  const double matrix_us = 3.0 + per_unit * (double)d->num_requests * d->num_kv_heads;
+  const double walk_us = 4.0 + (double)keys * (0.2 + d->head_dim / 400.0), launch_us = 10.0;
+  return (double)keys * shared < even && walk_us < matrix_us && launch_us < matrix_us;
 }
 
 // The same plan serves the flat, nested and tree forms of a call (count_extra_tiles shifts its chunk ranges for a chain).
@@ -394,6 +419,12 @@ la_status la_verify_attention_plan(const la_attn_desc *desc, const int32_t *pref
   if (st != LA_OK) return st;
   memset(out, 0, sizeof *out);
   out->path = (int32_t)plan.path;
+  if (plan.path == PATH_F32 && general_by_rows(desc, prefix_lens_host, chain_len)) {
+    out->rows_per_workgroup = 4;
+    out->chunks_total = desc->num_requests;
+    out->workgroups = (int32_t)(((int64_t)desc->num_requests * desc->gamma * desc->branch_len * desc->num_q_heads + 3) / 4);
+    return LA_OK;
+  }
   if (plan.path == PATH_MFMA) out->kernel_shape = plan.shape + 1;
   out->rows_per_workgroup = plan.tile_m;
   out->row_tiles = plan.n_row_tiles;
@@ -442,6 +473,7 @@ static la_status verify_attention(const la_attn_desc *desc, const void *q, const
   if (chain_len > 0 && !tree)
     for (int64_t t = 0; t < (int64_t)desc->num_requests * desc->gamma; ++t)
       seen = chain_vis_host[t] > seen ? chain_vis_host[t] : seen;
+  if (plan.path == PATH_F32 && general_by_rows(desc, prefix_lens_host, chain_len)) plan.shape = 0;
   count_extra_tiles(desc, seen, &plan);
   const size_t need = plan.part_o_bytes + plan.part_ml_bytes;
   bool partials = need > 0;
@@ -493,6 +525,7 @@ static la_status verify_attention(const la_attn_desc *desc, const void *q, const
     }
   }
   if (plan.path == PATH_F32) {
+    if (plan.shape == 0) return launch_attn_rows(p, stream) == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
     if (launch_attn_f32(p, plan.shape, stream) != hipSuccess) return LA_ERR_LAUNCH;
     return !partials || launch_attn_merge(p, stream) == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
   }

@@ -121,6 +121,9 @@ hipError_t launch_attn_stream(const AttnParams &p, int shape, hipStream_t stream
 hipError_t launch_attn_merge(const AttnParams &p, hipStream_t stream);
 // row_blocks: blocks of 16 query rows per workgroup (p.n_row_tiles counts those workgroups)
 hipError_t launch_attn_f32(const AttnParams &p, int row_blocks, hipStream_t stream);
+// the same, one wavefront per query row: at most attn_rows_max() rows over all requests, never split
+int64_t attn_rows_max();
+hipError_t launch_attn_rows(const AttnParams &p, hipStream_t stream);
 
 // ----------------------------------------------------------------------------
 // Speculative accept / resample.

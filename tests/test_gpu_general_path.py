@@ -120,3 +120,38 @@ def test_many_requests(oracle, requests, d, storage):
     for split in (0, 64, 192):
         check_full(oracle, case, 1e-5, split, lse_tol=1e-5)
     check_nested(oracle, case, 40, 1e-5, None, 128)
+
+
+def _by_rows(case, chain_len=0):
+    return B.la_verify_attention_plan(attn_desc(case), list(case.prefix_lens), chain_len)["row_tiles"] == 0
+
+
+ROWS = [
+    # (case, by rows in the flat call): units of 1 to 8 rows, prefixes up to the last length one round of 64 keys holds
+    (_case("rows_f32", (0, 15, 16, 3, 0, 1, 7, 12), 1, 1, 128, 128, 64, F32, paged=True), True),
+    (_case("rows_f32_d128", tuple([9, 0, 17, 1] * 3), 2, 1, 200, 100, 128, F32), True),
+    (_case("rows_f32_d256", (62, 5, 62, 0), 1, 1, 1024, 1024, 256, F32, paged=True), True),
+    (_case("rows_f32_past", (64, 5, 62, 0), 1, 1, 1024, 1024, 256, F32, paged=True), False),
+    (_case("rows_bf16", (7, 16, 2), 1, 2, 500, 500, 64, BF16, out="bf16"), True),
+    (_case("rows_bf16_d256", (11, 0, 30, 4), 1, 1, 750, 250, 256, BF16, paged=True, block_size=32), True),
+    (_case("rows_fp8", (13, 5), 1, 1, 600, 600, 64, FP8), True),
+    (_case("rows_fp8_d256", (9, 14), 2, 2, 400, 400, 256, FP8, paged=True), True),
+    (_case("rows_mixed", (6, 0, 11), 3, 1, 400, 400, 64, MIXED, paged=True), True),
+    (_case("rows_mixed_d256", (3, 8, 1), 2, 2, 800, 400, 256, MIXED, out="bf16"), True),
+    (_case("rows_nine", (3, 8, 1), 3, 3, 400, 400, 64, F32), False),
+    (_case("rows_few_units", (3, 8, 1), 1, 1, 40, 40, 64, F32), False),
+]
+
+
+@pytest.mark.parametrize("case,flat_by_rows", ROWS, ids=lambda v: getattr(v, "name", ""))
+def test_one_wavefront_per_row(oracle, case, flat_by_rows):
+    """Many requests or KV heads with a few rows of a few keys each: a kernel of its own, on both sides of its rule."""
+    assert _by_rows(case) == flat_by_rows
+    tol = 1e-5 if case.out_dtype == "f32" else 5e-3
+    check_full(oracle, case, tol, lse_tol=1e-5)
+    check_full(oracle, case, tol, 64, lse_tol=1e-5)
+    assert not _by_rows(case, 75) and (not flat_by_rows or case.name == "rows_f32_d256" or _by_rows(case, 1))
+    vis = np.random.default_rng(case.seed).integers(0, 5, size=(case.B, case.gamma))
+    check_nested(oracle, case, 4, tol, vis)
+    check_nested(oracle, case, 75, tol)
+    check_tree(oracle, case, 2, 1, 2, tol)
