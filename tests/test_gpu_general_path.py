@@ -155,3 +155,31 @@ def test_one_wavefront_per_row(oracle, case, flat_by_rows):
     check_nested(oracle, case, 4, tol, vis)
     check_nested(oracle, case, 75, tol)
     check_tree(oracle, case, 2, 1, 2, tol)
+
+
+def test_more_workgroups_than_one_grid_dimension_takes():
+    """4.2 million requests of one row: more threads than one dimension of a launch may have (2^32).  All requests share
+    one prefix, through the block table, so the reference is a plain product."""
+    n, prefix, d, bs = (1 << 22) + 5, 100, 64, 16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    draw = lambda *shape: torch.randn(shape, generator=gen, device="cuda")
+    q, kb, vb = draw(n, 1, 1, 1, d), draw(n, 1, 1, 1, d), draw(n, 1, 1, 1, d)
+    blocks = -(-prefix // bs)
+    kc, vc = draw(blocks, 1, bs, d), draw(blocks, 1, bs, d)
+    table = torch.arange(blocks, dtype=torch.int32, device="cuda").repeat(n, 1)
+    desc = B.make_attn_desc(num_requests=n, num_q_heads=1, num_kv_heads=1, head_dim=d, gamma=1, branch_len=1, block_size=bs,
+                            max_blocks_per_request=blocks, q_dtype="f32", kv_dtype="f32", branch_kv_dtype="f32",
+                            out_dtype="f32", softmax_scale=d ** -0.5)
+    lens = [prefix] * n
+    assert B.la_verify_attention_plan(desc, lens)["workgroups"] == n
+    out = torch.full_like(q, float("nan"))
+    B.la_verify_attention(desc, q, kc, vc, table, torch.full((n,), prefix, dtype=torch.int32, device="cuda"), lens, kb, vb,
+                          None, None, out, None, None)
+    k, v = kc.reshape(-1, d)[:prefix], vc.reshape(-1, d)[:prefix]
+    for at in range(0, n, 1 << 20):
+        x, y, z = (t[at:at + (1 << 20)].reshape(-1, d) for t in (q, kb, vb))
+        p = torch.softmax(torch.cat([x @ k.T, (x * y).sum(1, keepdim=True)], 1) * d ** -0.5, 1)
+        ref = p[:, :prefix] @ v + p[:, prefix:] * z
+        err = (out[at:at + (1 << 20)].reshape(-1, d) - ref).abs().amax(1) / ref.abs().amax(1)
+        assert float(err.max()) <= 1e-5
