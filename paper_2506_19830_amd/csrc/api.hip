@@ -275,6 +275,8 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, Attn
     const int64_t slots = (int64_t)num_cus() * si.per_cu;
     const int64_t longest = max_chunk(si, last_short);
     if (!chunk_fits(longest)) continue;
+    const double t_step = R > si.tile_m ? si.t_step_shared : si.t_step;
+    const double shared_us = (double)base_wgs * (double)(T + last_short) * 64.0 / si.step_keys / (double)slots * t_step;
     double prev_cost = 0.0;
     for (int n = 1; n <= 512; ++n) {
       int64_t len = max_p > 0 ? (max_p + n - 1) / n : 64;
@@ -285,14 +287,42 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, Attn
       for (int b = 0; b < d->num_requests; ++b) units += attn_num_chunks(prefix_lens_host[b], (int)len);
       const int64_t rounds = (base_wgs * units + slots - 1) / slots;
       const double merge_us = 3.0 + (double)units * n_rows * (d->head_dim + 2) * 4.0 / 3.0e6;  // read at ~3 TB/s
+      const double margin = si.stream && si.fp8 && rounds > 1 ? 1.06 : 1.0;
+      // One request: whatever the chunks, the slots share all steps, every round starts workgroups and the merge reads more
+      // partials the more chunks there are.  Once that alone costs the best plan so far, no later count can win.
+      if (d->num_requests == 1 && best_shape >= 0 &&
+          (merge_us + margin * ((double)rounds * si.t_fixed + shared_us)) * (1.0 - 1e-9) >= best_cost)
+        break;
       const int64_t n_max = attn_num_chunks((int)max_p, (int)len);
       const int64_t wg_tiles = (T + last_short + n_max - 1) / n_max;  // of the longest request
       const int64_t wg_steps = (wg_tiles * 64 + si.step_keys - 1) / si.step_keys;
-      const double t_step = R > si.tile_m ? si.t_step_shared : si.t_step;
-      // (an fp8 streaming plan of several rounds has measured at its model cost, the row-tile shapes it competes with there
-      // -- partly filled row tiles of 256 rows -- below theirs: the margin keeps those cases with the row tiles)
       double busy_us = (double)rounds * ((double)wg_steps * t_step + si.t_fixed);
-      if (d->num_requests > 1 && rounds > 1 && n <= 8 && units <= 64) {
+      bool model = d->num_requests > 1 && rounds > 1 && n <= 8 && units <= 64;
+      if (model && best_shape >= 0 && base_wgs * units <= 2 * slots) {
+        // Dealing the workgroups out costs microseconds of host time per candidate, and every call plans: not where even
+        // a bound of the result from below (the mean over the slots; `rounds` of the shortest workgroups on one slot; the
+        // longest one) leaves the best plan so far in place.  (Below twice the slots, where neither this candidate's cost
+        // nor the next one's ends the search.  Eight requests of 1500 keys, one row per KV head: 50 -> 15 us per plan.)
+        double total = 0.0, shortest = 0.0, longest_wg = 0.0;
+        for (int b = 0; b < d->num_requests; ++b) {
+          const int64_t nc = attn_num_chunks(prefix_lens_host[b], (int)len);
+          const int64_t tiles_b = (prefix_lens_host[b] + 63) / 64 + last_short;
+          const int64_t lo_tiles = tiles_b / nc, n_hi = tiles_b % nc;
+          const double lo = (double)((lo_tiles * 64 + si.step_keys - 1) / si.step_keys) * t_step + si.t_fixed;
+          const double hi = (double)(((lo_tiles + 1) * 64 + si.step_keys - 1) / si.step_keys) * t_step + si.t_fixed;
+          total += (double)base_wgs * (lo * (double)(nc - n_hi) + hi * (double)n_hi);
+          shortest = b == 0 || lo < shortest ? lo : shortest;
+          longest_wg = (n_hi ? hi : lo) > longest_wg ? (n_hi ? hi : lo) : longest_wg;
+        }
+        double bound = total / (double)slots;
+        bound = bound > (double)rounds * shortest ? bound : (double)rounds * shortest;
+        bound = bound > longest_wg ? bound : longest_wg;
+        if (bound * margin * (1.0 - 1e-9) + merge_us >= best_cost) {
+          busy_us = bound;
+          model = false;
+        }
+      }
+      if (model) {
         // Several requests of different lengths in several rounds, few chunks each: rounds x the longest chunk is
         // what the dispatch of equal workgroups gives; with unequal ones the workgroups are dealt out here as the
         // hardware deals them, in launch order (all workgroups of a chunk, chunk after chunk, request after request),
@@ -346,7 +376,7 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, Attn
       }
       // (an fp8 streaming plan of several rounds has measured at its model cost, the row-tile shapes it competes with there
       // -- partly filled row tiles of 256 rows -- below theirs: the margin keeps those cases with the row tiles)
-      const double cost = busy_us * (si.stream && si.fp8 && rounds > 1 ? 1.06 : 1.0) + merge_us;
+      const double cost = busy_us * margin + merge_us;
       if (best_shape < 0 || cost < best_cost)
         best_cost = cost, best_len = (int)len, best_shape = shape, best_short = last_short;
       if (len <= 64 || d->kv_split_tokens) break;
