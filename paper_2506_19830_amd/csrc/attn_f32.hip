@@ -420,37 +420,6 @@ struct General {
   }
 };
 
-// attn_select_chunk for more requests than the kernel arguments hold.  This path serves batches of any size, every one of
-// whose workgroups has to find its request: 64 requests at a time, a lane counting the chunks of one (1024 requests cut
-// into chunks of 64 keys, head dimension 64: 110 us, 1290 us with a walk over one request after the other; uncut, where
-// the unit is the request: 63 against 483 us at 1024 requests, 223 against 6700 us at 4096).
-__device__ __forceinline__ ChunkSel select_chunk_of_many(const AttnParams &p, int unit, int lane) {
-  ChunkSel s;
-  for (int b0 = 0;; b0 += 64) {
-    const int own_b = min(b0 + lane, p.B - 1), P = p.prefix_lens[own_b];
-    const int own = b0 + lane < p.B ? attn_num_chunks(P, p.chunk_len) : 0;
-    int incl = own;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int up = __shfl_up(incl, off);
-      if (lane >= off) incl += up;
-    }
-    const int total = __builtin_amdgcn_readlane(incl, 63);
-    if (unit >= total && b0 + 64 < p.B) {
-      unit -= total;
-      continue;
-    }
-    const uint64_t behind = __builtin_amdgcn_ballot_w64(incl > unit);
-    const int at = behind ? __builtin_ctzll(behind) : min(63, p.B - 1 - b0);
-    s.b = b0 + at;
-    s.P = __builtin_amdgcn_readlane(P, at);
-    s.n_chunks = __builtin_amdgcn_readlane(own, at);
-    s.c = s.n_chunks - 1 - (unit - (__builtin_amdgcn_readlane(incl, at) - s.n_chunks));
-    attn_chunk_range(s.P, p.chunk_len, p.last_short, s.c, &s.k_begin, &s.k_end);
-    return s;
-  }
-}
-
 template <int D, int KV, int BR, int RB, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_general_kernel(const AttnParams p) {
   using G = General<D, KV, BR, RB, NW>;
@@ -471,10 +440,8 @@ __global__ __launch_bounds__(64 * NW) void attn_general_kernel(const AttnParams 
   if (G::kF32 || (p.s_max == 1 && !p.n_inline)) {   // not split: the unit is the request
     sel.b = __builtin_amdgcn_readfirstlane(id / p.n_row_tiles), sel.c = 0, sel.n_chunks = 1, sel.k_begin = 0;
     sel.P = sel.k_end = __builtin_amdgcn_readfirstlane(p.prefix_lens[sel.b]);
-  } else if (p.n_inline) {
-    sel = attn_select_chunk(p, __builtin_amdgcn_readfirstlane(id / p.n_row_tiles));
   } else {
-    sel = select_chunk_of_many(p, __builtin_amdgcn_readfirstlane(id / p.n_row_tiles), g.lane);
+    sel = attn_select_chunk<true>(p, __builtin_amdgcn_readfirstlane(id / p.n_row_tiles));
   }
   g.b = sel.b, g.P = sel.P;
   const bool last_chunk = sel.c == sel.n_chunks - 1;

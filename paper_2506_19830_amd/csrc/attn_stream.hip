@@ -1099,7 +1099,7 @@ __device__ __forceinline__ bool stream16_chunk(const AttnParams &p, uint8_t *lds
   const int kvh = __builtin_amdgcn_readfirstlane(id % p.Hkv);
   id = __builtin_amdgcn_readfirstlane(id / p.Hkv);
   const int row_tile = __builtin_amdgcn_readfirstlane(id % p.n_row_tiles);
-  const ChunkSel sel = attn_select_chunk(p, __builtin_amdgcn_readfirstlane(id / p.n_row_tiles));
+  const ChunkSel sel = attn_select_chunk<true>(p, __builtin_amdgcn_readfirstlane(id / p.n_row_tiles));
   const int b = sel.b, n_chunks = sel.n_chunks, c = sel.c, k_begin = sel.k_begin, k_end = sel.k_end;
   const int n_pre_tiles = (k_end - k_begin + kTileN - 1) / kTileN;
   const int n_pre_steps = (n_pre_tiles + KSL - 1) / KSL;

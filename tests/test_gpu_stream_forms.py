@@ -98,3 +98,17 @@ def test_forced_shape(oracle, kv, kernel_shape, monkeypatch):
             tree["seg_mask"][:] = 0
             for got, lse in (run_attention_nested(case, inp, chain, split), run_attention_tree(case, inp, tree, split)):
                 assert np.array_equal(got, flat) and np.array_equal(lse, flat_lse)
+
+
+@pytest.mark.parametrize("kv", ["fp8_e4m3", "bf16"])
+@pytest.mark.parametrize("requests", [9, 64, 65, 130])
+def test_many_requests(oracle, requests, kv):
+    """More requests than the kernel arguments hold (8): ragged prefixes, some empty, cut into chunks and uncut."""
+    rng = np.random.default_rng(requests)
+    prefix = [int(x) for x in rng.choice([0, 1, 40, 64, 65, 129, 300], size=requests)]
+    prefix[-1], prefix[0] = 391, 0
+    case = make_case(kv, tuple(prefix), 2, 2, 4, 2, True, seed=410)
+    for split in (0, 64, 192):
+        check_full(oracle, case, TOL_LOWP, split)
+    check_nested(oracle, case, 70, TOL_LOWP, None, 128)
+    check_tree(oracle, case, 2, 2, 9, TOL_LOWP, 128)
