@@ -15,8 +15,10 @@ CASES = [
     W.AcceptCase("seg_p999", 8, 4, 32003, "f32", temperature=1.0, top_p=0.999, seed=521),
     W.AcceptCase("seg_flat", 8, 4, 32000, "bf16", target_std=0.5, temperature=1.0, top_p=0.9, seed=522),
     W.AcceptCase("seg_cold", 8, 4, 32000, "bf16", temperature=0.05, top_p=0.95, seed=523),
-    # long drafts: segments too small to hold anything
+    # long drafts: segments of 80 bytes (32 keys), which overflow; of 48 bytes, too small to be used at all
     W.AcceptCase("seg_long_draft", 2, 90, 4096, "bf16", temperature=0.6, top_p=0.95, seed=524),
+    W.AcceptCase("seg_no_segment", 2, 150, 4096, "bf16", temperature=0.6, top_p=0.95, seed=526),
+    W.AcceptCase("seg_no_segment_f32", 2, 200, 4100, "f32", temperature=0.6, top_p=0.95, seed=527),
     W.AcceptCase("seg_lookup", 6, 8, 152064, "bf16", temperature=0.6, top_p=0.95, point_mass=True, peak=14.0, seed=525),
 ]
 

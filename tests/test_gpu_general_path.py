@@ -64,6 +64,54 @@ def test_single_stage_over_many_blocks(oracle, storage):
     """Head dimension 256 keeps one K stage per wavefront, which every block overwrites: unsplit, 17 to 33 blocks each."""
     case = _case("wide_long", (4130,), 1, 5, 3, 1, 256, storage, paged=True)
     check_full(oracle, case, 1e-5, 0 if storage is F32 else 8192, lse_tol=1e-5)
+
+
+FORMS = [
+    # every storage type and head dimension: row blocks of 16 and 32, ragged and empty prefixes, tails of 1 to 63 keys
+    *[_case(f"forms_d{d}_{name}", (700, 0, 65, 333), 3, 11, 4, 2, d, storage, paged=True)
+      for d in (64, 256) for name, storage in (("bf16", BF16), ("fp8", FP8), ("mixed", MIXED))],
+    _case("forms_d64_rows16", (1100, 31), 2, 2, 8, 2, 64, MIXED, block_size=64),
+    _case("forms_f32_d64", (130, 0, 63), 3, 9, 4, 2, 64, F32, paged=True),
+    _case("forms_f32_d256", (130, 17), 3, 5, 4, 2, 256, F32),
+]
+
+
+@pytest.mark.parametrize("split", [0, 64, 320])
+@pytest.mark.parametrize("case", FORMS, ids=lambda c: c.name)
+def test_nested_and_tree(oracle, case, split):
+    """Chains around a key block of 32 (fp32: 16), visible parts of any length; trees of two shapes.  The last chunk takes
+    the prefix's tail, the chain or pool and the rows' own tokens in this order."""
+    rng = np.random.default_rng(split + case.seed)
+    for chain_len in (1, 15, 31, 32, 33, 130):
+        vis = rng.integers(0, chain_len + 1, size=(case.B, case.gamma))
+        vis[0, 0], vis[-1, -1] = 0, chain_len
+        check_nested(oracle, case, chain_len, 1e-5, vis, split)
+    for width, depth, step_len in ((2, 2, 11), (3, 1, 32)):
+        check_tree(oracle, case, width, depth, step_len, 1e-5, split)
+
+
+@pytest.mark.parametrize("idx", range(18))
+def test_random_shapes(oracle, idx):
+    """Flat, nested and tree calls of low-precision storage at head dimensions 64 and 256, everything else drawn."""
+    rng = np.random.default_rng(3000 + idx)
+    hkv, g = int(rng.choice([1, 2, 4])), int(rng.choice([1, 2, 5, 8]))
+    gamma, L = int(rng.choice([1, 2, 3, 5])), int(rng.choice([1, 2, 7, 16, 33, 90]))
+    prefix = tuple(int(x) for x in rng.choice([0, 1, 15, 64, 65, 200, 513, 1100], size=int(rng.choice([1, 2, 3, 10]))))
+    while len(prefix) * gamma * L * hkv * g > 4000:
+        L = max(1, L // 2)
+    case = _case("random", prefix, gamma, L, hkv * g, hkv, (64, 256)[idx % 2], (BF16, FP8, MIXED)[idx // 2 % 3],
+                 block_size=int(rng.choice([16, 32, 128])), paged=bool(rng.integers(0, 2)))
+    split = int(rng.choice([0, 64, 128, 448]))
+    kind = idx // 6
+    if kind == 0:
+        check_full(oracle, case, 1e-5, split, lse_tol=1e-5)
+    elif kind == 1:
+        chain_len = int(rng.choice([1, 5, 64, 65, 130]))
+        check_nested(oracle, case, chain_len, 1e-5, rng.integers(0, chain_len + 1, size=(case.B, gamma)), split)
+    else:
+        check_tree(oracle, case, *((2, 2), (2, 3), (3, 2))[int(rng.integers(0, 3))], int(rng.choice([1, 4, 17])), 1e-5, split)
+
+
 def _empty_last_chunk(case, split):
     """Does some request's last chunk hold no prefix key?  (The tiles of 64 keys are dealt out evenly, the last chunk
     counted as carrying the branch-private ones.)"""
