@@ -96,8 +96,8 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
 }
 
 // Sum over the 16 lanes of a DPP row, on the vector ALU (a shuffle goes through the LDS pipeline, two accesses per
-// double and step, which the workgroups of the fp64 kernels were queueing for).  The lanes of a row hold the same sum
-// in different orders: take it from one lane.
+// double and step, which the workgroups of the fp64 kernels were queueing for).  Every lane of a row ends with
+// the same bits: each step adds the same pairs in all of them, in one order or the other.
 template <int ROT>
 __device__ __forceinline__ double row_rotate(double v) {
   const uint64_t u = __builtin_bit_cast(uint64_t, v);

@@ -1,20 +1,20 @@
 // Merge of the split-prefix partials of verify attention (gfx950).
 //
-// Every (row tile, kv head, chunk) workgroup of the MFMA kernel leaves an
-// unnormalised partial (O_s, m_s, l_s) per query row, m in log2 units.  The exact
-// softmax over the union of the chunks is
+// Every (row tile, kv head, chunk) workgroup of the row-tile, streaming and
+// general kernels leaves an unnormalised partial (O_s, m_s, l_s) per query row,
+// m in log2 units.  The exact softmax over the union of the chunks is
 //     M = max_s m_s,   w_s = 2^(m_s - M),   O = sum_s w_s O_s / sum_s w_s l_s,
 //     lse = ln2 * (M + log2 sum_s w_s l_s).
-// One wavefront owns one output row: lane s < n_s loads (m_s, l_s), the maximum
-// and the denominator are wavefront shuffle reductions, the weights are then
-// broadcast lane by lane while each lane accumulates its D / 64 output columns.
+// More than eight chunks: one wavefront owns one output row, lane s < n_s loads
+// (m_s, l_s), the maximum and the denominator are wavefront shuffle reductions,
+// the weights are then broadcast lane by lane while each lane accumulates its
+// D / 64 output columns.  Up to eight: D / 4 threads own a row (below).
 #include "la_internal.hpp"
 
 namespace la {
 namespace {
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
 constexpr int kWaves = 4;
 

@@ -687,8 +687,6 @@ __device__ __forceinline__ bool stream_chunk(const AttnParams &p, uint8_t *lds, 
     for (int db = 0; db < 4; ++db) voff[db] = keyl * kRowBytes + (((2 * db + (grp & 1)) ^ fv) * 16) + 8 * (a & 1);
   }
   RowState<1> st;
-  st.row_tok[0] = row_tok;
-  st.row_bstart[0] = (row_tok / p.L) * p.L;
   st.m_run[0] = -INFINITY;
   st.l_run[0] = 0.f;
   st.base[0] = 0.f;
@@ -1120,8 +1118,6 @@ __device__ __forceinline__ bool stream16_chunk(const AttnParams &p, uint8_t *lds
   const int row = r0 + rb * 32 + ln;
   const int rr = min(row, p.R - 1), row_tok = rr / p.G;
   {
-    st.row_tok[0] = row_tok;
-    st.row_bstart[0] = (row_tok / p.L) * p.L;
     const uint8_t *qrow =
         (const uint8_t *)p.q + (((size_t)b * gl + row_tok) * p.Hq + kvh * p.G + (rr % p.G)) * (size_t)(kD * 2);
 #pragma unroll
