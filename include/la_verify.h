@@ -95,7 +95,8 @@ typedef enum {
  *  arrays the host cannot inspect: they must be positive and finite (a zero,
  *  negative or non-finite scale gives undefined results, not an error code).
  *  Every query row must see at least one key (always true: a token sees
- *  itself), and K, V, Q must be finite.
+ *  itself), and K, V, Q must be finite: a value that is not may reach every
+ *  row of its request, also those it is hidden from (requests are apart).
  * ------------------------------------------------------------------------- */
 typedef struct {
   int32_t num_requests;            /* B >= 1                                           */

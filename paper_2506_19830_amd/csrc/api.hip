@@ -253,10 +253,11 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, Attn
   // also runs the branch-private tiles (masked, general form: about three prefix tiles each in the row-tile
   // shapes, whole pipeline steps in the streaming shapes), which count as `last_short` tiles of its share.
   // With a bf16 cache the row-tile shapes are left to calls that force them (and to block strides the streaming shapes
-  // cannot address): over 45 calls of all forms, 24 to 1400 rows and 300 to 32768 keys, the better of the two bf16
-  // streaming shapes took 0.60 to 1.0 of the better row-tile shape's time (27434 + 12924 + 3678 + 3540 keys, 32 rows:
-  // 41 against 59 us; 8475 + 546 keys, 728 rows: 49 against 66 us).  A chunk length asked for (kv_split_tokens) that only
-  // the row tiles can hold, with twice the streaming shapes' table of block ids, leaves the call to them as well.
+  // cannot address): over 48 calls of all forms, 15 to 3248 rows and 295 to 32450 keys, the better of the two bf16
+  // streaming shapes took 0.7 to 1.0 of the better row-tile shape's time, 0.85 in the mean (29697 + 21770 + 18197 keys,
+  // 112 rows: 65 against 95 us; 25402 keys, 3248 rows: 180 against 200 us).  A chunk length asked for (kv_split_tokens)
+  // that only the row tiles can hold, with twice the streaming shapes' table of block ids, leaves the call to them as
+  // well.
   bool skip_row_tiles = false;
   if (d->kernel_shape == 0 && !plan->kv_fp8)
     for (int shape = attn_mfma_num_shapes(); shape < num_shapes(); ++shape) {
