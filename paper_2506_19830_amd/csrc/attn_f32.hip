@@ -431,8 +431,7 @@ __global__ __launch_bounds__(64 * NW) void attn_general_kernel(const AttnParams 
   g.m = g.lane & 15, g.kg = g.lane >> 4;
   g.ring = lds + g.wave * (G::kStages * G::kStageBytes);
   g.ring_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t *)g.ring;
-  int id = (int)(blockIdx.x + blockIdx.y * gridDim.x);
-  if (id >= p.Hkv * p.n_row_tiles * p.total_units) return;   // (the grid's last row; the whole workgroup)
+  int id = blockIdx.x + p.first_wg;
   g.kvh = __builtin_amdgcn_readfirstlane(id % p.Hkv);
   id = __builtin_amdgcn_readfirstlane(id / p.Hkv);
   const int row_tile = __builtin_amdgcn_readfirstlane(id % p.n_row_tiles);
@@ -618,8 +617,6 @@ __global__ __launch_bounds__(64 * NW) void attn_general_kernel(const AttnParams 
   }
 }
 
-constexpr int64_t kMaxGridX = 1 << 21;   // workgroups of at most 1024 threads
-
 template <int D, int KV, int BR, int RB, int NW>
 hipError_t launch_shape(const AttnParams &p, hipStream_t stream) {
   using G = General<D, KV, BR, RB, NW>;
@@ -634,10 +631,15 @@ hipError_t launch_shape(const AttnParams &p, hipStream_t stream) {
   if (configured != hipSuccess) return configured;
   if (p.n_row_tiles != (p.R + 16 * RB - 1) / (16 * RB)) return hipErrorInvalidValue;
   const int64_t grid = (int64_t)p.Hkv * p.n_row_tiles * p.total_units;
-  if (grid > INT32_MAX - kMaxGridX) return hipErrorInvalidValue;
-  // (one dimension of a launch holds less than 2^32 threads; the runtime drops what is beyond without an error)
-  const dim3 wgs((unsigned)(grid < kMaxGridX ? grid : kMaxGridX), (unsigned)((grid + kMaxGridX - 1) / kMaxGridX));
-  hipLaunchKernelGGL(kern, wgs, dim3(64 * NW), kLds, stream, p);
+  if (grid > INT32_MAX) return hipErrorInvalidValue;
+  // (a launch holds less than 2^32 threads; the runtime drops what is beyond without an error)
+  constexpr int64_t kMaxGrid = 1 << 21;
+  AttnParams q = p;
+  for (int64_t at = 0; at < grid; at += kMaxGrid) {
+    q.first_wg = (int)at;
+    const unsigned wgs = (unsigned)(grid - at < kMaxGrid ? grid - at : kMaxGrid);
+    hipLaunchKernelGGL(kern, dim3(wgs), dim3(64 * NW), kLds, stream, q);
+  }
   return hipGetLastError();
 }
 

@@ -49,8 +49,11 @@ struct AttnParams {
   int out_f32;      // output dtype: 1 = fp32, 0 = bf16
   int q_type, kv_type, br_type;  // la_dtype of Q, of the prefix cache, of the branch / chain / pool K and V
   float scale_log2; // softmax_scale * log2(e)
-  int force_again;  // streaming shapes (fp8): start with the give-up flag raised, so that every workgroup also runs its
-                    // second attempt (a self-test hook of the benchmark library; 0 otherwise)
+  union {
+    int force_again;  // streaming shapes (fp8): start with the give-up flag raised, so that every workgroup also runs its
+                      // second attempt (a self-test hook of the benchmark library; 0 otherwise)
+    int first_wg;     // general kernel: number of the launch's first workgroup (calls too large for one launch)
+  };
   // With few requests what a workgroup needs to find its chunk travels in the kernel arguments, prepared by the host
   // from its copy of the prefix lengths, so that no kernel start waits on a dependent load of prefix_lens or on
   // integer divisions: n_inline = B if B <= kMaxInlineLens, else 0.
