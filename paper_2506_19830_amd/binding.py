@@ -206,13 +206,17 @@ def _host_rows(rows):
     a row the array type does not take goes element by element.  Every row is iterated once only."""
     flat = array.array("i")
     for row in rows:
-        if not isinstance(row, (list, tuple)):
+        if type(row) is not list:
             row = list(row)
-        done = len(flat)
         try:
             flat.extend(row)
         except (TypeError, OverflowError):
-            del flat[done:]
+            for x in row:                       # what the array took of this row comes off again
+                try:
+                    array.array("i", (x,))
+                except (TypeError, OverflowError):
+                    break
+                flat.pop()
             flat.extend(ctypes.c_int32(int(x)).value for x in row)
     if not flat:
         return (ctypes.c_int32 * 1)()
