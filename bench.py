@@ -590,7 +590,7 @@ def main():
     kernel_name = ("attn_mfma_kernel" if plan["kernel_shape"] < 3 else
                    "attn_stream_kernel" if plan["kernel_shape"] < 6 else "attn_stream16_kernel")
     attn_ms = sum(prof_all[k][1] for k in ("attn_mfma", "attn_merge"))
-    accept_ms = sum(prof_all[k][1] for k in ("accept_stats", "accept_warp", "accept_decide", "accept_resid",
+    accept_ms = sum(prof_all[k][1] for k in ("accept_stats", "accept_warp", "accept_sample",
                                              "accept_pick") if k in prof_all)
     stats_launches, stats_ms = prof["accept_stats"]
     stats_gbs = acc_case.algorithmic_bytes() / (stats_ms / max(1, stats_launches) * 1e-3) / 1e9

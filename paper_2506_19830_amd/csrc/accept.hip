@@ -9,17 +9,14 @@
 //   stats   one coalesced pass over every logit row (NB*(2K+1) rows x V): per (row, slice)
 //           the exact maximum and sum 2^((x-max)*log2e/T), fp32.  This is the HBM-bound
 //           part: each logit is read exactly once, 16-byte loads, eight in flight per lane.
-//   decide  grid (fine slices, NB): every workgroup folds the slice statistics of its
+//   sample  grid (fine slices, NB): every workgroup folds the slice statistics of its
 //           branch, gathers p_i(x_i), q_i(x_i) and tests u*q < p in order (n); then the fp64
-//           resampling path starts: its share of sum exp(z - max) of the two rows at
-//           position n (target row n and draft row n, or target row K alone when n = K).
-//   resid   grid (fine slices, NB): fp64 normalisers from the shares above, then per lane
-//           the mass of its 8 consecutive tokens: max(0, p-q) (and p itself, which is the
-//           distribution of the bonus token and the fallback when the residual has no
-//           mass).  Per-lane and per-slice sums go to the workspace.
-//   pick    grid NB: the slice in which the running sum first exceeds u_sample * total,
-//           then the lane inside it (scan of the stored per-lane sums), then the token
-//           among that lane's 8 (re-evaluated by one lane).
+//           resampling path, one pass over target row n and draft row n (target row K alone
+//           when n = K): the slice's sums of exp(z - max), and of the same over the tokens
+//           whose residual max(0, p-q) is positive beyond doubt; tokens in doubt are listed.
+//   pick    grid NB: the normalisers, each slice's residual mass (its listed tokens settled),
+//           the slice in which the running sum first exceeds u_sample * total, then the lane
+//           inside it (its tokens evaluated again, eight per lane), then the token.
 //   warp    (only with top-k / top-p) one workgroup per target row: the smallest logit the row keeps and the
 //           mass of the kept tokens.  Both filters are predicates on a token's value (keep v iff fewer than k
 //           tokens are larger; keep v iff the mass of the larger kept tokens is below top_p * Z_k), so equal
@@ -27,12 +24,12 @@
 //           With a small k, or where those fall short, a bound taken from the lanes' largest logits leaves a short
 //           list of candidate tokens, which is sorted and walked in descending order; otherwise (and whenever such a list overflows or falls short) two radix selections over an
 //           order-preserving key of the logit: the k-th largest by count, then among those the value at which
-//           the descending cumulative mass reaches top_p of the kept mass.  decide / resid / pick then use
+//           the descending cumulative mass reaches top_p of the kept mass.  sample / pick then use
 //           p(v) = [key(v) >= key_min] * exp((x_v - max)/T) / Z_kept for the target rows.
 //   rowz    (only with top-p alone) grid (fine-slice groups, target rows): the fp64 mass of every target row in
 //           fine slices, which warp folds: top-p's threshold is a share of the whole row's mass; and the tokens
 //           heavy enough to be kept, for warp.
-// The two resampling rows are re-read twice (2 of the 2K+1 rows of a branch; cache hits).
+// The two resampling rows are re-read once (2 of the 2K+1 rows of a branch; cache hits).
 // fp64 there makes the blocked running sum agree with a sequential one to ~1e-16, so the
 // drawn token does not depend on the summation order.
 #include <limits.h>
@@ -77,21 +74,28 @@ template <int ROT>
 __device__ __forceinline__ float row_rotate(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + ROT, 0xf, 0xf, false));
 }
+// over the 16 lanes of a DPP row
+__device__ __forceinline__ float row_max(float v) {
+  v = fmaxf(v, row_rotate<8>(v));
+  v = fmaxf(v, row_rotate<4>(v));
+  v = fmaxf(v, row_rotate<2>(v));
+  return fmaxf(v, row_rotate<1>(v));
+}
+__device__ __forceinline__ float row_sum(float v) {
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  return v + row_rotate<1>(v);
+}
 __device__ __forceinline__ float lane_value(float v, int lane) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
 __device__ __forceinline__ float wave_max_dpp(float v) {
-  v = fmaxf(v, row_rotate<8>(v));
-  v = fmaxf(v, row_rotate<4>(v));
-  v = fmaxf(v, row_rotate<2>(v));
-  v = fmaxf(v, row_rotate<1>(v));
+  v = row_max(v);
   return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
 }
 __device__ __forceinline__ float wave_sum_dpp(float v) {
-  v += row_rotate<8>(v);
-  v += row_rotate<4>(v);
-  v += row_rotate<2>(v);
-  v += row_rotate<1>(v);
+  v = row_sum(v);
   return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
@@ -1167,33 +1171,59 @@ __global__ __launch_bounds__(kWarpThreads) void accept_warp_kernel(const AcceptP
   if (tid == 0) {
     p.warp_key[rw] = key_min;
     p.warp_z[rw] = zw;
-    p.warp_max[rw] = m;
   }
 }
 
 // ---------------------------------------------------------------------------------------------
-// decide: grid (n_fine, NB).  Accepted length of the branch (every workgroup derives it; slice 0 publishes it),
-// then this slice's share of the fp64 normalisers of the resampling rows.
+// sample: grid (n_fine, NB).  Accepted length of the branch (every workgroup derives it; slice 0 publishes it), then
+// what this slice contributes to the normalisers of the resampling rows and to the residual.
+//
+// The residual max(0, a/Zt - b/Zq) of a token (a, b its unnormalised masses in the target and the draft row) needs both
+// normalisers, which all workgroups of the branch contribute to, but its sign nearly never does: Zt/Zq is known from the
+// fp32 statistics to a part in 10^5 or better.  So one pass over the two rows gives, per slice, the sums of a and b, and
+// the sums of a and of b over the tokens whose residual is positive beyond doubt; the few tokens in doubt go to a list.
+// The pick kernel, with the exact normalisers, adds the listed ones that turn out positive -- and checks that the fp32
+// quotient was within the margin allowed for it.  With two passes (normalisers, then residuals) and a launch between
+// them the exponentials were evaluated twice: 16.5 + 17.7 us at 32 branches of 152064.
 // ---------------------------------------------------------------------------------------------
+constexpr int kAmb = 48;   // tokens in doubt a wavefront can list of its 512 tokens of a slice
+constexpr uint32_t kAmbOver = 255;
+struct Doubt {
+  double a, b;
+};
+__device__ __forceinline__ Doubt *doubt_list(const AcceptParams &p, int nb, int c, int wave) {
+  return (Doubt *)p.amb + (((size_t)nb * p.n_fine + c) * (kThreads / 64) + wave) * kAmb;
+}
+
+// What the resampling of a branch needs besides its slices' sums: maxima of its two rows and their fp32 masses.
+struct alignas(16) BranchHead {
+  float mt, mq, zt, zq;
+  // The residual of a token with logits x, y is positive iff (x - y) / T > ln(e^(mt/T) zt / (e^(mq/T) zq)), here in fp32
+  // and log2 units: x - y in doubt if it is within `margin` of that.  One half of the margin is for the fp32 masses (sums
+  // of at most 2^21 terms in blocks, a few 1e-6; the exponents' rounding grows with their size), which pick checks, the
+  // other for the three roundings of the comparison (each 2^-24 of at most 2 max|m| log2(e)/T + 21).
+  __device__ __forceinline__ float margin(const AcceptParams &p) const {
+    return 2e-5f + 1e-6f * (fmaxf(fabsf(mt), fabsf(mq)) * p.inv_temp_log2);
+  }
+};
+
 template <bool BF16>
-__global__ __launch_bounds__(kThreads) void accept_decide_kernel(const AcceptParams p) {
+__global__ __launch_bounds__(kThreads) void accept_sample_kernel(const AcceptParams p) {
   constexpr int kPass = 64;                       // drafted positions examined per pass
-  constexpr int kStage = 2048;                    // slice statistics (max, sum) staged in LDS per pass
+  constexpr int kRow = 16;                        // lanes that fold one row's slice statistics (a DPP row)
   __shared__ float sm[2][kPass], sz[2][kPass];    // [target|draft][position in pass]: folded row statistics
-  __shared__ f32x2 s_stat[kStage];
-  __shared__ float s_top[2];                      // maxima of the resampling rows
+  __shared__ BranchHead s_head;                   // of the resampling rows
   __shared__ float s_bonus;                       // maximum of target row K
-  __shared__ int s_first, s_have_bonus;
-  __shared__ double red[2][kThreads / 64];
+  __shared__ int s_first;
+  __shared__ double red[4][kThreads / 64];
+  __shared__ uint32_t s_amb[kThreads / 64];
   const int c = blockIdx.x, nb = blockIdx.y, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int n_t = p.NB * (p.K + 1);
   const int n_which = p.draft ? 2 : 1;   // point-mass draft: there are no draft rows
-  if (tid == 0) s_first = p.K, s_have_bonus = 0;
-  __syncthreads();
-  int i0 = 0;
+  if (tid == 0) s_first = p.K;
   bool have_top = false;
-  for (; i0 < p.K; i0 += kPass) {   // a later pass cannot lower the first rejection found in an earlier one
+  for (int i0 = 0; i0 < p.K; i0 += kPass) {   // a later pass cannot lower the first rejection found in an earlier one
     const int cnt = min(kPass, p.K - i0);
     // what a position's test needs from global memory besides the row statistics; issued first so that the two
     // dependent round trips (token, then its two logits) overlap the fold below
@@ -1206,42 +1236,30 @@ __global__ __launch_bounds__(kThreads) void accept_decide_kernel(const AcceptPar
       tx = load_logit<BF16>(p.target, ((size_t)nb * (p.K + 1) + i) * p.V + x);
       if (p.draft) dx = load_logit<BF16>(p.draft, ((size_t)nb * p.K + i) * p.V + x);
     }
-    // rows folded in this pass: cnt target rows, cnt draft rows and, in the last pass, target row K (the bonus row)
+    // rows folded in this pass: cnt target rows, cnt draft rows and, in the last pass, target row K (the bonus row);
+    // sixteen lanes per row
     const int bonus = i0 + cnt == p.K ? 1 : 0;
     const int n_rows = n_which * cnt + bonus;
-    auto row_of = [&](int slot) {
-      if (slot == n_which * cnt) return nb * (p.K + 1) + p.K;
+    for (int slot = tid / kRow; slot < n_rows; slot += kThreads / kRow) {
       const int which = slot >= cnt, j = slot - which * cnt;
-      return which ? n_t + nb * p.K + i0 + j : nb * (p.K + 1) + i0 + j;
-    };
-    if (n_rows * p.n_chunks <= kStage) {
-      // all slice statistics in one round of loads, then one lane per row folds its slices from LDS
-      for (int idx = tid; idx < n_rows * p.n_chunks; idx += kThreads) {
-        const int slot = idx / p.n_chunks, ch = idx - slot * p.n_chunks;
-        s_stat[idx] = *(const f32x2 *)(p.stats + ((size_t)row_of(slot) * p.n_chunks + ch) * 2);
-      }
-      __syncthreads();
-      if (tid < n_rows) {
-        const f32x2 *st = s_stat + tid * p.n_chunks;
-        float m = -INFINITY;
-        for (int ch = 0; ch < p.n_chunks; ++ch) m = fmaxf(m, st[ch][0]);
-        float z = 0.f;
-        for (int ch = 0; ch < p.n_chunks; ++ch)
-          z += st[ch][1] * __builtin_amdgcn_exp2f((st[ch][0] - m) * p.inv_temp_log2);
-        if (tid == n_which * cnt) {
+      const bool is_bonus = slot == n_which * cnt;
+      const int rw = is_bonus ? nb * (p.K + 1) + p.K : which ? n_t + nb * p.K + i0 + j : nb * (p.K + 1) + i0 + j;
+      const f32x2 *st = (const f32x2 *)(p.stats + (size_t)rw * p.n_chunks * 2);
+      const int l = tid % kRow;
+      f32x2 own = {-INFINITY, 0.f};
+      if (l < p.n_chunks) own = st[l];
+      float m = own.x;
+      for (int ch = l + kRow; ch < p.n_chunks; ch += kRow) m = fmaxf(m, st[ch].x);
+      m = row_max(m);
+      float z = own.y * __builtin_amdgcn_exp2f((own.x - m) * p.inv_temp_log2);
+      for (int ch = l + kRow; ch < p.n_chunks; ch += kRow)
+        z += st[ch].y * __builtin_amdgcn_exp2f((st[ch].x - m) * p.inv_temp_log2);
+      z = row_sum(z);
+      if (l == 0) {
+        if (is_bonus)
           s_bonus = m;
-          s_have_bonus = 1;
-        } else {
-          const int which = tid >= cnt, j = tid - which * cnt;
+        else
           sm[which][j] = m, sz[which][j] = z;
-        }
-      }
-    } else {
-      for (int slot = wave; slot < n_which * cnt; slot += kThreads / 64) {   // wavefront per row
-        const int which = slot >= cnt, j = slot - which * cnt;
-        float m, z;
-        wave_fold_row(p, row_of(slot), lane, m, z);
-        if (lane == 0) sm[which][j] = m, sz[which][j] = z;
       }
     }
     __syncthreads();
@@ -1261,8 +1279,11 @@ __global__ __launch_bounds__(kThreads) void accept_decide_kernel(const AcceptPar
     }
     __syncthreads();
     if (s_first < p.K) {  // uniform: the first rejection lies in this pass
-      // exact maxima of the resampling rows: target row n and draft row n, both folded in this pass
-      if (!have_top && tid == 0) s_top[0] = sm[0][s_first - i0], s_top[1] = p.draft ? sm[1][s_first - i0] : 0.f;
+      // statistics of the resampling rows: target row n and draft row n, both folded in this pass
+      if (!have_top && tid == 0) {
+        const int j = s_first - i0;
+        s_head = {sm[0][j], p.draft ? sm[1][j] : 0.f, sz[0][j], p.draft ? sz[1][j] : 1.f};
+      }
       have_top = true;
       // the workgroup that reports the ratios goes on through the remaining passes (every position gets its ratio,
       // also those behind the rejection); s_first cannot change any more, atomicMin only lowers it to values < i
@@ -1271,171 +1292,128 @@ __global__ __launch_bounds__(kThreads) void accept_decide_kernel(const AcceptPar
     __syncthreads();  // sm / sz free for the next pass
   }
   const int n = s_first;
-  // everything accepted: the maximum of target row K alone
-  if (n < p.K) {
-    // s_top was set in the pass that found n
-  } else if (s_have_bonus) {
-    if (tid == 0) s_top[0] = s_bonus, s_top[1] = 0.f;
-  } else if (wave == 0) {
-    float m, z;
-    wave_fold_row(p, nb * (p.K + 1) + p.K, lane, m, z);
-    if (lane == 0) s_top[0] = m, s_top[1] = 0.f;
-  }
+  // everything accepted: target row K alone (folded in the last pass), which no draft row is compared with
+  if (n == p.K && tid == 0) s_head = {s_bonus, 0.f, 1.f, 1.f};
   __syncthreads();
-  const float mt = s_top[0], mq = s_top[1];
-  if (c == 0 && tid == 0) {
-    p.accepted_len[nb] = n;
-    p.n_acc[nb] = n;
-    p.rowmax[2 * nb] = mt;
-    p.rowmax[2 * nb + 1] = mq;
+  BranchHead head = s_head;
+  const bool with_draft = n < p.K && p.draft;
+  float x_min = 0.f;
+  if (p.warp_key) {   // the kept mass replaces the row's full normaliser
+    x_min = key_value(p.warp_key[nb * (p.K + 1) + n]);
+    head.zt = (float)p.warp_z[nb * (p.K + 1) + n];
   }
-  const int v0 = c * kFine;
+  // point-mass draft after a rejection: the drafted token has no residual mass
+  const int removed = (n < p.K && !p.draft) ? p.tokens[(size_t)nb * p.K + n] : -1;
   const size_t trow = ((size_t)nb * (p.K + 1) + n) * p.V;
   const size_t drow = ((size_t)nb * p.K + (n < p.K ? n : 0)) * p.V;
-  const double mt_t = (double)mt * p.inv_temp, mq_t = (double)mq * p.inv_temp;
-  double st = 0.0, sq = 0.0;
   const bool vec = ((size_t)p.V * (BF16 ? 2 : 4)) % 16 == 0;
-  const bool with_draft = n < p.K && p.draft;
-  const int vb = v0 + tid * kFinePer;
+  const int vb = c * kFine + tid * kFinePer;
   float tx[kFinePer], dx[kFinePer];
   load_fine<BF16>(p.target, trow, vb, p.V, vec, tx);
   if (with_draft) load_fine<BF16>(p.draft, drow, vb, p.V, vec, dx);
-#pragma unroll
+  if (c == 0 && tid == 0) {
+    p.accepted_len[nb] = n;
+    p.n_acc[nb] = n;
+    ((BranchHead *)p.heads)[nb] = head;
+  }
+  const double mt_t = (double)head.mt * p.inv_temp, mq_t = (double)head.mq * p.inv_temp;
+  // (log2 units; x - y above the threshold: the residual is positive)
+  const float margin = head.margin(p);
+  const float threshold = (float)(((double)head.mt - (double)head.mq) * (double)p.inv_temp_log2 +
+                                  (double)__builtin_amdgcn_logf(head.zt / head.zq));
   // no bounds test per token: load_fine gives -inf past V, whose mass is exactly 0, and the eight exponentials of a
   // lane can then be evaluated side by side instead of one dependent chain after the other
-  for (int e = 0; e < kFinePer; ++e) {
-    st += mass64(tx[e], mt_t, p.inv_temp);
-    if (with_draft) sq += mass64(dx[e], mq_t, p.inv_temp);
+  if (p.warp_key) {   // (comparing values is comparing keys)
+#pragma unroll
+    for (int e = 0; e < kFinePer; ++e) tx[e] = tx[e] >= x_min ? tx[e] : -INFINITY;
   }
-  st = wave_sum(st);
-  sq = wave_sum(sq);
-  if ((tid & 63) == 0) red[0][tid >> 6] = st, red[1][tid >> 6] = sq;
+  double a[kFinePer], b[kFinePer];
+#pragma unroll
+  for (int e = 0; e < kFinePer; ++e) {
+    a[e] = mass64(tx[e], mt_t, p.inv_temp);
+    if (with_draft) b[e] = mass64(dx[e], mq_t, p.inv_temp);
+  }
+  double sa = 0.0, sb = 0.0, pa = 0.0, pb = 0.0;
+  uint32_t doubt = 0;   // bit e: token e is in doubt
+  if (with_draft) {
+#pragma unroll
+    for (int e = 0; e < kFinePer; ++e) {
+      sa += a[e];
+      sb += b[e];
+      // (a token without mass in the target row has no residual and is never in doubt)
+      const float d = __builtin_fmaf(tx[e] - dx[e], p.inv_temp_log2, -threshold);
+      const bool some = tx[e] > -INFINITY, pos = some && d > margin;
+      pa += pos ? a[e] : 0.0;
+      pb += pos ? b[e] : 0.0;
+      if (some && fabsf(d) <= margin) doubt |= 1u << e;
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < kFinePer; ++e) {
+      sa += a[e];
+      pa += vb + e == removed ? 0.0 : a[e];
+    }
+  }
+  uint32_t n_amb = 0;
+  if (with_draft && __ballot(doubt != 0)) {   // the wavefront's tokens in doubt, in token order
+    const int own = __popc(doubt);
+    int incl = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int up = __shfl_up(incl, off);
+      if (lane >= off) incl += up;
+    }
+    n_amb = (uint32_t)__shfl(incl, 63);
+    if (n_amb > kAmb) {
+      n_amb = kAmbOver;
+    } else {
+      Doubt *to = doubt_list(p, nb, c, wave) + (incl - own);
+#pragma unroll
+      for (int e = 0; e < kFinePer; ++e)
+        if (doubt & (1u << e)) *to++ = {a[e], b[e]};
+    }
+  }
+  sa = wave_sum(sa);
+  pa = wave_sum(pa);
+  if (with_draft) sb = wave_sum(sb), pb = wave_sum(pb);
+  if (lane == 0) {
+    red[0][wave] = sa, red[1][wave] = sb, red[2][wave] = pa, red[3][wave] = pb;
+    s_amb[wave] = n_amb;
+  }
   __syncthreads();
-  if (tid == 0) {
-    p.zsum[((size_t)nb * 2 + 0) * p.n_fine + c] = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-    p.zsum[((size_t)nb * 2 + 1) * p.n_fine + c] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+  if (tid < 4) {
+    double *to = tid < 2 ? p.zsum : p.rsum;
+    to[((size_t)nb * 2 + (tid & 1)) * p.n_fine + c] = (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
+    if (tid == 0)
+      p.amb_n[(size_t)nb * p.n_fine + c] = s_amb[0] | s_amb[1] << 8 | s_amb[2] << 16 | s_amb[3] << 24;
   }
 }
 
-// Two rows of n <= kMaxFine doubles each, folded together so that their loads are one round trip.  load: a lane's
-// terms (index tid + kThreads*j) into registers.  sum: the two sums, the same values in every lane of the workgroup
-// and in every workgroup that folds the same terms (fixed association: per lane its terms in index order, a
-// butterfly inside each wavefront, the wavefronts in order); with buf0 / buf1 given the terms are also left there.
+// Two rows of n <= kMaxFine doubles, loaded together: a lane's terms are those at tid + kThreads * j.
 struct FoldPair {
-  double a[kMaxFine / kThreads], b[kMaxFine / kThreads];
+  static constexpr int kTerms = kMaxFine / kThreads;
+  double a[kTerms], b[kTerms];
   __device__ __forceinline__ void load(const double *v0, const double *v1, int n) {
 #pragma unroll
-    for (int j = 0; j < kMaxFine / kThreads; ++j) {
+    for (int j = 0; j < kTerms; ++j) {
       const int c = threadIdx.x + kThreads * j;
       a[j] = c < n ? v0[c] : 0.0;
       b[j] = c < n ? v1[c] : 0.0;
     }
   }
-  __device__ __forceinline__ void sum(int n, double *buf0, double *buf1, double *s0, double *s1) const {
-    __shared__ double fold_red[2][kThreads / 64];
-    double x = 0.0, y = 0.0;
-#pragma unroll
-    for (int j = 0; j < kMaxFine / kThreads; ++j) {
-      const int c = threadIdx.x + kThreads * j;
-      if (c < n) {
-        if (buf0) buf0[c] = a[j];
-        if (buf1) buf1[c] = b[j];
-        x += a[j];
-        y += b[j];
-      }
-    }
-    x = wave_sum(x);
-    y = wave_sum(y);
-    __syncthreads();   // fold_red free again (a previous call's readers are past their reads)
-    if ((threadIdx.x & 63) == 0) fold_red[0][threadIdx.x >> 6] = x, fold_red[1][threadIdx.x >> 6] = y;
-    __syncthreads();
-    *s0 = (fold_red[0][0] + fold_red[0][1]) + (fold_red[0][2] + fold_red[0][3]);
-    *s1 = (fold_red[1][0] + fold_red[1][1]) + (fold_red[1][2] + fold_red[1][3]);
-  }
 };
 
-// residual mass and target mass of the tokens of branch nb at position n, fp64
-template <bool BF16>
-struct ResidCtx {
-  const void *target, *draft;
-  size_t trow, drow;
-  double mt, mq, inv_zt, inv_zq, inv_temp;   // maxima over T, reciprocals of the normalisers, 1/T
-  bool has_draft;
-  int removed;   // point-mass draft after a rejection: the drafted token, which has no residual mass; else -1
-  uint32_t key_min;   // warped target: smallest key the row keeps (0: everything)
-  // tx, dx: the target and draft logit of token v (dx is read only with a draft row)
-  __device__ __forceinline__ void eval(int v, float tx, float dx, double &r, double &pm) const {
-    pm = order_key(tx) >= key_min ? mass64(tx, mt, inv_temp) * inv_zt : 0.0;
-    r = v == removed ? 0.0 : pm;
-    if (has_draft) {
-      const double qm = mass64(dx, mq, inv_temp) * inv_zq;
-      r = pm - qm;
-      if (r < 0.0) r = 0.0;
-    }
-  }
-};
-
-template <bool BF16>
-__device__ __forceinline__ ResidCtx<BF16> make_ctx(const AcceptParams &p, int nb) {
-  ResidCtx<BF16> x;
-  FoldPair zs;   // the slice shares of the two normalisers: requested together with everything else below
-  zs.load(p.zsum + ((size_t)nb * 2 + 0) * p.n_fine, p.zsum + ((size_t)nb * 2 + 1) * p.n_fine, p.n_fine);
-  const int n = p.n_acc[nb];
-  x.target = p.target;
-  x.draft = p.draft;
-  x.trow = ((size_t)nb * (p.K + 1) + n) * p.V;
-  x.has_draft = n < p.K && p.draft;
-  x.removed = (n < p.K && !p.draft) ? p.tokens[(size_t)nb * p.K + n] : -1;
-  x.drow = x.has_draft ? ((size_t)nb * p.K + n) * p.V : 0;
-  x.inv_temp = p.inv_temp;
-  x.mt = (double)p.rowmax[2 * nb] * p.inv_temp;
-  x.mq = (double)p.rowmax[2 * nb + 1] * p.inv_temp;
-  double zt, zq;
-  zs.sum(p.n_fine, nullptr, nullptr, &zt, &zq);
-  if (!x.has_draft) zq = 1.0;
-  x.key_min = 0;
-  if (p.warp_key) {   // the kept mass replaces the row's full normaliser
-    x.key_min = p.warp_key[nb * (p.K + 1) + n];
-    zt = p.warp_z[nb * (p.K + 1) + n];
-  }
-  x.inv_zt = 1.0 / zt;
-  x.inv_zq = 1.0 / zq;
-  return x;
-}
-
-// ---------------------------------------------------------------------------------------------
-// resid: grid (n_fine, NB): per-lane and per-slice fp64 sums of the residual and of p
-// ---------------------------------------------------------------------------------------------
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void accept_resid_kernel(const AcceptParams p) {
-  __shared__ double red[2][kThreads / 64];
-  const int c = blockIdx.x, nb = blockIdx.y, tid = threadIdx.x;
-  const ResidCtx<BF16> ctx = make_ctx<BF16>(p, nb);
-  const int v0 = c * kFine;
-  double sr = 0.0, sp = 0.0;
-  const bool vec = ((size_t)p.V * (BF16 ? 2 : 4)) % 16 == 0;
-  const int vb = v0 + tid * kFinePer;
-  float tx[kFinePer], dx[kFinePer];
-  load_fine<BF16>(ctx.target, ctx.trow, vb, p.V, vec, tx);
-  if (ctx.has_draft) load_fine<BF16>(ctx.draft, ctx.drow, vb, p.V, vec, dx);
-#pragma unroll
-  for (int e = 0; e < kFinePer; ++e) {   // (past V: -inf, no mass of either kind)
-    double r, pm;
-    ctx.eval(vb + e, tx[e], ctx.has_draft ? dx[e] : 0.f, r, pm);
-    sr += r;
-    sp += pm;
-  }
-  double *ls = p.lane_sums + (((size_t)nb * p.n_fine + c) * kThreads + tid) * 2;
-  ls[0] = sr;
-  ls[1] = sp;
-  sr = wave_sum(sr);
-  sp = wave_sum(sp);
-  if ((tid & 63) == 0) red[0][tid >> 6] = sr, red[1][tid >> 6] = sp;
+// Sums of two doubles per lane over the workgroup, the same values in every lane, in a fixed association (a butterfly
+// inside each wavefront, the wavefronts in order).
+__device__ __forceinline__ void block_sum2(double &x, double &y) {
+  __shared__ double fold_red[2][kThreads / 64];
+  x = wave_sum(x);
+  y = wave_sum(y);
+  __syncthreads();   // fold_red free again (a previous call's readers are past their reads)
+  if ((threadIdx.x & 63) == 0) fold_red[0][threadIdx.x >> 6] = x, fold_red[1][threadIdx.x >> 6] = y;
   __syncthreads();
-  if (tid == 0) {
-    p.rsum[((size_t)nb * 2 + 0) * p.n_fine + c] = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-    p.rsum[((size_t)nb * 2 + 1) * p.n_fine + c] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
-  }
+  x = (fold_red[0][0] + fold_red[0][1]) + (fold_red[0][2] + fold_red[0][3]);
+  y = (fold_red[1][0] + fold_red[1][1]) + (fold_red[1][2] + fold_red[1][3]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1444,18 +1422,128 @@ __global__ __launch_bounds__(kThreads) void accept_resid_kernel(const AcceptPara
 template <bool BF16>
 __global__ __launch_bounds__(kThreads) void accept_pick_kernel(const AcceptParams p) {
   __shared__ double buf0[kMaxFine], buf1[kMaxFine];   // slice sums of the residual and of p
+  __shared__ uint32_t s_amb[kMaxFine];                // tokens in doubt per slice, a byte per wavefront of its workgroup
   __shared__ double s_before;
   __shared__ double wave_tot[kThreads / 64];
   __shared__ int s_slice, s_lane, s_last_lane;
+  constexpr int kTerms = FoldPair::kTerms;
   const int nb = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  FoldPair rs;   // requested before the context's own loads, so that both arrive in one round trip
-  rs.load(p.rsum + ((size_t)nb * 2 + 0) * p.n_fine, p.rsum + ((size_t)nb * 2 + 1) * p.n_fine, p.n_fine);
+  // everything that does not depend on the accepted length is requested in one round trip
+  FoldPair tot, pos;
+  tot.load(p.zsum + ((size_t)nb * 2 + 0) * p.n_fine, p.zsum + ((size_t)nb * 2 + 1) * p.n_fine, p.n_fine);
+  pos.load(p.rsum + ((size_t)nb * 2 + 0) * p.n_fine, p.rsum + ((size_t)nb * 2 + 1) * p.n_fine, p.n_fine);
+  uint32_t amb[kTerms];
+#pragma unroll
+  for (int j = 0; j < kTerms; ++j) {
+    const int c = tid + kThreads * j;
+    amb[j] = c < p.n_fine ? p.amb_n[(size_t)nb * p.n_fine + c] : 0u;
+  }
+  const BranchHead head = ((const BranchHead *)p.heads)[nb];
+  const int n = p.n_acc[nb];
   const double u = (double)p.u_sample[nb];
-  const ResidCtx<BF16> ctx = make_ctx<BF16>(p, nb);
+  const bool with_draft = n < p.K && p.draft;
+  const int removed = (n < p.K && !p.draft) ? p.tokens[(size_t)nb * p.K + n] : -1;
+  const size_t trow = ((size_t)nb * (p.K + 1) + n) * p.V;
+  const size_t drow = ((size_t)nb * p.K + (n < p.K ? n : 0)) * p.V;
+  uint32_t key_min = 0;
+  double zw = 0.0;
+  if (p.warp_key) {
+    key_min = p.warp_key[nb * (p.K + 1) + n];
+    zw = p.warp_z[nb * (p.K + 1) + n];
+  }
+  double zt = 0.0, zq = 0.0;
+#pragma unroll
+  for (int j = 0; j < kTerms; ++j) zt += tot.a[j], zq += tot.b[j];
+  block_sum2(zt, zq);
+  if (p.warp_key) zt = zw;   // the kept mass replaces the row's full normaliser
+  if (!with_draft) zq = 1.0;
+  const double inv_zt = 1.0 / zt, inv_zq = 1.0 / zq;
+  const double mt_t = (double)head.mt * p.inv_temp, mq_t = (double)head.mq * p.inv_temp;
+  // the residual and p of the eight tokens of slice c that this lane owns: all loads first, then the masses side by side
+  // (tokens past V read as -inf and have no mass)
+  auto eval = [&](int c, double (&r)[kFinePer], double (&pm)[kFinePer]) {
+    const int v0 = c * kFine + tid * kFinePer;
+    const bool vec = ((size_t)p.V * (BF16 ? 2 : 4)) % 16 == 0;
+    float tx[kFinePer], dx[kFinePer];
+    load_fine<BF16>(p.target, trow, v0, p.V, vec, tx);
+    if (with_draft) load_fine<BF16>(p.draft, drow, v0, p.V, vec, dx);
+#pragma unroll
+    for (int e = 0; e < kFinePer; ++e) {
+      pm[e] = order_key(tx[e]) >= key_min ? mass64(tx[e], mt_t, p.inv_temp) * inv_zt : 0.0;
+      r[e] = v0 + e == removed ? 0.0 : pm[e];
+      if (with_draft) {
+        r[e] = pm[e] - mass64(dx[e], mq_t, p.inv_temp) * inv_zq;
+        if (r[e] < 0.0) r[e] = 0.0;
+      }
+    }
+  };
+  // the tokens counted as positive or negative by the fp32 quotient are so if the exact one lies within half the margin
+  // of it; else every slice is evaluated again
+  const bool trusted = !with_draft || fabs((double)head.zt / (double)head.zq * zq * inv_zt - 1.0) <=
+                                          0.5 * 0.69 * (double)head.margin(p);   // (log2 units)
+  auto overflowed = [](uint32_t w) {
+    return (w & 255u) == kAmbOver || (w >> 8 & 255u) == kAmbOver || (w >> 16 & 255u) == kAmbOver || w >> 24 == kAmbOver;
+  };
+  bool any = false, over = false;
+#pragma unroll
+  for (int j = 0; j < kTerms; ++j) {
+    const int c = tid + kThreads * j;
+    if (c < p.n_fine) {
+      buf0[c] = pos.a[j] * inv_zt - pos.b[j] * inv_zq;
+      buf1[c] = tot.a[j] * inv_zt;
+      if (!trusted) amb[j] = kAmbOver;
+      s_amb[c] = amb[j];
+      any = any || amb[j];
+      over = over || overflowed(amb[j]);
+    }
+  }
+  if (__syncthreads_or(any)) {
+    const bool some_over = __syncthreads_or(over);
+    // sixteen lanes per slice, the loads of its four lists in one round trip
+    for (int c = tid / 16; c < p.n_fine; c += kThreads / 16) {
+      const uint32_t w = s_amb[c];
+      if (w == 0 || overflowed(w)) continue;
+      Doubt t[kThreads / 64][kAmb / 16];
+#pragma unroll
+      for (int k = 0; k < kThreads / 64; ++k)
+#pragma unroll
+        for (int i = 0; i < kAmb / 16; ++i) {
+          t[k][i] = {0.0, 0.0};
+          if (i * 16 + tid % 16 < (int)(w >> (8 * k) & 255u)) t[k][i] = doubt_list(p, nb, c, k)[i * 16 + tid % 16];
+        }
+      double add = 0.0;
+#pragma unroll
+      for (int k = 0; k < kThreads / 64; ++k)
+#pragma unroll
+        for (int i = 0; i < kAmb / 16; ++i) {
+          const double r = t[k][i].a * inv_zt - t[k][i].b * inv_zq;
+          add += r > 0.0 ? r : 0.0;
+        }
+      add = row_sum(add);
+      if (tid % 16 == 0) buf0[c] += add;
+    }
+    __syncthreads();
+    // lists that did not hold them: the whole slice again, by the workgroup
+    for (int c = 0; some_over && c < p.n_fine; ++c) {
+      if (!overflowed(s_amb[c])) continue;   // (uniform)
+      double r[kFinePer], pm[kFinePer], sr = 0.0, none = 0.0;
+      eval(c, r, pm);
+#pragma unroll
+      for (int e = 0; e < kFinePer; ++e) sr += r[e];
+      block_sum2(sr, none);
+      if (tid == 0) buf0[c] = sr;
+    }
+    __syncthreads();
+  }
   // total residual mass; without mass (rounding only) the draw is from p_n itself
-  double S, Sp;
-  rs.sum(p.n_fine, buf0, buf1, &S, &Sp);
+  double S = 0.0, Sp = 0.0;
+#pragma unroll
+  for (int j = 0; j < kTerms; ++j) {
+    const int c = tid + kThreads * j;
+    if (c < p.n_fine) S += buf0[c], Sp += buf1[c];
+  }
+  block_sum2(S, Sp);
   int mode = 0;
   const double *buf = buf0;
   if (!(S > 0.0)) {   // uniform
@@ -1504,8 +1592,17 @@ __global__ __launch_bounds__(kThreads) void accept_pick_kernel(const AcceptParam
   }
   __syncthreads();
   const int cs = s_slice;
-  // lane of that slice whose 8 tokens contain the crossing: inclusive scan of the stored per-lane sums
-  const double mine = p.lane_sums[(((size_t)nb * p.n_fine + cs) * kThreads + tid) * 2 + mode];
+  // lane of that slice whose 8 tokens contain the crossing: inclusive scan of the lanes' sums
+  double mass[kFinePer], mine = 0.0;
+  {
+    double r[kFinePer], pm[kFinePer];
+    eval(cs, r, pm);
+#pragma unroll
+    for (int e = 0; e < kFinePer; ++e) {
+      mass[e] = mode ? pm[e] : r[e];
+      mine += mass[e];
+    }
+  }
   double incl = mine;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -1524,20 +1621,7 @@ __global__ __launch_bounds__(kThreads) void accept_pick_kernel(const AcceptParam
   __syncthreads();
   const int pick_lane = s_lane != INT_MAX ? s_lane : s_last_lane;
   if (tid == pick_lane) {
-    // the lane's eight tokens once more: all loads first, then the eight masses side by side (tokens past V read as
-    // -inf and have no mass), then the walk
     const int v0 = cs * kFine + tid * kFinePer;
-    const bool vec = ((size_t)p.V * (BF16 ? 2 : 4)) % 16 == 0;
-    float tx[kFinePer], dx[kFinePer];
-    load_fine<BF16>(ctx.target, ctx.trow, v0, p.V, vec, tx);
-    if (ctx.has_draft) load_fine<BF16>(ctx.draft, ctx.drow, v0, p.V, vec, dx);
-    double mass[kFinePer];
-#pragma unroll
-    for (int e = 0; e < kFinePer; ++e) {
-      double r, pm;
-      ctx.eval(v0 + e, tx[e], ctx.has_draft ? dx[e] : 0.f, r, pm);
-      mass[e] = mode ? pm : r;
-    }
     double run = lo;
     int tok = -1, last = -1;
 #pragma unroll
@@ -1553,6 +1637,14 @@ __global__ __launch_bounds__(kThreads) void accept_pick_kernel(const AcceptParam
 }
 
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// The part of the workspace that holds lists: 4 KiB per fine slice and branch.  top-p alone: the candidate segments, all
+// of it, until the warp kernel has read them; then the lists of tokens in doubt (3 KiB per slice), their counts and the
+// branches' heads.
+inline size_t lists_bytes(int NB, int n_fine) { return align_up((size_t)NB * n_fine * kThreads * 2 * sizeof(double)); }
+static_assert(kThreads / 64 * kAmb * sizeof(Doubt) + sizeof(uint32_t) + sizeof(BranchHead) <=
+                  kThreads * 2 * sizeof(double),
+              "a slice's share of the lists, its count and (one slice per branch) the branch's head");
 
 template <bool BF16>
 hipError_t launch_typed(const AcceptParams &p, hipStream_t stream) {
@@ -1580,14 +1672,8 @@ hipError_t launch_typed(const AcceptParams &p, hipStream_t stream) {
     if (e != hipSuccess) return e;
   }
   {
-    ProfileScope scope(SLOT_ACCEPT_DECIDE, stream);
-    hipLaunchKernelGGL(accept_decide_kernel<BF16>, dim3(p.n_fine, p.NB), dim3(kThreads), 0, stream, p);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  {
-    ProfileScope scope(SLOT_ACCEPT_RESID, stream);
-    hipLaunchKernelGGL(accept_resid_kernel<BF16>, dim3(p.n_fine, p.NB), dim3(kThreads), 0, stream, p);
+    ProfileScope scope(SLOT_ACCEPT_SAMPLE, stream);
+    hipLaunchKernelGGL(accept_sample_kernel<BF16>, dim3(p.n_fine, p.NB), dim3(kThreads), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -1611,11 +1697,11 @@ size_t accept_workspace_bytes(int NB, int K, int V, bool bf16, int *n_chunks_out
   b += align_up((size_t)NB * sizeof(int32_t));                             // n_acc
   b += align_up((size_t)NB * 2 * n_fine * sizeof(double));                 // zsum
   b += align_up((size_t)NB * 2 * n_fine * sizeof(double));                 // rsum
-  b += align_up((size_t)NB * 2 * sizeof(float));                           // rowmax
-  b += align_up((size_t)NB * n_fine * kThreads * 2 * sizeof(double));      // lane_sums
+  b += align_up((size_t)NB * 2 * sizeof(float));                           // (not used any more)
+  b += lists_bytes(NB, n_fine);                                            // lists (tokens in doubt / candidates)
   b += align_up((size_t)NB * (K + 1) * sizeof(uint32_t));                  // warp_key
   b += align_up((size_t)NB * (K + 1) * sizeof(double));                    // warp_z
-  b += align_up((size_t)NB * (K + 1) * sizeof(float));                     // warp_max
+  b += align_up((size_t)NB * (K + 1) * sizeof(float));                     // (not used any more)
   b += align_up((size_t)NB * (K + 1) * n_fine * sizeof(double));           // warp_zs
   return b;
 }
@@ -1630,24 +1716,24 @@ void accept_carve_workspace(AcceptParams &p, void *ws) {
   at += align_up((size_t)p.NB * 2 * p.n_fine * sizeof(double));
   p.rsum = (double *)at;
   at += align_up((size_t)p.NB * 2 * p.n_fine * sizeof(double));
-  p.rowmax = (float *)at;
   at += align_up((size_t)p.NB * 2 * sizeof(float));
-  p.lane_sums = (double *)at;
-  // the candidate segments of a call with top-p alone share the space: equal parts, 16-byte aligned, none if too small
   {
+    const size_t slices = (size_t)p.NB * p.n_fine;
+    p.amb = at;
+    p.heads = at + slices * (kThreads / 64) * kAmb * sizeof(Doubt);
+    p.amb_n = (uint32_t *)(p.heads + (size_t)p.NB * sizeof(BranchHead));
+    // the candidate segments of a call with top-p alone share the space: equal parts, 16-byte aligned, none if too small
     const size_t groups = (size_t)(p.K + 1) * ((p.n_fine + kRowzGroup - 1) / kRowzGroup);
     const size_t bytes = ((size_t)p.n_fine * kThreads * 2 * sizeof(double) / groups) & ~(size_t)15;
     p.cand = at;
     p.cand_bytes = bytes >= 64 ? (int)bytes : 0;
   }
-  at += align_up((size_t)p.NB * p.n_fine * kThreads * 2 * sizeof(double));
+  at += lists_bytes(p.NB, p.n_fine);
   const bool warp = (p.top_k > 0 && p.top_k < p.V) || p.top_p < 1.0f;
   p.warp_key = warp ? (uint32_t *)at : nullptr;
   at += align_up((size_t)p.NB * (p.K + 1) * sizeof(uint32_t));
   p.warp_z = warp ? (double *)at : nullptr;
-  at += align_up((size_t)p.NB * (p.K + 1) * sizeof(double));
-  p.warp_max = warp ? (float *)at : nullptr;
-  at += align_up((size_t)p.NB * (p.K + 1) * sizeof(float));
+  at += align_up((size_t)p.NB * (p.K + 1) * sizeof(double)) + align_up((size_t)p.NB * (p.K + 1) * sizeof(float));
   p.warp_zs = warp ? (double *)at : nullptr;
 }
 

@@ -10,7 +10,7 @@ namespace la {
 namespace {
 
 const char *kSlotNames[SLOT_COUNT] = {"attn_mfma",     "attn_merge",   "attn_f32",   "accept_stats", "accept_warp",
-                                      "accept_decide", "accept_resid", "accept_pick", "kv_commit",
+                                      "accept_sample", "accept_pick", "kv_commit",
                                       "calib_mfma",    "calib_read"};
 struct ProfileRecord {
   int slot;

@@ -99,8 +99,7 @@ enum KernelSlot {
   SLOT_ATTN_F32,
   SLOT_ACCEPT_STATS,
   SLOT_ACCEPT_WARP,
-  SLOT_ACCEPT_DECIDE,
-  SLOT_ACCEPT_RESID,
+  SLOT_ACCEPT_SAMPLE,
   SLOT_ACCEPT_PICK,
   SLOT_KV_COMMIT,
   SLOT_CALIB_MFMA,
@@ -145,18 +144,18 @@ struct AcceptParams {
   // workspace
   float *stats;                // [rows = NB*(2K+1), n_chunks, 2]  (exact max, sum 2^((x-max)*log2e/T))
   int32_t *n_acc;              // [NB]
-  double *zsum;                // [NB, 2, n_fine]  fp64 sum exp(z - max) of the resampling rows
-  double *rsum;                // [NB, 2, n_fine]  fp64 slice sums of the residual and of p
-  float *rowmax;               // [NB, 2] exact row maxima (raw logits) of the resampling rows
-  double *lane_sums;           // [NB, n_fine, 256, 2] per-lane sums of the residual and of p
-  uint8_t *cand;               // top-p alone: candidate segments of every target row, in the space of lane_sums
+  double *zsum;                // [NB, 2, n_fine]  fp64 slice sums of exp(z - max) of the target and the draft resampling row
+  double *rsum;                // [NB, 2, n_fine]  the same over the tokens whose residual is positive beyond doubt
+  uint8_t *amb;                // [NB, n_fine, 4, 48] masses of the tokens in doubt
+  uint32_t *amb_n;             // [NB, n_fine] their number, a byte per wavefront of the slice's workgroup
+  uint8_t *heads;              // [NB] row maxima and fp32 masses of the resampling rows
+  uint8_t *cand;               // top-p alone: candidate segments of every target row, in the space of the lists above
   int cand_bytes;              // size of one segment (0: none)
   // top-k / top-p warping of the target rows (off: top_k == 0 and top_p >= 1)
   int top_k;
   float top_p;
   uint32_t *warp_key;          // [NB*(K+1)] order-preserving key of the smallest logit a row keeps
   double *warp_z;              // [NB*(K+1)] sum exp((x - max)/T) over the kept tokens
-  float *warp_max;             // [NB*(K+1)] row maximum (raw logits)
   double *warp_zs;             // [NB*(K+1), n_fine] fp64 slice sums of exp((x - max)/T) of every target row (top-p alone)
 };
 
