@@ -34,13 +34,17 @@
 // drawn token does not depend on the summation order.
 #include <limits.h>
 
+#include <type_traits>
+
 #include "la_internal.hpp"
 
 namespace la {
 namespace {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) uint16_t u16x2;
 
 constexpr int kThreads = 256;
 constexpr int kFinePer = 8;                 // tokens per lane in the fp64 kernels (load_fine reads eight)
@@ -135,6 +139,225 @@ __device__ __forceinline__ const uint8_t *stacked_row(const AcceptParams &p, int
   return (const uint8_t *)p.draft + (size_t)(rw - n_t) * p.V * esz;
 }
 
+// exp(y) in fp64 for the arguments met here (y = (x - max)/T <= 0 up to rounding; the result only has to be the same
+// function of y everywhere it is used, and within an ulp or two of the true value).  y = k ln2 + r with |r| <= ln2/2
+// by a two-term reduction (k * ln2_hi is exact for |k| < 2^11), e^r by its Taylor polynomial of degree 13
+// (remainder < 5e-18), then the scaling by 2^k, which also takes results below the normal range to denormals / zero.
+// About 20 fp64 instructions, against several times that for the general library routine.
+// a * b + c with the constant c read from scalar registers (left to itself the compiler copies every constant of the
+// polynomial into a vector register pair first, two moves per step, to use the two-address form of the instruction)
+__device__ __forceinline__ double fma_const(double a, double b, double c) {
+  double d;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+  return d;
+}
+
+__device__ __forceinline__ double exp64(double y) {
+  y = fmax(y, -750.0);   // (y <= 0 up to rounding: x never exceeds the row maximum)
+  // k = nearest integer to y * log2(e): adding 1.5 * 2^52 leaves it in the low bits of the sum (as a double by taking
+  // the constant off again, as an integer in the low word of the bit pattern); the rounding and conversion
+  // instructions this replaces run at a quarter of the rate of an addition
+  const double shifted = __builtin_fma(y, 1.4426950408889634074, 6755399441055744.0);
+  const double k = shifted - 6755399441055744.0;
+  const int ki = (int)(uint32_t)__builtin_bit_cast(uint64_t, shifted);
+  double r = __builtin_fma(-k, 6.93147180369123816490e-01, y);
+  r = __builtin_fma(-k, 1.90821492927058770002e-10, r);
+  double q = fma_const(r, 1.0 / 6227020800.0, 1.0 / 479001600.0);
+  q = fma_const(q, r, 1.0 / 39916800.0);
+  q = fma_const(q, r, 1.0 / 3628800.0);
+  q = fma_const(q, r, 1.0 / 362880.0);
+  q = fma_const(q, r, 1.0 / 40320.0);
+  q = fma_const(q, r, 1.0 / 5040.0);
+  q = fma_const(q, r, 1.0 / 720.0);
+  q = fma_const(q, r, 1.0 / 120.0);
+  q = fma_const(q, r, 1.0 / 24.0);
+  q = fma_const(q, r, 1.0 / 6.0);
+  q = __builtin_fma(q, r, 0.5);
+  q = __builtin_fma(q, r, 1.0);
+  q = __builtin_fma(q, r, 1.0);
+  return __builtin_ldexp(q, ki);
+}
+
+// fp64 probability mass (unnormalised) of one logit: exp(x/T - max/T)
+__device__ __forceinline__ double mass64(float x, double mx_over_t, double inv_temp) {
+  return exp64((double)x * inv_temp - mx_over_t);
+}
+
+// ---------------------------------------------------------------------------------------------
+// exp(x / T) of the bf16 logits 2^-12 <= |x| < 64, both signs, in the order of their bit patterns: a table in LDS that
+// the kernels walking whole rows look their masses up in.  An exponential costs about 110 cycles of a SIMD, a lookup about
+// 20 and an LDS read; with 4608 entries nearly every token of a row is in it (of normal logits of deviation 3 one
+// token in 15000 is not; it takes the exponential).  The stats kernel's first workgroups write it to the workspace, to
+// the last bit or two: the product x / T is carried in two terms.  Measured at V = 152064: sample 21.2 -> 14.6 us (32
+// branches, draft rows), rowz 15.4 -> 12.5 us (54 rows; in slices of eight per workgroup 14.4, of four 13.4).
+//
+// The masses of such a row are in units of e^0, not of e^(max/T): nothing but their quotients leaves the call, and with
+// |max| / T up to 300 no sum overflows and a token that vanishes weighs e^-445 of the row at most.  A row beyond that keeps
+// the maximum as its unit and the exponential per token (mass_unit).  T below 0.11, where table entries leave the range
+// of a double, fp32 logits, and calls of a few slices, whose workspace has no room for it, have no table.
+// ---------------------------------------------------------------------------------------------
+constexpr int kTabLo = 115 * 128;               // bit pattern of 2^-12
+constexpr int kTabHalf = 18 * 128;              // up to 2^6
+constexpr int kTab = 2 * kTabHalf + 2;          // a zero behind the positive values, the negative ones, a zero behind those
+constexpr float kTabMaxExponent = 300.f;
+
+__device__ __forceinline__ double table_entry(int i, double inv_temp) {
+  const int neg = i > kTabHalf, j = i - neg * (kTabHalf + 1);
+  if (j == kTabHalf) return 0.0;
+  const double x = (double)bf16_lo((uint32_t)(j + kTabLo + neg * 0x8000));
+  const double y = x * inv_temp, rest = __builtin_fma(x, inv_temp, -y);
+  const double e = exp64(y);
+  return __builtin_fma(e, rest, e);
+}
+
+// max / T where that is the unit of a row's masses, else 0
+__device__ __forceinline__ double mass_unit(const AcceptParams &p, float row_max) {
+  const double m_t = (double)row_max * p.inv_temp;
+  return p.exp_tab && fabs(m_t) <= (double)kTabMaxExponent ? 0.0 : m_t;
+}
+// what a mass in the row's unit is in units of e^(max/T)
+__device__ __forceinline__ double unit_over_max(const AcceptParams &p, float row_max) {
+  return exp64(mass_unit(p, row_max) - (double)row_max * p.inv_temp);
+}
+
+// The table from the workspace to LDS, by n_threads threads, with all loads in flight at once; barrier to follow.
+template <int n_threads>
+struct TableCopy {
+  static constexpr int kLoads = (kTab / 2 + n_threads - 1) / n_threads;
+  u32x4 w[kLoads];
+  __device__ __forceinline__ void load(const double *from) {
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      const int i = threadIdx.x + j * n_threads;
+      w[j] = ((const u32x4 *)from)[i < kTab / 2 ? i : 0];
+    }
+  }
+  __device__ __forceinline__ void store(double *to) const {
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      const int i = threadIdx.x + j * n_threads;
+      if (i < kTab / 2) ((u32x4 *)to)[i] = w[j];
+    }
+  }
+};
+
+// The kFinePer consecutive logits of a row that a lane of the walking kernels owns, from token v (a multiple of kFinePer)
+// on, as loaded (bf16: two to a word); tokens at or past V read as -inf.  vec: every row starts on a 16-byte boundary.
+template <bool BF16>
+struct FineWords {
+  u32x4 w[BF16 ? 1 : 2];
+  __device__ __forceinline__ void load(const void *base, size_t row_off, int v, int V, bool vec) {
+    const uint8_t *at = (const uint8_t *)base + (row_off + v) * (BF16 ? 2 : 4);
+    if (vec && v + 8 <= V) {
+      w[0] = *(const u32x4 *)at;
+      if constexpr (!BF16) w[1] = *(const u32x4 *)(at + 16);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (BF16) {
+          const uint32_t lo = v + 2 * e < V ? ((const uint16_t *)at)[2 * e] : 0xFF80u;   // -inf
+          const uint32_t hi = v + 2 * e + 1 < V ? ((const uint16_t *)at)[2 * e + 1] : 0xFF80u;
+          w[0][e] = lo | hi << 16;
+        } else {
+          w[0][e] = v + e < V ? ((const uint32_t *)at)[e] : 0xFF800000u;
+          w[1][e] = v + 4 + e < V ? ((const uint32_t *)at)[4 + e] : 0xFF800000u;
+        }
+      }
+    }
+  }
+  // values below x_min become -inf
+  __device__ __forceinline__ void keep(float x_min) {
+    float x[8];
+    get(x);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if constexpr (BF16) {
+        const uint32_t word = w[0][k];
+        w[0][k] = (x[2 * k] >= x_min ? word & 0xFFFFu : 0xFF80u) | (x[2 * k + 1] >= x_min ? word & 0xFFFF0000u : 0xFF800000u);
+      } else {
+        const uint32_t a = w[0][k], b = w[1][k];
+        w[0][k] = x[k] >= x_min ? a : 0xFF800000u;
+        w[1][k] = x[4 + k] >= x_min ? b : 0xFF800000u;
+      }
+    }
+  }
+  __device__ __forceinline__ void get(float (&x)[8]) const {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if constexpr (BF16) {
+        const uint32_t word = w[0][k];
+        x[2 * k] = bf16_lo(word);
+        x[2 * k + 1] = bf16_hi(word);
+      } else {
+        const uint32_t a = w[0][k], b = w[1][k];
+        x[k] = as_f32(a);
+        x[4 + k] = as_f32(b);
+      }
+    }
+  }
+};
+
+// The masses of eight logits in their row's unit (o_t = mass_unit).  TAB: by the table, and by the exponential for
+// what is not in it.
+template <bool BF16, bool TAB>
+__device__ __forceinline__ void masses(const FineWords<BF16> &words, const double *tab, double o_t, const AcceptParams &p,
+                                       double (&m)[8]) {
+  if constexpr (!TAB) {
+    float x[8];
+    words.get(x);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) m[e] = mass64(x[e], o_t, p.inv_temp);
+  } else {
+    // two tokens per instruction: their places in the table, kTabHalf (a zero) for what is not in it
+    u16x2 most = {0, 0};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t word = words.w[0][k];
+      const u16x2 u = __builtin_bit_cast(u16x2, word);
+      u16x2 i = (u & (uint16_t)0x7FFF) - (uint16_t)kTabLo;
+      most = __builtin_elementwise_max(most, i);
+      i = __builtin_elementwise_min(i, (u16x2){kTabHalf, kTabHalf}) + (u >> 15) * (uint16_t)(kTabHalf + 1);
+      m[2 * k] = tab[i.x];
+      m[2 * k + 1] = tab[i.y];
+    }
+    if (__ballot(most.x >= kTabHalf || most.y >= kTabHalf) || o_t != 0.0) {
+      float x[8];
+      words.get(x);
+      const float zero_below = (float)((o_t - 746.0) / p.inv_temp);   // (-inf among them)
+      uint32_t rest = 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t i = ((__builtin_bit_cast(uint32_t, x[e]) >> 16) & 0x7FFFu) - (uint32_t)kTabLo;
+        if (i >= (uint32_t)kTabHalf || o_t != 0.0) {
+          m[e] = 0.0;
+          if (x[e] > zero_below) rest |= 1u << e;
+        }
+      }
+      while (__ballot(rest != 0)) {   // one token per lane and round
+        const int bit = __ffs((int)rest) - 1;
+        float v = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v = e == bit ? x[e] : v;
+        const double mv = mass64(v, o_t, p.inv_temp);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m[e] = e == bit ? mv : m[e];
+        rest &= rest - 1;
+      }
+    }
+  }
+}
+
+// The mass of one logit by the same rule and to the same bits, the table read from the workspace: what the pick kernel
+// evaluates again has to agree with the sums it was chosen by.
+template <bool BF16>
+__device__ __forceinline__ double mass_again(float x, double o_t, const AcceptParams &p) {
+  if constexpr (BF16) {
+    const uint32_t u = __builtin_bit_cast(uint32_t, x) >> 16, i = (u & 0x7FFFu) - (uint32_t)kTabLo;
+    if (p.exp_tab && o_t == 0.0 && i < (uint32_t)kTabHalf) return p.exp_tab[i + (u >> 15) * (kTabHalf + 1)];
+  }
+  return mass64(x, o_t, p.inv_temp);
+}
+
 // ---------------------------------------------------------------------------------------------
 // stats: grid (n_chunks, rows); a slice is 256 lanes x 8 16-byte loads (16384 bf16 / 8192 fp32 logits)
 // ---------------------------------------------------------------------------------------------
@@ -207,6 +430,9 @@ __global__ __launch_bounds__(kThreads, 6) void accept_stats_kernel(const AcceptP
     f32x2 out = {m, (red[1][0] + red[1][1]) + (red[1][2] + red[1][3])};
     *(f32x2 *)(p.stats + ((size_t)rw * p.n_chunks + c) * 2) = out;
   }
+  if (BF16 && p.exp_tab)
+    for (int i = (rw * p.n_chunks + c) * kThreads; i < kTab; i += gridDim.x * gridDim.y * kThreads)
+      if (i + tid < kTab) p.exp_tab[i + tid] = table_entry(i + tid, p.inv_temp);
 }
 
 // Fold the slice statistics of one row into its maximum and sum 2^((x-max)*c); called by a whole wavefront, lanes
@@ -229,77 +455,36 @@ __device__ __forceinline__ uint32_t order_key(float x) {
   return b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);
 }
 
-// exp(y) in fp64 for the arguments met here (y = (x - max)/T <= 0 up to rounding; the result only has to be the same
-// function of y everywhere it is used, and within an ulp or two of the true value).  y = k ln2 + r with |r| <= ln2/2
-// by a two-term reduction (k * ln2_hi is exact for |k| < 2^11), e^r by its Taylor polynomial of degree 13
-// (remainder < 5e-18), then the scaling by 2^k, which also takes results below the normal range to denormals / zero.
-// About 20 fp64 instructions, against several times that for the general library routine.
-// a * b + c with the constant c read from scalar registers (left to itself the compiler copies every constant of the
-// polynomial into a vector register pair first, two moves per step, to use the two-address form of the instruction)
-__device__ __forceinline__ double fma_const(double a, double b, double c) {
-  double d;
-  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
-  return d;
-}
-
-__device__ __forceinline__ double exp64(double y) {
-  y = fmax(y, -750.0);   // (y <= 0 up to rounding: x never exceeds the row maximum)
-  // k = nearest integer to y * log2(e): adding 1.5 * 2^52 leaves it in the low bits of the sum (as a double by taking
-  // the constant off again, as an integer in the low word of the bit pattern); the rounding and conversion
-  // instructions this replaces run at a quarter of the rate of an addition
-  const double shifted = __builtin_fma(y, 1.4426950408889634074, 6755399441055744.0);
-  const double k = shifted - 6755399441055744.0;
-  const int ki = (int)(uint32_t)__builtin_bit_cast(uint64_t, shifted);
-  double r = __builtin_fma(-k, 6.93147180369123816490e-01, y);
-  r = __builtin_fma(-k, 1.90821492927058770002e-10, r);
-  double q = fma_const(r, 1.0 / 6227020800.0, 1.0 / 479001600.0);
-  q = fma_const(q, r, 1.0 / 39916800.0);
-  q = fma_const(q, r, 1.0 / 3628800.0);
-  q = fma_const(q, r, 1.0 / 362880.0);
-  q = fma_const(q, r, 1.0 / 40320.0);
-  q = fma_const(q, r, 1.0 / 5040.0);
-  q = fma_const(q, r, 1.0 / 720.0);
-  q = fma_const(q, r, 1.0 / 120.0);
-  q = fma_const(q, r, 1.0 / 24.0);
-  q = fma_const(q, r, 1.0 / 6.0);
-  q = __builtin_fma(q, r, 0.5);
-  q = __builtin_fma(q, r, 1.0);
-  q = __builtin_fma(q, r, 1.0);
-  return __builtin_ldexp(q, ki);
-}
-
-// fp64 probability mass (unnormalised) of one logit: exp(x/T - max/T)
-__device__ __forceinline__ double mass64(float x, double mx_over_t, double inv_temp) {
-  return exp64((double)x * inv_temp - mx_over_t);
-}
-
-// The kFinePer consecutive logits of a row that a lane of the fp64 kernels owns, from token v (a multiple of
-// kFinePer) on; tokens at or past V read as -inf.  vec: every row starts on a 16-byte boundary, so the eight values
-// are one (bf16) or two (fp32) 16-byte loads.
-template <bool BF16>
-__device__ __forceinline__ void load_fine(const void *base, size_t row_off, int v, int V, bool vec, float (&x)[8]) {
-  if (vec && v + 8 <= V) {
-    if constexpr (BF16) {
-      const u32x4 w = *(const u32x4 *)((const uint16_t *)base + row_off + v);
+// The N (4 or 8) consecutive logits of a row that a lane owns, from token v (a multiple of N) on; tokens at or past V read as
+// -inf.  vec: every row starts on a 16-byte boundary.
+template <bool BF16, int N>
+__device__ __forceinline__ void load_own(const void *base, size_t row_off, int v, int V, bool vec, float (&x)[N]) {
+  if constexpr (N == 8) {
+    FineWords<BF16> w;
+    w.load(base, row_off, v, V, vec);
+    w.get(x);
+  } else {
+    static_assert(N == 4, "tokens per lane of the pick kernel");
+    if (vec && v + 4 <= V) {
+      if constexpr (BF16) {
+        const u32x2 w = *(const u32x2 *)((const uint16_t *)base + row_off + v);
+        const uint32_t lo = w.x, hi = w.y;
+        x[0] = bf16_lo(lo);
+        x[1] = bf16_hi(lo);
+        x[2] = bf16_lo(hi);
+        x[3] = bf16_hi(hi);
+      } else {
+        const u32x4 w = *(const u32x4 *)((const float *)base + row_off + v);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t word = w[k];
-        x[2 * k] = bf16_lo(word);
-        x[2 * k + 1] = bf16_hi(word);
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t word = w[e];
+          x[e] = as_f32(word);
+        }
       }
     } else {
-      const u32x4 w0 = *(const u32x4 *)((const float *)base + row_off + v);
-      const u32x4 w1 = *(const u32x4 *)((const float *)base + row_off + v + 4);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t a = w0[k], b = w1[k];
-        x[k] = as_f32(a);
-        x[4 + k] = as_f32(b);
-      }
+      for (int e = 0; e < N; ++e) x[e] = v + e < V ? load_logit<BF16>(base, row_off + v + e) : -INFINITY;
     }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = v + e < V ? load_logit<BF16>(base, row_off + v + e) : -INFINITY;
   }
 }
 
@@ -797,7 +982,7 @@ constexpr int kListRank = 768;
 
 template <bool BF16>
 __device__ __forceinline__ bool warp_top_p_list(const AcceptParams &p, const void *row, const double *zs,
-                                                double mx_over_t, double *red, uint32_t *list, double *cmass,
+                                                double mx_over_t, double unit, double *red, uint32_t *list, double *cmass,
                                                 double *zk_out, uint32_t *key_min_out, double *z_out) {
   __shared__ int s_cnt[2][kWarpThreads / 64];
   __shared__ int s_n, s_ok;
@@ -816,6 +1001,7 @@ __device__ __forceinline__ bool warp_top_p_list(const AcceptParams &p, const voi
   double zk = 0.0;
 #pragma unroll
   for (int w = 0; w < kWarpThreads / 64; ++w) zk += red[w];
+  zk *= unit;   // in units of e^(max/T), as all masses below
   *zk_out = zk;
   const float lo_val = key_value(lo);   // -inf when fewer than kListRank lanes own a token: the whole row is listed
   if (tid == 0) s_n = 0;
@@ -881,7 +1067,16 @@ __device__ __forceinline__ bool warp_top_p_list(const AcceptParams &p, const voi
 // exponentials are spread over the chip here instead of being one workgroup's pass in the warp kernel.  A workgroup
 // takes several slices so that its start-up (the row maximum from the slice statistics) is shared and all its loads
 // are in flight together.
-constexpr int kRowzGroup = 4;
+template <bool TAB>
+struct RowzShape {
+  static constexpr int kHalves = TAB ? 2 : 1;
+  static constexpr int kT = kHalves * kThreads;
+  static constexpr int kPer = TAB ? 3 : 4;
+  static constexpr int kGroup = kHalves * kPer;   // fine slices of a workgroup
+};
+__host__ __device__ inline int rowz_group(const AcceptParams &p) {
+  return p.exp_tab ? RowzShape<true>::kGroup : RowzShape<false>::kGroup;
+}
 //
 // It also lists the tokens top-p can keep.  With Z the row's mass, tokens whose own mass is below (1 - top_p) Z / V
 // weigh less than (1 - top_p) Z together, so none of them is kept, and of a row that is peaked enough for a short list
@@ -896,20 +1091,26 @@ struct CandHeader {
 };
 template <bool BF16>
 __device__ __forceinline__ uint8_t *cand_segment(const AcceptParams &p, int rw, int group) {
-  return p.cand + ((size_t)rw * ((p.n_fine + kRowzGroup - 1) / kRowzGroup) + group) * p.cand_bytes;
+  return p.cand + ((size_t)rw * ((p.n_fine + rowz_group(p) - 1) / rowz_group(p)) + group) * p.cand_bytes;
 }
-constexpr int kCandLds = 1024;   // most keys of a segment
+constexpr int kCandLds = 1024;      // most keys of a segment
+constexpr int kCandLdsTab = 1792;   // ... of twice the slices (four workgroups' tables and lists fit a CU's LDS)
 template <bool BF16>
 __device__ __forceinline__ int cand_capacity(const AcceptParams &p) {
-  return min(kCandLds, (p.cand_bytes - (int)sizeof(CandHeader)) / (BF16 ? 2 : 4));
+  return min(BF16 && p.exp_tab ? kCandLdsTab : kCandLds, (p.cand_bytes - (int)sizeof(CandHeader)) / (BF16 ? 2 : 4));
 }
 
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void accept_rowz_kernel(const AcceptParams p) {
-  __shared__ double red[kRowzGroup][kThreads / 64];
-  __shared__ int s_cnt[kThreads / 64];
-  __shared__ uint32_t s_list[kCandLds + 1];   // (one more: the second half of the last word)
-  const int c0 = blockIdx.x * kRowzGroup, rw = blockIdx.y, tid = threadIdx.x;
+template <bool BF16, bool TAB>
+__global__ __launch_bounds__(RowzShape<TAB>::kT, (TAB ? 6 : 1)) void accept_rowz_kernel(const AcceptParams p) {
+  using Sh = RowzShape<TAB>;
+  typedef typename std::conditional<BF16, uint16_t, uint32_t>::type key_t;
+  __shared__ double red[Sh::kPer][Sh::kT / 64];
+  __shared__ int s_cnt[Sh::kT / 64];
+  __shared__ alignas(4) key_t s_list[(TAB ? kCandLdsTab : kCandLds) + 2];   // (bf16: the second half of the last word)
+  __shared__ alignas(16) double s_tab[TAB ? kTab : 2];
+  const int rw = blockIdx.y, tid = threadIdx.x;
+  // slices c0 .. c0 + kPer - 1 of this half of the workgroup
+  const int ht = tid % kThreads, c0 = blockIdx.x * Sh::kGroup + tid / kThreads * Sh::kPer;
   const int lane = tid & 63, wave = tid >> 6;
   const bool vec = ((size_t)p.V * (BF16 ? 2 : 4)) % 16 == 0;
   // the row maximum from the slice statistics (exact, so the same value in every workgroup and in the warp kernel) and
@@ -917,10 +1118,16 @@ __global__ __launch_bounds__(kThreads) void accept_rowz_kernel(const AcceptParam
   const bool one_round = p.n_chunks <= 64;
   f32x2 st = {-INFINITY, 0.f};
   if (one_round && lane < p.n_chunks) st = *(const f32x2 *)(p.stats + ((size_t)rw * p.n_chunks + lane) * 2);
-  float x[kRowzGroup][kFinePer];
+  TableCopy<Sh::kT> copy;
+  if constexpr (TAB) copy.load(p.exp_tab);
+  FineWords<BF16> w[Sh::kPer];
 #pragma unroll
-  for (int g = 0; g < kRowzGroup; ++g)   // (slices past the row read as -inf)
-    load_fine<BF16>(p.target, (size_t)rw * p.V, (c0 + g) * kFine + tid * kFinePer, p.V, vec, x[g]);
+  for (int g = 0; g < Sh::kPer; ++g)   // (slices past the row read as -inf)
+    w[g].load(p.target, (size_t)rw * p.V, (c0 + g) * kFine + ht * kFinePer, p.V, vec);
+  if constexpr (TAB) {
+    copy.store(s_tab);
+    __syncthreads();
+  }
   float m, z32;
   if (one_round) {
     m = wave_max_dpp(st.x);
@@ -928,18 +1135,21 @@ __global__ __launch_bounds__(kThreads) void accept_rowz_kernel(const AcceptParam
   } else {
     wave_fold_row(p, rw, lane, m, z32);
   }
-  const double mx_over_t = (double)m * p.inv_temp;
+  const double o_t = mass_unit(p, m);
   // (a token without mass -- a masked one, or a place past V -- is never listed)
   const float bound =
       fmaxf(m + __builtin_amdgcn_logf(8.0f * (1.0f - p.top_p) * z32 / (float)p.V) / p.inv_temp_log2, -3.402823466e38f);
   uint32_t marks = 0;   // bit g*8 + e: token e of slice g is listed
 #pragma unroll
-  for (int g = 0; g < kRowzGroup; ++g) {
-    double acc = 0.0;
+  for (int g = 0; g < Sh::kPer; ++g) {
+    float x[kFinePer];
+    double mass[kFinePer], acc = 0.0;
+    w[g].get(x);
+    masses<BF16, TAB>(w[g], s_tab, o_t, p, mass);   // (past V: -inf, mass 0)
 #pragma unroll
     for (int e = 0; e < kFinePer; ++e) {
-      acc += mass64(x[g][e], mx_over_t, p.inv_temp);   // (past V: -inf, mass 0)
-      if (x[g][e] >= bound) marks |= 1u << (g * kFinePer + e);
+      acc += mass[e];
+      if (x[e] >= bound) marks |= 1u << (g * kFinePer + e);
     }
     acc = wave_sum(acc);
     if (lane == 0) red[g][wave] = acc;
@@ -953,36 +1163,41 @@ __global__ __launch_bounds__(kThreads) void accept_rowz_kernel(const AcceptParam
   }
   if (lane == 63) s_cnt[wave] = incl;
   __syncthreads();
-  if (tid < kRowzGroup && c0 + tid < p.n_fine)
-    p.warp_zs[(size_t)rw * p.n_fine + c0 + tid] = (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
+  if (ht < Sh::kPer && c0 + ht < p.n_fine) {
+    const double *r = red[ht] + tid / kThreads * (kThreads / 64);
+    p.warp_zs[(size_t)rw * p.n_fine + c0 + ht] = (r[0] + r[1]) + (r[2] + r[3]);
+  }
   if (p.cand_bytes) {   // (uniform)
     // in rounds, one listed token per lane and round, its logit read once more (few, and just loaded: a test per token in
     // straight code took 4 us of the kernel's 18); through LDS, then in whole words to the segment
     uint8_t *seg = cand_segment<BF16>(p, rw, blockIdx.x);
-    const int total = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+    int total = 0;
+#pragma unroll
+    for (int i = 0; i < Sh::kT / 64; ++i) total += s_cnt[i];
     if (tid == 0) ((CandHeader *)seg)->n = (uint32_t)total;
     if (total > cand_capacity<BF16>(p)) return;   // (uniform)
     int at = incl - own;
-    for (int w = 0; w < wave; ++w) at += s_cnt[w];
+    for (int i = 0; i < wave; ++i) at += s_cnt[i];
     for (; marks; marks &= marks - 1, ++at) {
       const int bit = __ffs((int)marks) - 1;
-      const int v = (c0 + bit / kFinePer) * kFine + tid * kFinePer + bit % kFinePer;
+      const int v = (c0 + bit / kFinePer) * kFine + ht * kFinePer + bit % kFinePer;
       const uint32_t key = order_key(load_logit<BF16>(p.target, (size_t)rw * p.V + v));
-      s_list[at] = BF16 ? key >> 16 : key;
+      s_list[at] = (key_t)(BF16 ? key >> 16 : key);
     }
     __syncthreads();
     uint32_t *to = (uint32_t *)(seg + sizeof(CandHeader));   // (the segment ends on a multiple of 16 bytes)
-    if constexpr (BF16) {
-      for (int i = tid; 2 * i < total; i += kThreads) to[i] = s_list[2 * i] | s_list[2 * i + 1] << 16;
-    } else {
-      for (int i = tid; i < total; i += kThreads) to[i] = s_list[i];
-    }
+    const int words = BF16 ? (total + 1) / 2 : total;
+    for (int i = tid; i < words; i += Sh::kT) to[i] = ((const uint32_t *)s_list)[i];
   }
 }
 
 // top-p without top-k from the segments accept_rowz_kernel wrote.  The threshold is the largest c with
 // mass{key >= c} >= top_p * zk: the tokens at or above it stay -- the mass above each of them is below the target --
-// and no other does.  It is found from the top bits down, two bits per round, the fp64 masses of a lane's keys in
+// and no other does.
+// bf16 rows have few distinct values between the listed tokens' smallest and the row maximum (128 an octave): the tokens
+// are counted per value, and the threshold is read off the running mass over the values in descending order
+// (warp_top_p_bins: 14.7 -> 7.8 us at 54 rows of 152064, T 0.6, top_p 0.95, and no limit on the list's length: 24 rows at
+// T 1.0, which list 26000 tokens each and went the long way, take 36 instead of 214 us for the call).  Where the list spans more values, and for fp32 rows, it is found from the top bits down, two bits per round, the fp64 masses of a lane's keys in
 // registers and three sums per round; every sum runs in a fixed order.  Bound by its chain of loads, barriers and
 // rounds, 54 workgroups on the chip: 44.3 -> 14.6 us at 54 rows of 152064 (T 0.6, top_p 0.95) against two passes of a
 // workgroup over its row and a sort; with the sums through LDS shuffles it was 21.4 us.  false: a segment is incomplete, the list is
@@ -990,18 +1205,106 @@ __global__ __launch_bounds__(kThreads) void accept_rowz_kernel(const AcceptParam
 constexpr int kCandPer = 8;                        // keys per lane
 constexpr int kCandMax = kCandPer * kWarpThreads;  // (the LDS list holds as many)
 
+// The form for bf16 rows.  m: the row maximum; zk: the row's mass; keys0: the first 16 bytes a lane reads of its wavefront's
+// first segment, requested before the segments' counts were known; s_n: the counts.  false: the listed tokens span more
+// values than there are bins, or fall short of the target (the same decision in every lane).
+constexpr int kBinPer = 4;                       // values per lane
+constexpr int kBins = kBinPer * kWarpThreads;    // 32 octaves; the counts share the list's storage
+
+__device__ __forceinline__ bool warp_top_p_bins(const AcceptParams &p, int rw, float m, double zk, u32x4 keys0, const int *s_n,
+                                                int n_g, uint32_t *bins, uint32_t *key_min_out, double *z_out) {
+  constexpr int kW = kWarpThreads / 64;
+  __shared__ int s_outside, s_at[kW];
+  __shared__ double s_mass[kW], s_at_mass[kW];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t top = order_key(m) >> 16;
+  if (tid == 0) s_outside = 0;
+  *(u32x4 *)(bins + tid * kBinPer) = (u32x4){0, 0, 0, 0};
+  __syncthreads();
+  for (int g = wave; g < n_g; g += kW) {
+    const u32x4 *keys = (const u32x4 *)(cand_segment<true>(p, rw, g) + sizeof(CandHeader));
+    const int cnt = s_n[g];
+    for (int i = lane; i * 8 < cnt; i += 64) {   // eight keys to a load (a segment ends on a multiple of 16 bytes)
+      const u32x4 w = g == wave && i == lane ? keys0 : keys[i];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t word = w[k];
+        const uint32_t b0 = top - (word & 0xFFFFu), b1 = top - (word >> 16);
+        const bool in0 = i * 8 + 2 * k < cnt, in1 = i * 8 + 2 * k + 1 < cnt;
+        if (in0 && b0 < kBins) atomicAdd(&bins[b0], 1u);
+        if (in1 && b1 < kBins) atomicAdd(&bins[b1], 1u);
+        if ((in0 && b0 >= kBins) || (in1 && b1 >= kBins)) s_outside = 1;
+      }
+    }
+  }
+  __syncthreads();
+  if (s_outside) return false;
+  const double o_t = mass_unit(p, m);
+  const u32x4 n_of = *(const u32x4 *)(bins + tid * kBinPer);
+  auto key_of = [&](int bin) {   // (the sixteen low bits of a widened bf16 value's key)
+    const uint32_t k = (top - (uint32_t)bin) << 16;
+    return k | ((k >> 31) ? 0u : 0xFFFFu);
+  };
+  double mass[kBinPer], own = 0.0;
+#pragma unroll
+  for (int j = 0; j < kBinPer; ++j) {
+    const uint32_t n = n_of[j];
+    mass[j] = 0.0;
+    if (__ballot(n != 0))
+      mass[j] = n ? (double)n * mass64(key_value(key_of(tid * kBinPer + j)), o_t, p.inv_temp) : 0.0;
+    own += mass[j];
+  }
+  // running mass in descending order of the values: lanes, then wavefronts, in order
+  double incl = own;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const double up = __shfl_up(incl, off);
+    if (lane >= off) incl += up;
+  }
+  if (lane == 63) s_mass[wave] = incl;
+  __syncthreads();
+  double before = 0.0;
+  for (int w = 0; w < wave; ++w) before += s_mass[w];
+  const double target = (double)p.top_p * zk;
+  double run = before + (incl - own), at_mass = 0.0;
+  int at = INT_MAX;   // this lane's first value at which the running mass reaches the target
+#pragma unroll
+  for (int j = 0; j < kBinPer; ++j) {
+    run += mass[j];
+    if (at == INT_MAX && mass[j] > 0.0 && run >= target) at = tid * kBinPer + j, at_mass = run;
+  }
+  const uint64_t hits = __ballot(at != INT_MAX);
+  const int src = hits ? __ffsll((unsigned long long)hits) - 1 : 0;
+  const int first = __shfl(at, src);
+  const double first_mass = __shfl(at_mass, src);
+  if (lane == 0) s_at[wave] = first, s_at_mass[wave] = first_mass;
+  __syncthreads();
+  int bin = INT_MAX;
+  double z = 0.0;
+#pragma unroll
+  for (int w = 0; w < kW; ++w)
+    if (bin == INT_MAX && s_at[w] != INT_MAX) bin = s_at[w], z = s_at_mass[w];
+  if (bin == INT_MAX) return false;
+  *key_min_out = key_of(bin);
+  *z_out = z * unit_over_max(p, m);
+  return true;
+}
+
 template <bool BF16>
 __device__ __forceinline__ bool warp_top_p_segments(const AcceptParams &p, int rw, double *red, uint32_t *list, float *row_max_out,
                                                     uint32_t *key_min_out, double *z_out) {
   constexpr int kW = kWarpThreads / 64;
-  constexpr int kMaxGroups = kMaxFine / kRowzGroup;
-  __shared__ int s_off[kMaxGroups + 1], s_wave[kW], s_bad;
+  constexpr int kMaxGroups = kMaxFine / RowzShape<false>::kGroup;
+  __shared__ int s_off[kMaxGroups + 1], s_n[kMaxGroups], s_wave[kW], s_bad;
   __shared__ uint32_t s_low[kW];
   __shared__ double s_sum[2][3][kW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int n_g = (p.n_fine + kRowzGroup - 1) / kRowzGroup, cap = cand_capacity<BF16>(p);
+  const int n_g = (p.n_fine + rowz_group(p) - 1) / rowz_group(p), cap = cand_capacity<BF16>(p);
   // zk from the row's fine-slice sums, in a fixed order: slice t in lane t, a butterfly per wavefront, the wavefronts
   // in order
+  u32x4 keys0 = {0, 0, 0, 0};
+  if (BF16 && wave < n_g && (int)sizeof(CandHeader) + (lane + 1) * 16 <= p.cand_bytes)
+    keys0 = ((const u32x4 *)(cand_segment<BF16>(p, rw, wave) + sizeof(CandHeader)))[lane];
   double acc = 0.0;
   for (int t = tid; t < p.n_fine; t += kWarpThreads) acc += p.warp_zs[(size_t)rw * p.n_fine + t];
   // where each segment's keys go in the list (n_g <= kMaxGroups <= the workgroup)
@@ -1012,7 +1315,7 @@ __device__ __forceinline__ bool warp_top_p_segments(const AcceptParams &p, int r
   if (lane == 0) red[wave] = acc;
   m = wave_max_dpp(m);
   *row_max_out = m;
-  const double mx_over_t = (double)m * p.inv_temp;
+  const double o_t = mass_unit(p, m);   // the masses here are in the unit of the slice sums
   const bool bad = own > cap;
   int incl = own;
 #pragma unroll
@@ -1030,13 +1333,18 @@ __device__ __forceinline__ bool warp_top_p_segments(const AcceptParams &p, int r
     base += w < wave ? s_wave[w] : 0;
     n += s_wave[w];
   }
-  if (tid < n_g) s_off[tid] = base + incl - own;
+  if (tid < n_g) s_off[tid] = base + incl - own, s_n[tid] = own;
   if (tid == n_g) s_off[n_g] = n;
   double zk = 0.0;
 #pragma unroll
   for (int w = 0; w < kW; ++w) zk += red[w];
   __syncthreads();
-  if (s_bad || n > kCandMax || n < 1) return false;
+  if (s_bad || n < 1) return false;
+  if constexpr (BF16) {
+    if (warp_top_p_bins(p, rw, m, zk, keys0, s_n, n_g, list, key_min_out, z_out)) return true;
+    __syncthreads();
+  }
+  if (n > kCandMax) return false;
   for (int g = wave; g < n_g; g += kW) {
     const uint8_t *keys = cand_segment<BF16>(p, rw, g) + sizeof(CandHeader);
     const int off = s_off[g], cnt = s_off[g + 1] - off;
@@ -1060,7 +1368,7 @@ __device__ __forceinline__ bool warp_top_p_segments(const AcceptParams &p, int r
       if (i < n) {
         key[j] = list[i];
         low = min(low, key[j]);
-        mass[j] = mass64(key_value(key[j]), mx_over_t, p.inv_temp);
+        mass[j] = mass64(key_value(key[j]), o_t, p.inv_temp);
       }
       total += mass[j];
     }
@@ -1115,7 +1423,7 @@ __device__ __forceinline__ bool warp_top_p_segments(const AcceptParams &p, int r
     bit = sh - 1;
   }
   *key_min_out = lo;
-  *z_out = z;
+  *z_out = z * unit_over_max(p, m);
   return true;
 }
 
@@ -1158,7 +1466,7 @@ __global__ __launch_bounds__(kWarpThreads) void accept_warp_kernel(const AcceptP
     if (p.top_p < 1.0f) {
       double zk = 0.0;
       if (!use_k)
-        listed = warp_top_p_list<BF16>(p, row, p.warp_zs + (size_t)rw * p.n_fine, mx_over_t, red, cnt, mass + kCand,
+        listed = warp_top_p_list<BF16>(p, row, p.warp_zs + (size_t)rw * p.n_fine, mx_over_t, unit_over_max(p, m), red, cnt, mass + kCand,
                                        &zk, &key_min, &zw);
       else
         zk = kept_mass<BF16>(row, p.V, mx_over_t, p.inv_temp, key_min, red, &s_slot);
@@ -1175,7 +1483,7 @@ __global__ __launch_bounds__(kWarpThreads) void accept_warp_kernel(const AcceptP
 }
 
 // ---------------------------------------------------------------------------------------------
-// sample: grid (n_fine, NB).  Accepted length of the branch (every workgroup derives it; slice 0 publishes it), then
+// sample: grid (n_fine slices, one or two to a workgroup; NB).  Accepted length of the branch (every workgroup derives it; slice 0 publishes it), then
 // what this slice contributes to the normalisers of the resampling rows and to the residual.
 //
 // The residual max(0, a/Zt - b/Zq) of a token (a, b its unnormalised masses in the target and the draft row) needs both
@@ -1207,21 +1515,35 @@ struct alignas(16) BranchHead {
   }
 };
 
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void accept_sample_kernel(const AcceptParams p) {
+// Slices of a workgroup, 256 lanes each: two share a table (four workgroups' tables fit a CU's LDS).  Measured: four slices
+// per workgroup, in two rounds, leave some CUs three workgroups and others two (15.0 against 14.6 us at 32 branches of
+// 152064); 64 registers instead of 70, for a fourth workgroup per CU, spill.
+template <bool TAB>
+constexpr int kSampleSlices = TAB ? 2 : 1;
+
+template <bool BF16, bool TAB>
+__global__ __launch_bounds__(kSampleSlices<TAB> * kThreads, (TAB ? 6 : 1)) void accept_sample_kernel(const AcceptParams p) {
+  constexpr int kHalves = kSampleSlices<TAB>, kT = kHalves * kThreads;
   constexpr int kPass = 64;                       // drafted positions examined per pass
   constexpr int kRow = 16;                        // lanes that fold one row's slice statistics (a DPP row)
   __shared__ float sm[2][kPass], sz[2][kPass];    // [target|draft][position in pass]: folded row statistics
   __shared__ BranchHead s_head;                   // of the resampling rows
   __shared__ float s_bonus;                       // maximum of target row K
   __shared__ int s_first;
-  __shared__ double red[4][kThreads / 64];
-  __shared__ uint32_t s_amb[kThreads / 64];
-  const int c = blockIdx.x, nb = blockIdx.y, tid = threadIdx.x;
+  __shared__ double red[4][kT / 64];
+  __shared__ uint32_t s_amb[kT / 64];
+  __shared__ alignas(16) double s_tab[TAB ? kTab : 2];
+  const int nb = blockIdx.y, tid = threadIdx.x;
+  const int ht = tid % kThreads, c = blockIdx.x * kHalves + tid / kThreads;   // lane of the slice, slice
+  const bool first_wg = blockIdx.x == 0;
   const int lane = tid & 63, wave = tid >> 6;
   const int n_t = p.NB * (p.K + 1);
   const int n_which = p.draft ? 2 : 1;   // point-mass draft: there are no draft rows
   if (tid == 0) s_first = p.K;
+  TableCopy<kT> copy;
+  if constexpr (TAB) {
+    copy.load(p.exp_tab);   // (stored once the loads of the first pass have been requested)
+  }
   bool have_top = false;
   for (int i0 = 0; i0 < p.K; i0 += kPass) {   // a later pass cannot lower the first rejection found in an earlier one
     const int cnt = min(kPass, p.K - i0);
@@ -1240,7 +1562,7 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(const AcceptPar
     // sixteen lanes per row
     const int bonus = i0 + cnt == p.K ? 1 : 0;
     const int n_rows = n_which * cnt + bonus;
-    for (int slot = tid / kRow; slot < n_rows; slot += kThreads / kRow) {
+    for (int slot = tid / kRow; slot < n_rows; slot += kT / kRow) {
       const int which = slot >= cnt, j = slot - which * cnt;
       const bool is_bonus = slot == n_which * cnt;
       const int rw = is_bonus ? nb * (p.K + 1) + p.K : which ? n_t + nb * p.K + i0 + j : nb * (p.K + 1) + i0 + j;
@@ -1262,6 +1584,7 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(const AcceptPar
           sm[which][j] = m, sz[which][j] = z;
       }
     }
+    if (TAB && i0 == 0) copy.store(s_tab);
     __syncthreads();
     if (tid < cnt) {
       const int i = i0 + tid;
@@ -1275,7 +1598,7 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(const AcceptPar
       float qx = 1.0f;   // point-mass draft at x
       if (p.draft) qx = __builtin_amdgcn_exp2f((dx - sm[1][tid]) * p.inv_temp_log2) / sz[1][tid];
       if (!(u * qx < px)) atomicMin(&s_first, i);
-      if (c == 0 && p.ratio) p.ratio[(size_t)nb * p.K + i] = px / qx;
+      if (first_wg && p.ratio) p.ratio[(size_t)nb * p.K + i] = px / qx;
     }
     __syncthreads();
     if (s_first < p.K) {  // uniform: the first rejection lies in this pass
@@ -1287,7 +1610,7 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(const AcceptPar
       have_top = true;
       // the workgroup that reports the ratios goes on through the remaining passes (every position gets its ratio,
       // also those behind the rejection); s_first cannot change any more, atomicMin only lowers it to values < i
-      if (!(c == 0 && p.ratio)) break;
+      if (!(first_wg && p.ratio)) break;
     }
     __syncthreads();  // sm / sz free for the next pass
   }
@@ -1307,45 +1630,48 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(const AcceptPar
   const size_t trow = ((size_t)nb * (p.K + 1) + n) * p.V;
   const size_t drow = ((size_t)nb * p.K + (n < p.K ? n : 0)) * p.V;
   const bool vec = ((size_t)p.V * (BF16 ? 2 : 4)) % 16 == 0;
-  const int vb = c * kFine + tid * kFinePer;
-  float tx[kFinePer], dx[kFinePer];
-  load_fine<BF16>(p.target, trow, vb, p.V, vec, tx);
-  if (with_draft) load_fine<BF16>(p.draft, drow, vb, p.V, vec, dx);
-  if (c == 0 && tid == 0) {
+  const int vb = c * kFine + ht * kFinePer;
+  FineWords<BF16> wt, wd;   // (a slice past the row reads as -inf)
+  wt.load(p.target, trow, vb, p.V, vec);
+  if (with_draft) wd.load(p.draft, drow, vb, p.V, vec);
+  if (first_wg && tid == 0) {
     p.accepted_len[nb] = n;
     p.n_acc[nb] = n;
     ((BranchHead *)p.heads)[nb] = head;
   }
-  const double mt_t = (double)head.mt * p.inv_temp, mq_t = (double)head.mq * p.inv_temp;
+  const double ot = mass_unit(p, head.mt), oq = mass_unit(p, head.mq);
   // (log2 units; x - y above the threshold: the residual is positive)
   const float margin = head.margin(p);
   const float threshold = (float)(((double)head.mt - (double)head.mq) * (double)p.inv_temp_log2 +
                                   (double)__builtin_amdgcn_logf(head.zt / head.zq));
-  // no bounds test per token: load_fine gives -inf past V, whose mass is exactly 0, and the eight exponentials of a
-  // lane can then be evaluated side by side instead of one dependent chain after the other
-  if (p.warp_key) {   // (comparing values is comparing keys)
-#pragma unroll
-    for (int e = 0; e < kFinePer; ++e) tx[e] = tx[e] >= x_min ? tx[e] : -INFINITY;
-  }
+  // no bounds test per token: load_fine gives -inf past V, whose mass is exactly 0, and the eight masses of a lane can
+  // then be evaluated side by side instead of one dependent chain after the other
+  if (p.warp_key) wt.keep(x_min);   // (comparing values is comparing keys)
   double a[kFinePer], b[kFinePer];
-#pragma unroll
-  for (int e = 0; e < kFinePer; ++e) {
-    a[e] = mass64(tx[e], mt_t, p.inv_temp);
-    if (with_draft) b[e] = mass64(dx[e], mq_t, p.inv_temp);
-  }
+  masses<BF16, TAB>(wt, s_tab, ot, p, a);
   double sa = 0.0, sb = 0.0, pa = 0.0, pb = 0.0;
   uint32_t doubt = 0;   // bit e: token e is in doubt
   if (with_draft) {
+    masses<BF16, TAB>(wd, s_tab, oq, p, b);
+    float tx[kFinePer], dx[kFinePer], closest = INFINITY;
+    wt.get(tx);
+    wd.get(dx);
 #pragma unroll
     for (int e = 0; e < kFinePer; ++e) {
       sa += a[e];
       sb += b[e];
-      // (a token without mass in the target row has no residual and is never in doubt)
+      // (where neither row has mass this is a NaN, and both terms are zero)
       const float d = __builtin_fmaf(tx[e] - dx[e], p.inv_temp_log2, -threshold);
-      const bool some = tx[e] > -INFINITY, pos = some && d > margin;
+      const bool pos = d > margin;
       pa += pos ? a[e] : 0.0;
       pb += pos ? b[e] : 0.0;
-      if (some && fabsf(d) <= margin) doubt |= 1u << e;
+      closest = fminf(closest, fabsf(d));
+      tx[e] = d;
+    }
+    if (__ballot(closest <= margin)) {
+#pragma unroll
+      for (int e = 0; e < kFinePer; ++e)   // (a token without mass in the target row has no residual)
+        if (fabsf(tx[e]) <= margin && a[e] > 0.0) doubt |= 1u << e;
     }
   } else {
 #pragma unroll
@@ -1366,8 +1692,8 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(const AcceptPar
     n_amb = (uint32_t)__shfl(incl, 63);
     if (n_amb > kAmb) {
       n_amb = kAmbOver;
-    } else {
-      Doubt *to = doubt_list(p, nb, c, wave) + (incl - own);
+    } else {   // (a slice past the row holds none)
+      Doubt *to = doubt_list(p, nb, c, wave % (kThreads / 64)) + (incl - own);
 #pragma unroll
       for (int e = 0; e < kFinePer; ++e)
         if (doubt & (1u << e)) *to++ = {a[e], b[e]};
@@ -1381,63 +1707,95 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(const AcceptPar
     s_amb[wave] = n_amb;
   }
   __syncthreads();
-  if (tid < 4) {
-    double *to = tid < 2 ? p.zsum : p.rsum;
-    to[((size_t)nb * 2 + (tid & 1)) * p.n_fine + c] = (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
-    if (tid == 0)
-      p.amb_n[(size_t)nb * p.n_fine + c] = s_amb[0] | s_amb[1] << 8 | s_amb[2] << 16 | s_amb[3] << 24;
+  if (ht < 4 && c < p.n_fine) {   // lane k of a slice: sum k
+    const double *r = red[ht] + tid / kThreads * (kThreads / 64);
+    double *to = ht < 2 ? p.zsum : p.rsum;
+    to[((size_t)nb * 2 + (ht & 1)) * p.n_fine + c] = (r[0] + r[1]) + (r[2] + r[3]);
+    if (ht == 0) {
+      const uint32_t *n_of = s_amb + tid / kThreads * (kThreads / 64);
+      p.amb_n[(size_t)nb * p.n_fine + c] = n_of[0] | n_of[1] << 8 | n_of[2] << 16 | n_of[3] << 24;
+    }
   }
 }
 
-// Two rows of n <= kMaxFine doubles, loaded together: a lane's terms are those at tid + kThreads * j.
-struct FoldPair {
-  static constexpr int kTerms = kMaxFine / kThreads;
-  double a[kTerms], b[kTerms];
-  __device__ __forceinline__ void load(const double *v0, const double *v1, int n) {
+// One double per wavefront from LDS, added up: the same value in every lane.
+template <int kW>
+__device__ __forceinline__ double sum_of_waves(const double *v) {
+  static_assert(kW <= 16, "a DPP row holds one value per wavefront");
+  const int i = threadIdx.x % 16;
+  return row_sum(i < kW ? v[i] : 0.0);
+}
+
+// Where a running sum over the workgroup's values crosses thr = u * total: v is a lane's (non-negative) value, lanes in
+// order.  Every lane gets the total, its own exclusive prefix, the first lane whose running sum exceeds thr (the last lane
+// with a value if rounding hides it; -1 without any).  One barrier inside, one expected before the next call.
+template <int kW>
+struct Crossing {
+  double total, excl, thr;
+  int lane;
+  __device__ __forceinline__ void find(double v, double u, double base, bool have_total, double total_in, double *s_tot) {
+    const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double incl = v;
 #pragma unroll
-    for (int j = 0; j < kTerms; ++j) {
-      const int c = threadIdx.x + kThreads * j;
-      a[j] = c < n ? v0[c] : 0.0;
-      b[j] = c < n ? v1[c] : 0.0;
+    for (int off = 1; off < 64; off <<= 1) {
+      const double up = __shfl_up(incl, off);
+      if (l >= off) incl += up;
+    }
+    const uint64_t some = __ballot(v > 0.0);
+    if (l == 63) s_tot[wave] = incl;
+    __shared__ int s_last[kW], s_hit[kW];
+    if (l == 0) s_last[wave] = some ? (int)threadIdx.x + 63 - __clzll((long long)some) : -1;
+    __syncthreads();
+    total = have_total ? total_in : sum_of_waves<kW>(s_tot);
+    const int i = threadIdx.x % 16;
+    excl = base + row_sum(i < wave ? s_tot[i] : 0.0) + (incl - v);
+    thr = u * total;
+    const uint64_t hit = __ballot(v > 0.0 && excl + v > thr);
+    if (l == 0) s_hit[wave] = hit ? (int)threadIdx.x + __ffsll((unsigned long long)hit) - 1 : INT_MAX;
+    __syncthreads();
+    const uint64_t waves = __ballot(l < kW && s_hit[l < kW ? l : 0] != INT_MAX);
+    if (waves) {
+      lane = s_hit[__ffsll((unsigned long long)waves) - 1];
+    } else {
+      lane = -1;
+      for (int w = 0; w < kW; ++w) lane = max(lane, s_last[w]);
     }
   }
 };
 
-// Sums of two doubles per lane over the workgroup, the same values in every lane, in a fixed association (a butterfly
-// inside each wavefront, the wavefronts in order).
-__device__ __forceinline__ void block_sum2(double &x, double &y) {
-  __shared__ double fold_red[2][kThreads / 64];
-  x = wave_sum(x);
-  y = wave_sum(y);
-  __syncthreads();   // fold_red free again (a previous call's readers are past their reads)
-  if ((threadIdx.x & 63) == 0) fold_red[0][threadIdx.x >> 6] = x, fold_red[1][threadIdx.x >> 6] = y;
-  __syncthreads();
-  x = (fold_red[0][0] + fold_red[0][1]) + (fold_red[0][2] + fold_red[0][3]);
-  y = (fold_red[1][0] + fold_red[1][1]) + (fold_red[1][2] + fold_red[1][3]);
+// ---------------------------------------------------------------------------------------------
+// pick: grid NB.  Bound by its chain of loads, barriers and scans, one workgroup per branch.  T lanes: 512, four tokens of the
+// chosen slice each, from 16 slices on (32 branches of 152064: 9.3 us; 256 lanes, of eight tokens, 11.8, 1024 lanes 10.7);
+// 256 where the rows are short and many.
+// ---------------------------------------------------------------------------------------------
+__device__ __forceinline__ double residual(double pm, double qm) {
+#pragma clang fp contract(off)
+  return pm - qm;
 }
 
-// ---------------------------------------------------------------------------------------------
-// pick: grid NB
-// ---------------------------------------------------------------------------------------------
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void accept_pick_kernel(const AcceptParams p) {
+template <bool BF16, int T>
+__global__ __launch_bounds__(T) void accept_pick_kernel(const AcceptParams p) {
+  constexpr int kW = T / 64, kOwn = kFine / T, kTerms = kMaxFine / T;   // (a lane's slices: tid * kTerms + j)
+  constexpr int kLists = kThreads / 64;               // lists of a slice
   __shared__ double buf0[kMaxFine], buf1[kMaxFine];   // slice sums of the residual and of p
-  __shared__ uint32_t s_amb[kMaxFine];                // tokens in doubt per slice, a byte per wavefront of its workgroup
-  __shared__ double s_before;
-  __shared__ double wave_tot[kThreads / 64];
-  __shared__ int s_slice, s_lane, s_last_lane;
-  constexpr int kTerms = FoldPair::kTerms;
+  __shared__ uint32_t s_amb[kMaxFine];                // tokens in doubt per slice, a byte per list
+  __shared__ double s_sum[2][kW], s_tot[kW], s_before;
+  __shared__ int s_flags[kW], s_slice;
   const int nb = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   // everything that does not depend on the accepted length is requested in one round trip
-  FoldPair tot, pos;
-  tot.load(p.zsum + ((size_t)nb * 2 + 0) * p.n_fine, p.zsum + ((size_t)nb * 2 + 1) * p.n_fine, p.n_fine);
-  pos.load(p.rsum + ((size_t)nb * 2 + 0) * p.n_fine, p.rsum + ((size_t)nb * 2 + 1) * p.n_fine, p.n_fine);
+  double ta[kTerms], tb[kTerms], pa[kTerms], pb[kTerms];
   uint32_t amb[kTerms];
+  const size_t at0 = ((size_t)nb * 2 + 0) * p.n_fine, at1 = ((size_t)nb * 2 + 1) * p.n_fine;
 #pragma unroll
   for (int j = 0; j < kTerms; ++j) {
-    const int c = tid + kThreads * j;
-    amb[j] = c < p.n_fine ? p.amb_n[(size_t)nb * p.n_fine + c] : 0u;
+    const int c = tid * kTerms + j;
+    const bool in = c < p.n_fine;
+    ta[j] = in ? p.zsum[at0 + c] : 0.0;
+    tb[j] = in ? p.zsum[at1 + c] : 0.0;
+    pa[j] = in ? p.rsum[at0 + c] : 0.0;
+    pb[j] = in ? p.rsum[at1 + c] : 0.0;
+    amb[j] = in ? p.amb_n[(size_t)nb * p.n_fine + c] : 0u;
   }
   const BranchHead head = ((const BranchHead *)p.heads)[nb];
   const int n = p.n_acc[nb];
@@ -1446,67 +1804,77 @@ __global__ __launch_bounds__(kThreads) void accept_pick_kernel(const AcceptParam
   const int removed = (n < p.K && !p.draft) ? p.tokens[(size_t)nb * p.K + n] : -1;
   const size_t trow = ((size_t)nb * (p.K + 1) + n) * p.V;
   const size_t drow = ((size_t)nb * p.K + (n < p.K ? n : 0)) * p.V;
-  uint32_t key_min = 0;
+  float x_min = -INFINITY;
   double zw = 0.0;
-  if (p.warp_key) {
-    key_min = p.warp_key[nb * (p.K + 1) + n];
+  if (p.warp_key) {   // (comparing values is comparing keys)
+    x_min = key_value(p.warp_key[nb * (p.K + 1) + n]);
     zw = p.warp_z[nb * (p.K + 1) + n];
   }
   double zt = 0.0, zq = 0.0;
 #pragma unroll
-  for (int j = 0; j < kTerms; ++j) zt += tot.a[j], zq += tot.b[j];
-  block_sum2(zt, zq);
-  if (p.warp_key) zt = zw;   // the kept mass replaces the row's full normaliser
+  for (int j = 0; j < kTerms; ++j) zt += ta[j], zq += tb[j];
+  zt = wave_sum(zt);
+  zq = wave_sum(zq);
+  if (lane == 0) s_sum[0][wave] = zt, s_sum[1][wave] = zq;
+  __syncthreads();
+  zt = sum_of_waves<kW>(s_sum[0]);
+  zq = sum_of_waves<kW>(s_sum[1]);
+  // the kept mass of a warped row replaces its full normaliser; it and the heads' are in units of e^(max/T)
+  if (p.warp_key) zt = zw / unit_over_max(p, head.mt);
   if (!with_draft) zq = 1.0;
   const double inv_zt = 1.0 / zt, inv_zq = 1.0 / zq;
-  const double mt_t = (double)head.mt * p.inv_temp, mq_t = (double)head.mq * p.inv_temp;
-  // the residual and p of the eight tokens of slice c that this lane owns: all loads first, then the masses side by side
+  const double mt_t = mass_unit(p, head.mt), mq_t = mass_unit(p, head.mq);
+  // the residual and p of the tokens of slice c that this lane owns: all loads first, then the masses side by side
   // (tokens past V read as -inf and have no mass)
-  auto eval = [&](int c, double (&r)[kFinePer], double (&pm)[kFinePer]) {
-    const int v0 = c * kFine + tid * kFinePer;
+  auto eval = [&](int c, double (&r)[kOwn], double (&pm)[kOwn]) {
+    const int v0 = c * kFine + tid * kOwn;
     const bool vec = ((size_t)p.V * (BF16 ? 2 : 4)) % 16 == 0;
-    float tx[kFinePer], dx[kFinePer];
-    load_fine<BF16>(p.target, trow, v0, p.V, vec, tx);
-    if (with_draft) load_fine<BF16>(p.draft, drow, v0, p.V, vec, dx);
+    float tx[kOwn], dx[kOwn];
+    load_own<BF16, kOwn>(p.target, trow, v0, p.V, vec, tx);
+    if (with_draft) load_own<BF16, kOwn>(p.draft, drow, v0, p.V, vec, dx);
 #pragma unroll
-    for (int e = 0; e < kFinePer; ++e) {
-      pm[e] = order_key(tx[e]) >= key_min ? mass64(tx[e], mt_t, p.inv_temp) * inv_zt : 0.0;
+    for (int e = 0; e < kOwn; ++e) {
+      // (no fused multiply-add over the difference: a token's residual is then the same here as from its listed masses)
+      pm[e] = tx[e] >= x_min ? mass_again<BF16>(tx[e], mt_t, p) * inv_zt : 0.0;
       r[e] = v0 + e == removed ? 0.0 : pm[e];
-      if (with_draft) {
-        r[e] = pm[e] - mass64(dx[e], mq_t, p.inv_temp) * inv_zq;
-        if (r[e] < 0.0) r[e] = 0.0;
-      }
+      if (with_draft) r[e] = fmax(residual(pm[e], mass_again<BF16>(dx[e], mq_t, p) * inv_zq), 0.0);
     }
   };
   // the tokens counted as positive or negative by the fp32 quotient are so if the exact one lies within half the margin
   // of it; else every slice is evaluated again
-  const bool trusted = !with_draft || fabs((double)head.zt / (double)head.zq * zq * inv_zt - 1.0) <=
-                                          0.5 * 0.69 * (double)head.margin(p);   // (log2 units)
+  const bool trusted =
+      !with_draft || fabs((double)head.zt / (double)head.zq * (zq * unit_over_max(p, head.mq)) /
+                              (zt * unit_over_max(p, head.mt)) - 1.0) <= 0.5 * 0.69 * (double)head.margin(p);   // (log2)
   auto overflowed = [](uint32_t w) {
     return (w & 255u) == kAmbOver || (w >> 8 & 255u) == kAmbOver || (w >> 16 & 255u) == kAmbOver || w >> 24 == kAmbOver;
   };
   bool any = false, over = false;
 #pragma unroll
   for (int j = 0; j < kTerms; ++j) {
-    const int c = tid + kThreads * j;
+    const int c = tid * kTerms + j;
     if (c < p.n_fine) {
-      buf0[c] = pos.a[j] * inv_zt - pos.b[j] * inv_zq;
-      buf1[c] = tot.a[j] * inv_zt;
+      buf0[c] = residual(pa[j] * inv_zt, pb[j] * inv_zq);
+      buf1[c] = ta[j] * inv_zt;
       if (!trusted) amb[j] = kAmbOver;
       s_amb[c] = amb[j];
       any = any || amb[j];
       over = over || overflowed(amb[j]);
     }
   }
-  if (__syncthreads_or(any)) {
-    const bool some_over = __syncthreads_or(over);
+  {
+    const int flags = (__ballot(any) ? 1 : 0) | (__ballot(over) ? 2 : 0);
+    if (lane == 0) s_flags[wave] = flags;
+  }
+  __syncthreads();
+  const int flags = lane < kW ? s_flags[lane] : 0;
+  if (__ballot(flags & 1)) {   // (uniform)
     // sixteen lanes per slice, the loads of its four lists in one round trip
-    for (int c = tid / 16; c < p.n_fine; c += kThreads / 16) {
+    for (int c = tid / 16; c < p.n_fine; c += T / 16) {
       const uint32_t w = s_amb[c];
       if (w == 0 || overflowed(w)) continue;
-      Doubt t[kThreads / 64][kAmb / 16];
+      Doubt t[kLists][kAmb / 16];
 #pragma unroll
-      for (int k = 0; k < kThreads / 64; ++k)
+      for (int k = 0; k < kLists; ++k)
 #pragma unroll
         for (int i = 0; i < kAmb / 16; ++i) {
           t[k][i] = {0.0, 0.0};
@@ -1514,125 +1882,94 @@ __global__ __launch_bounds__(kThreads) void accept_pick_kernel(const AcceptParam
         }
       double add = 0.0;
 #pragma unroll
-      for (int k = 0; k < kThreads / 64; ++k)
+      for (int k = 0; k < kLists; ++k)
 #pragma unroll
         for (int i = 0; i < kAmb / 16; ++i) {
-          const double r = t[k][i].a * inv_zt - t[k][i].b * inv_zq;
-          add += r > 0.0 ? r : 0.0;
+          add += fmax(residual(t[k][i].a * inv_zt, t[k][i].b * inv_zq), 0.0);
         }
       add = row_sum(add);
       if (tid % 16 == 0) buf0[c] += add;
     }
     __syncthreads();
-    // lists that did not hold them: the whole slice again, by the workgroup
-    for (int c = 0; some_over && c < p.n_fine; ++c) {
-      if (!overflowed(s_amb[c])) continue;   // (uniform)
-      double r[kFinePer], pm[kFinePer], sr = 0.0, none = 0.0;
-      eval(c, r, pm);
+    if (__ballot(flags & 2)) {   // lists that did not hold them: the whole slice again, by the workgroup
+      for (int c = 0; c < p.n_fine; ++c) {
+        if (!overflowed(s_amb[c])) continue;   // (uniform)
+        double r[kOwn], pm[kOwn], sr = 0.0;
+        eval(c, r, pm);
 #pragma unroll
-      for (int e = 0; e < kFinePer; ++e) sr += r[e];
-      block_sum2(sr, none);
-      if (tid == 0) buf0[c] = sr;
-    }
-    __syncthreads();
-  }
-  // total residual mass; without mass (rounding only) the draw is from p_n itself
-  double S = 0.0, Sp = 0.0;
-#pragma unroll
-  for (int j = 0; j < kTerms; ++j) {
-    const int c = tid + kThreads * j;
-    if (c < p.n_fine) S += buf0[c], Sp += buf1[c];
-  }
-  block_sum2(S, Sp);
-  int mode = 0;
-  const double *buf = buf0;
-  if (!(S > 0.0)) {   // uniform
-    mode = 1;
-    S = Sp;
-    buf = buf1;
-  }
-  const double thr = u * S;
-  if (wave == 0) {
-    // slice in which the running sum (buf still holds the slice sums) first exceeds thr; the last slice with mass
-    // if rounding hides the crossing.  Lane j owns `per` consecutive slices; an exclusive scan over the lanes gives
-    // the mass before its first one.
-    const int per = (p.n_fine + 63) / 64;
-    const int c0 = min(p.n_fine, lane * per), c1 = min(p.n_fine, c0 + per);
-    double own = 0.0;
-    for (int c = c0; c < c1; ++c) own += buf[c];
-    double incl = own;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const double up = __shfl_up(incl, off);
-      if (lane >= off) incl += up;
-    }
-    const double prev = __shfl_up(incl, 1);
-    double acc = lane ? prev : 0.0;
-    int cross = INT_MAX, last = -1;
-    double before = 0.0, before_last = 0.0;
-    for (int c = c0; c < c1; ++c) {
-      const double r = buf[c];
-      if (r > 0.0) last = c, before_last = acc;
-      if (cross == INT_MAX && acc + r > thr) cross = c, before = acc;
-      acc += r;
-    }
-    const uint64_t hit = __ballot(cross != INT_MAX), has = __ballot(last >= 0);
-    int cs = 0;
-    double bef = 0.0;
-    if (hit) {
-      const int src = __ffsll((unsigned long long)hit) - 1;
-      cs = __shfl(cross, src);
-      bef = __shfl(before, src);
-    } else if (has) {
-      const int src = 63 - __clzll((long long)has);
-      cs = __shfl(last, src);
-      bef = __shfl(before_last, src);
-    }
-    if (lane == 0) s_before = bef, s_slice = cs, s_lane = INT_MAX, s_last_lane = -1;
-  }
-  __syncthreads();
-  const int cs = s_slice;
-  // lane of that slice whose 8 tokens contain the crossing: inclusive scan of the lanes' sums
-  double mass[kFinePer], mine = 0.0;
-  {
-    double r[kFinePer], pm[kFinePer];
-    eval(cs, r, pm);
-#pragma unroll
-    for (int e = 0; e < kFinePer; ++e) {
-      mass[e] = mode ? pm[e] : r[e];
-      mine += mass[e];
-    }
-  }
-  double incl = mine;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const double up = __shfl_up(incl, off);
-    if (lane >= off) incl += up;
-  }
-  if (lane == 63) wave_tot[wave] = incl;
-  __syncthreads();
-  double base = s_before;
-  for (int w = 0; w < wave; ++w) base += wave_tot[w];
-  const double hi = base + incl, lo = hi - mine;
-  if (mine > 0.0) {
-    atomicMax(&s_last_lane, tid);
-    if (hi > thr && !(lo > thr)) atomicMin(&s_lane, tid);
-  }
-  __syncthreads();
-  const int pick_lane = s_lane != INT_MAX ? s_lane : s_last_lane;
-  if (tid == pick_lane) {
-    const int v0 = cs * kFine + tid * kFinePer;
-    double run = lo;
-    int tok = -1, last = -1;
-#pragma unroll
-    for (int e = 0; e < kFinePer; ++e) {
-      run += mass[e];
-      if (mass[e] > 0.0) {
-        last = v0 + e;
-        if (tok < 0 && run > thr) tok = v0 + e;
+        for (int e = 0; e < kOwn; ++e) sr += r[e];
+        sr = wave_sum(sr);
+        if (lane == 0) s_sum[0][wave] = sr;
+        __syncthreads();
+        sr = sum_of_waves<kW>(s_sum[0]);
+        if (tid == 0) buf0[c] = sr;
+        __syncthreads();
       }
     }
-    p.next_token[nb] = tok >= 0 ? tok : last;
+  }
+  // The slice in which the running sum first exceeds u times the total residual mass (the last slice with mass if rounding
+  // hides the crossing), the lane of that slice whose tokens contain the crossing, the token.  Without mass (rounding only:
+  // in the sums, or in the chosen slice's tokens) the draw is from p_n itself.
+  for (int mode = 0; mode < 2; ++mode) {
+    const double *buf = mode ? buf1 : buf0;
+    double own[kTerms], sum = 0.0;
+#pragma unroll
+    for (int j = 0; j < kTerms; ++j) {
+      const int c = tid * kTerms + j;
+      own[j] = c < p.n_fine ? buf[c] : 0.0;
+      sum += own[j];
+    }
+    Crossing<kW> slices;
+    slices.find(sum, u, 0.0, false, 0.0, s_tot);
+    if (!(slices.total > 0.0) && mode == 0) {   // (uniform)
+      __syncthreads();
+      continue;
+    }
+    if (tid == (slices.lane < 0 ? 0 : slices.lane)) {
+      double acc = slices.excl, before = acc;
+      int cs = tid * kTerms;
+      bool found = false;
+#pragma unroll
+      for (int j = 0; j < kTerms; ++j) {
+        if (!found && own[j] > 0.0) cs = tid * kTerms + j, before = acc, found = acc + own[j] > slices.thr;
+        acc += own[j];
+      }
+      s_slice = cs;
+      s_before = before;
+    }
+    __syncthreads();
+    const int cs = s_slice;
+    double mass[kOwn], mine = 0.0;
+    {
+      double r[kOwn], pm[kOwn];
+      eval(cs, r, pm);
+#pragma unroll
+      for (int e = 0; e < kOwn; ++e) {
+        mass[e] = mode ? pm[e] : r[e];
+        mine += mass[e];
+      }
+    }
+    Crossing<kW> lanes;
+    lanes.find(mine, u, s_before, true, slices.total, s_tot);
+    if (lanes.lane < 0) {   // (uniform)
+      __syncthreads();
+      continue;
+    }
+    if (tid == lanes.lane) {
+      const int v0 = cs * kFine + tid * kOwn;
+      double run = lanes.excl;
+      int tok = -1, last = -1;
+#pragma unroll
+      for (int e = 0; e < kOwn; ++e) {
+        run += mass[e];
+        if (mass[e] > 0.0) {
+          last = v0 + e;
+          if (tok < 0 && run > lanes.thr) tok = v0 + e;
+        }
+      }
+      p.next_token[nb] = tok >= 0 ? tok : last;
+    }
+    break;
   }
 }
 
@@ -1662,8 +1999,11 @@ hipError_t launch_typed(const AcceptParams &p, hipStream_t stream) {
   if (p.warp_key) {
     ProfileScope scope(SLOT_ACCEPT_WARP, stream);
     if (p.top_p < 1.0f && !(p.top_k > 0 && p.top_k < p.V)) {   // top-p alone needs every target row's whole mass
-      hipLaunchKernelGGL(accept_rowz_kernel<BF16>, dim3((p.n_fine + kRowzGroup - 1) / kRowzGroup, p.NB * (p.K + 1)),
-                         dim3(kThreads), 0, stream, p);
+      const dim3 grid((p.n_fine + rowz_group(p) - 1) / rowz_group(p), p.NB * (p.K + 1));
+      if (BF16 && p.exp_tab)
+        hipLaunchKernelGGL((accept_rowz_kernel<BF16, BF16>), grid, dim3(RowzShape<true>::kT), 0, stream, p);
+      else
+        hipLaunchKernelGGL((accept_rowz_kernel<BF16, false>), grid, dim3(kThreads), 0, stream, p);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
@@ -1673,13 +2013,19 @@ hipError_t launch_typed(const AcceptParams &p, hipStream_t stream) {
   }
   {
     ProfileScope scope(SLOT_ACCEPT_SAMPLE, stream);
-    hipLaunchKernelGGL(accept_sample_kernel<BF16>, dim3(p.n_fine, p.NB), dim3(kThreads), 0, stream, p);
+    if (BF16 && p.exp_tab)
+      hipLaunchKernelGGL((accept_sample_kernel<BF16, BF16>), dim3((p.n_fine + 1) / 2, p.NB), dim3(2 * kThreads), 0, stream, p);
+    else
+      hipLaunchKernelGGL((accept_sample_kernel<BF16, false>), dim3(p.n_fine, p.NB), dim3(kThreads), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   {
     ProfileScope scope(SLOT_ACCEPT_PICK, stream);
-    hipLaunchKernelGGL(accept_pick_kernel<BF16>, dim3(p.NB), dim3(kThreads), 0, stream, p);
+    if (p.n_fine >= 16)
+      hipLaunchKernelGGL((accept_pick_kernel<BF16, 512>), dim3(p.NB), dim3(512), 0, stream, p);
+    else
+      hipLaunchKernelGGL((accept_pick_kernel<BF16, 256>), dim3(p.NB), dim3(256), 0, stream, p);
     return hipGetLastError();
   }
 }
@@ -1722,9 +2068,13 @@ void accept_carve_workspace(AcceptParams &p, void *ws) {
     p.amb = at;
     p.heads = at + slices * (kThreads / 64) * kAmb * sizeof(Doubt);
     p.amb_n = (uint32_t *)(p.heads + (size_t)p.NB * sizeof(BranchHead));
+    // the table ends the space, out of the way of both kinds of lists (64 slices leave 64 KiB behind the lists in doubt)
+    const bool tab = p.bf16 && slices >= 64 && p.inv_temp <= 1.0 / 0.11;
+    p.exp_tab = tab ? (double *)(at + lists_bytes(p.NB, p.n_fine) - kTab * sizeof(double)) : nullptr;
     // the candidate segments of a call with top-p alone share the space: equal parts, 16-byte aligned, none if too small
-    const size_t groups = (size_t)(p.K + 1) * ((p.n_fine + kRowzGroup - 1) / kRowzGroup);
-    const size_t bytes = ((size_t)p.n_fine * kThreads * 2 * sizeof(double) / groups) & ~(size_t)15;
+    const size_t groups = (size_t)p.NB * (p.K + 1) * ((p.n_fine + rowz_group(p) - 1) / rowz_group(p));
+    const size_t space = slices * kThreads * 2 * sizeof(double) - (tab ? kTab * sizeof(double) : 0);
+    const size_t bytes = (space / groups) & ~(size_t)15;
     p.cand = at;
     p.cand_bytes = bytes >= 64 ? (int)bytes : 0;
   }

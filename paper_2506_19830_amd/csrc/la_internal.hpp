@@ -149,6 +149,7 @@ struct AcceptParams {
   uint8_t *amb;                // [NB, n_fine, 4, 48] masses of the tokens in doubt
   uint32_t *amb_n;             // [NB, n_fine] their number, a byte per wavefront of the slice's workgroup
   uint8_t *heads;              // [NB] row maxima and fp32 masses of the resampling rows
+  double *exp_tab;             // exp(x / T) of the bf16 logits, or null (see accept.hip)
   uint8_t *cand;               // top-p alone: candidate segments of every target row, in the space of the lists above
   int cand_bytes;              // size of one segment (0: none)
   // top-k / top-p warping of the target rows (off: top_k == 0 and top_p >= 1)
