@@ -1196,8 +1196,9 @@ __global__ __launch_bounds__(RowzShape<TAB>::kT, (TAB ? 6 : 1)) void accept_rowz
 // and no other does.
 // bf16 rows have few distinct values between the listed tokens' smallest and the row maximum (128 an octave): the tokens
 // are counted per value, and the threshold is read off the running mass over the values in descending order
-// (warp_top_p_bins: 14.7 -> 7.8 us at 54 rows of 152064, T 0.6, top_p 0.95, and no limit on the list's length: 24 rows at
-// T 1.0, which list 26000 tokens each and went the long way, take 36 instead of 214 us for the call).  Where the list spans more values, and for fp32 rows, it is found from the top bits down, two bits per round, the fp64 masses of a lane's keys in
+// (warp_top_p_bins: 14.7 -> 7.8 us at 54 rows of 152064, T 0.6, top_p 0.95; and the list may be of any length: a call with
+// 15 rows at T 1.0, whose lists were too long for the form below, takes 36 instead of 214 us).  Where the list spans more
+// values, and for fp32 rows, it is found from the top bits down, two bits per round, the fp64 masses of a lane's keys in
 // registers and three sums per round; every sum runs in a fixed order.  Bound by its chain of loads, barriers and
 // rounds, 54 workgroups on the chip: 44.3 -> 14.6 us at 54 rows of 152064 (T 0.6, top_p 0.95) against two passes of a
 // workgroup over its row and a sort; with the sums through LDS shuffles it was 21.4 us.  false: a segment is incomplete, the list is
