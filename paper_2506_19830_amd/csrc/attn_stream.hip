@@ -926,10 +926,22 @@ __global__ __launch_bounds__(64 * kWaves) void attn_stream_kernel(const AttnPara
 //                 of key block 0; the others 16 / 32 rows on)
 // KEEP (unmasked tiles only): the base is never moved and O never rescaled, as in stream_tile_fast and for its
 // reason; `give_up` is the workgroup's flag.
-template <int MASK, bool KEEP = false>
+// HOLD (with KEEP; the 8 x 1 shape, whose registers allow it): the base comes from stream_tile16_first, the accumulators'
+// start values from held->c_init, 16 registers that stay instead of 16 moves per tile, and the largest block sum is kept
+// for a test behind the loop.  So nothing in the tile branches: the tests, with a store of the flag behind them, cut it
+// into pieces the compiler schedules one by one, with a full wait for the fragments in flight at each cut.  Measured: four
+// requests of 81920 keys, 3072 rows x 8 kv heads 1012 -> 967 us, two of 24219 keys, 1104 rows x 8 kv heads 158 -> 145 us;
+// the two-slice shape and the fp8 ones, hand-scheduled around the cuts, stayed within a percent and lost 1 to 3 % on the
+// shortest calls (the base is a chain of its own there), so they keep the other form.
+struct Held {
+  f32x16 c_init;
+  float largest_sum;
+};
+template <int MASK, bool KEEP = false, bool HOLD = false>
 __device__ __forceinline__ void stream_tile16(const uint8_t *kt, RowState<1> &st, int koff0,
                                               const int (&voff)[2][4], int lh, int first, int limit,
-                                              int32_t *give_up = nullptr) {
+                                              int32_t *give_up = nullptr, Held *held = nullptr) {
+  static_assert(!HOLD || KEEP, "start values that stay belong to a base that stays");
   static_assert(!KEEP || MASK == MASK_NONE, "only unmasked tiles keep their base");
   using G = Geo<false>;
   const uint8_t *vt = kt + G::kHalf;
@@ -962,8 +974,12 @@ __device__ __forceinline__ void stream_tile16(const uint8_t *kt, RowState<1> &st
   uint32_t p0[1][8], p1[1][8];
   float sum0[1], sum1[1], mt[1], alpha[1], off[1];
   {
-    const float nb = kFastable ? -st.base[0] : 0.f;
-    s0[0] = f32x16{nb, nb, nb, nb, nb, nb, nb, nb, nb, nb, nb, nb, nb, nb, nb, nb};
+    if constexpr (HOLD) {
+      s0[0] = held->c_init;
+    } else {
+      const float nb = kFastable ? -st.base[0] : 0.f;
+      s0[0] = f32x16{nb, nb, nb, nb, nb, nb, nb, nb, nb, nb, nb, nb, nb, nb, nb, nb};
+    }
     s1[0] = s0[0];
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
@@ -973,6 +989,17 @@ __device__ __forceinline__ void stream_tile16(const uint8_t *kt, RowState<1> &st
       s0[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0, st.qf[0][t], s0[0], 0, 0, 0);
       s1[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1, st.qf[0][t], s1[0], 0, 0, 0);
     }
+  }
+  if constexpr (HOLD) {
+    block_probs<1, true>(s0, 1.f, off, p0, sum0);
+    st.l_run[0] += sum0[0];
+    pv(0, p0);
+    __builtin_amdgcn_sched_barrier(0);
+    block_probs<1, true>(s1, 1.f, off, p1, sum1);
+    held->largest_sum = fmaxf(held->largest_sum, fmaxf(sum0[0], sum1[0]));
+    st.l_run[0] += sum1[0];
+    pv(1, p1);
+    return;
   }
   if constexpr (KEEP) {
     block_probs<1, true>(s0, 1.f, off, p0, sum0);
@@ -1021,6 +1048,22 @@ __device__ __forceinline__ void stream_tile16(const uint8_t *kt, RowState<1> &st
   if (raise0 || raise1) st.base[0] = (st.m_run[0] == -INFINITY) ? 0.f : st.m_run[0];  // base == running maximum
   st.l_run[0] += sum1[0];
   pv(1, p1);
+}
+
+// Before a wavefront's first tile of the HOLD form: its base, the row maximum over the tile's first key block rounded up to
+// an integer (the weights that later combine the chunks are then exact powers of two).
+__device__ __forceinline__ void stream_tile16_first(const uint8_t *kt, RowState<1> &st, int koff0, Held &held) {
+  f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < 8; ++t)
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(kt + (koff0 ^ (32 * t))), st.qf[0][t], s, 0, 0, 0);
+  float m = s[0];
+#pragma unroll
+  for (int j = 1; j < 16; ++j) m = fmaxf(m, s[j]);
+  m = ceilf(xhalf_max(m));
+  st.m_run[0] = m, st.base[0] = m;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) held.c_init[j] = -m;
 }
 
 // The second attempt's form of the tile (see stream_tile_lean): one key block after the other, not unrolled.
@@ -1199,14 +1242,20 @@ __device__ __forceinline__ bool stream16_chunk(const AttnParams &p, uint8_t *lds
   }
 
   const bool active = r0 + rb * 32 < p.R;
+  constexpr bool kHold = KSL == 1;
+  Held held;
+  held.largest_sum = 0.f;
   int step = 0;
   if constexpr (!GENERAL) {  // the steps all of whose tiles are full prefix tiles, in a loop of their own
     for (; step < n_full_steps; ++step) {
       wait_later<IPW, NST - 2>(min(n_steps - 1, step + NST - 2) - step);
       __builtin_amdgcn_s_barrier();
       if (step + NST - 1 < n_steps) issue(step + NST - 1);
-      if (active)
-        stream_tile16<MASK_NONE, true>(lds + (step % NST) * kStepBytes + ks * G::kTile, st, koff0, voff, lh, 0, 0, give_up);
+      if (active) {
+        const uint8_t *kt = lds + (step % NST) * kStepBytes + ks * G::kTile;
+        if (kHold && step == 0) stream_tile16_first(kt, st, koff0, held);
+        stream_tile16<MASK_NONE, true, kHold>(kt, st, koff0, voff, lh, 0, 0, give_up, &held);
+      }
     }
   }
   int row_vis = 0;  // nested form: chain tokens the row's branch sees
@@ -1251,6 +1300,7 @@ __device__ __forceinline__ bool stream16_chunk(const AttnParams &p, uint8_t *lds
   }
   wait_vmcnt<0>();  // no direct load may still be on its way to LDS when the workgroup gives its LDS back
   if constexpr (!GENERAL) {
+    if (kHold && !(held.largest_sum <= kTrigger)) *(volatile int32_t *)give_up = 1;
     __syncthreads();  // every wavefront's flag store has landed before anyone reads the flag
     if (__builtin_expect(*(volatile int32_t *)give_up != 0, 0)) return false;
   }
