@@ -363,3 +363,25 @@ def test_product_package_does_not_import_the_oracle():
         if f.suffix in (".py", ".hip", ".hpp", ".h", ".cpp"):
             text = f.read_text()
             assert "import oracle" not in text and "from oracle" not in text and "la_oracle" not in text, f
+
+
+@pytest.mark.parametrize("lens,gamma,L,hq,hkv,kv,shape,chunk,total", [
+    ((5120,), 1, 4, 16, 4, "fp8_e4m3", 3, 192, 27),
+    ((6531,), 1, 4, 16, 4, "bf16", 7, 192, 35),
+    ((131072,), 1, 1, 8, 8, "bf16", 7, 4096, 32),
+    ((1,), 1, 1, 8, 8, "bf16", 7, 64, 1),
+    ((577, 576), 8, 64, 40, 8, "bf16", 6, 640, 2),
+    ((3553, 1018, 7148), 1, 5, 40, 8, "fp8_e4m3", 3, 448, 27),
+    ((2476, 1833), 1, 74, 40, 8, "fp8_e4m3", 4, 512, 9),
+    ((375, 856, 5016, 843, 2495, 420), 3, 8, 16, 4, "fp8_e4m3", 3, 448, 24),
+    ((700, 64, 0, 9000), 8, 48, 64, 8, "bf16", 6, 1856, 8),
+    ((24576, 8192, 16384), 6, 64, 40, 8, "fp8_e4m3", 1, 4096, 12),
+])
+def test_plan_is_the_cheapest_of_all_chunk_counts(lens, gamma, L, hq, hkv, kv, shape, chunk, total):
+    """The planner passes over chunk counts that round to a chunk length it has seen and stops at a lower bound of the
+    cost; the plans are those of a search that looks at every count up to 512 (computed with one)."""
+    desc = good_desc(num_requests=len(lens), num_q_heads=hq, num_kv_heads=hkv, gamma=gamma, branch_len=L, block_size=16,
+                     max_blocks_per_request=(max(lens) + 15) // 16, kv_dtype=kv, branch_kv_dtype=kv)
+    plan = B.la_verify_attention_plan(desc, list(lens))
+    assert (plan["kernel_shape"], plan["chunk_tokens"], plan["chunks_total"]) == (shape, chunk, total)
+
