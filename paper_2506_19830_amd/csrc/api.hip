@@ -264,13 +264,24 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, Attn
       const ShapeInfo si = shape_info(shape);
       skip_row_tiles |= stream_ok(si) && chunk_fits(max_chunk(si, last_short_tiles(si)));
     }
+  // fp8, at most 64 rows per KV head: of the streaming shapes only the one of 64 rows.  The others have wavefronts whose
+  // rows do not exist, and fewer key slices.  Their shorter step tempts the model to chunks of one tile, but over 40 flat
+  // calls of 8 to 64 rows and 305 to 29507 keys the 128-row shape took 1.0 to 1.38 of the time, 1.15 in the mean (28431 +
+  // 307 keys, 64 rows, two heads: 23.3 against 19.0 us), and no less at any chunk length asked for.  bf16 has no such line:
+  // there each of its two shapes is ahead in part of the range.
+  bool narrow = false;
+  if (d->kernel_shape == 0 && R <= 64)
+    for (int shape = attn_mfma_num_shapes(); shape < num_shapes(); ++shape) {
+      const ShapeInfo si = shape_info(shape);
+      narrow |= si.fp8 && si.tile_m == 64 && stream_ok(si) && chunk_fits(max_chunk(si, last_short_tiles(si)));
+    }
   double best_cost = 0.0;
   int best_len = 0, best_shape = -1, best_short = 0;
   const int64_t T = (max_p + 63) / 64;
   for (int shape = 0; shape < num_shapes(); ++shape) {
     if (d->kernel_shape > 0 && shape != d->kernel_shape - 1) continue;
     const ShapeInfo si = shape_info(shape);
-    if (si.stream ? !stream_ok(si) : skip_row_tiles) continue;
+    if (si.stream ? !stream_ok(si) || (narrow && si.tile_m > 64) : skip_row_tiles) continue;
     const int64_t base_wgs = (int64_t)d->num_kv_heads * ((R + si.tile_m - 1) / si.tile_m);
     const int last_short = last_short_tiles(si);
     const int64_t slots = (int64_t)num_cus() * si.per_cu;

@@ -385,3 +385,15 @@ def test_plan_is_the_cheapest_of_all_chunk_counts(lens, gamma, L, hq, hkv, kv, s
     plan = B.la_verify_attention_plan(desc, list(lens))
     assert (plan["kernel_shape"], plan["chunk_tokens"], plan["chunks_total"]) == (shape, chunk, total)
 
+
+@pytest.mark.parametrize("lens,gamma,L,hq,hkv", [
+    ((822,), 1, 6, 32, 8), ((1,), 1, 1, 8, 8), ((28431, 307), 8, 1, 16, 2), ((2585,), 1, 64, 2, 2),
+])
+def test_fp8_calls_of_one_64_row_tile(lens, gamma, L, hq, hkv):
+    """At most 64 rows per KV head run on the streaming shape of 64 rows; with a chunk length asked for on no wider
+    streaming shape; a forced shape is taken as before."""
+    kw = dict(num_requests=len(lens), num_q_heads=hq, num_kv_heads=hkv, gamma=gamma, branch_len=L, block_size=16,
+              max_blocks_per_request=(max(lens) + 15) // 16, kv_dtype="fp8_e4m3", branch_kv_dtype="fp8_e4m3")
+    shape = lambda **k: B.la_verify_attention_plan(good_desc(**kw, **k), list(lens))["kernel_shape"]
+    assert shape() == 3 and shape(kernel_shape=4) == 4
+    assert shape(kv_split_tokens=64) not in (4, 5)
