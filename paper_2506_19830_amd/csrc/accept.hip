@@ -22,9 +22,10 @@
 //           tokens are larger; keep v iff the mass of the larger kept tokens is below top_p * Z_k), so equal
 //           logits are never split.  With top-p alone the threshold is searched among the candidates rowz listed.
 //           With a small k, or where those fall short, a bound taken from the lanes' largest logits leaves a short
-//           list of candidate tokens, which is sorted and walked in descending order; otherwise (and whenever such a list overflows or falls short) two radix selections over an
-//           order-preserving key of the logit: the k-th largest by count, then among those the value at which
-//           the descending cumulative mass reaches top_p of the kept mass.  sample / pick then use
+//           list of candidate tokens, which is sorted and walked in descending order; otherwise (and whenever such
+//           a list overflows or falls short) two radix selections over an order-preserving key of the logit: the
+//           k-th largest by count, then among those the value at which the descending cumulative mass reaches
+//           top_p of the kept mass.  sample / pick then use
 //           p(v) = [key(v) >= key_min] * exp((x_v - max)/T) / Z_kept for the target rows.
 //   rowz    (only with top-p alone) grid (fine-slice groups, target rows): the fp64 mass of every target row in
 //           fine slices, which warp folds: top-p's threshold is a share of the whole row's mass; and the tokens
@@ -1083,8 +1084,8 @@ __host__ __device__ inline int rowz_group(const AcceptParams &p) {
 // the same holds for eight times that mass (normal logits, V = 152064, 31 to 8600 tokens kept: from 24 times on).  The
 // bound taken is that of eight times the mass, from the fp32 statistics; whether the listed tokens hold top_p Z is
 // checked exactly by the warp kernel.  (Normal logits of deviation 3, T = 0.6, top_p = 0.95: 2900 listed, 350 kept.)
-// A workgroup writes its tokens' keys in token order to a segment of p.cand, whose space the per-lane sums of the
-// resampling path use later; the warp kernel finds the threshold among them without reading the row.  A segment that
+// A workgroup writes its tokens' keys in token order to a segment of p.cand, whose space the lists of the resampling
+// path use later; the warp kernel finds the threshold among them without reading the row.  A segment that
 // does not fit says so by its count, and the row takes the long way.
 struct CandHeader {
   uint32_t n, pad[3];   // tokens at or above the bound (more than fit: the segment is not complete)
@@ -1484,8 +1485,9 @@ __global__ __launch_bounds__(kWarpThreads) void accept_warp_kernel(const AcceptP
 }
 
 // ---------------------------------------------------------------------------------------------
-// sample: grid (n_fine slices, one or two to a workgroup; NB).  Accepted length of the branch (every workgroup derives it; slice 0 publishes it), then
-// what this slice contributes to the normalisers of the resampling rows and to the residual.
+// sample: grid (n_fine slices, one or two to a workgroup; NB).  Accepted length of the branch (every workgroup derives
+// it; slice 0 publishes it), then what this slice contributes to the normalisers of the resampling rows and to the
+// residual.
 //
 // The residual max(0, a/Zt - b/Zq) of a token (a, b its unnormalised masses in the target and the draft row) needs both
 // normalisers, which all workgroups of the branch contribute to, but its sign nearly never does: Zt/Zq is known from the
