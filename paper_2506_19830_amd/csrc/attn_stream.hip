@@ -926,13 +926,16 @@ __global__ __launch_bounds__(64 * kWaves) void attn_stream_kernel(const AttnPara
 //                 of key block 0; the others 16 / 32 rows on)
 // KEEP (unmasked tiles only): the base is never moved and O never rescaled, as in stream_tile_fast and for its
 // reason; `give_up` is the workgroup's flag.
-// HOLD (with KEEP; the 8 x 1 shape, whose registers allow it): the base comes from stream_tile16_first, the accumulators'
-// start values from held->c_init, 16 registers that stay instead of 16 moves per tile, and the largest block sum is kept
-// for a test behind the loop.  So nothing in the tile branches: the tests, with a store of the flag behind them, cut it
-// into pieces the compiler schedules one by one, with a full wait for the fragments in flight at each cut.  Measured: four
-// requests of 81920 keys, 3072 rows x 8 kv heads 1012 -> 967 us, two of 24219 keys, 1104 rows x 8 kv heads 158 -> 145 us;
-// the two-slice shape and the fp8 ones, hand-scheduled around the cuts, stayed within a percent and lost 1 to 3 % on the
-// shortest calls (the base is a chain of its own there), so they keep the other form.
+// HOLD (with KEEP; the 8 x 1 shape, whose registers allow it; from a wavefront's second tile on, the first one sets the
+// base): the accumulators' start values come from held->c_init, 16 registers that stay instead of 16 moves per tile, and
+// the largest block sum is kept for a test behind the loop.  So nothing in the tile branches: the tests, with a store of the
+// flag behind them, cut it into pieces the compiler schedules one by one, with a full wait for the fragments in flight at
+// each cut.  Measured: four requests of 81920 keys, 3072 rows x 8 kv heads 999 -> 952 us, two of 24219 keys, 1104 rows x 8
+// kv heads 231 -> 219 us; the two-slice shape and the fp8 ones, hand-scheduled around the cuts, stayed within a percent and
+// lost 1 to 3 % on the shortest calls, so they keep the other form.
+// The base is the exact maximum of the first tile, which gives the row's largest key of that tile the probability 2^0: a row
+// that one early key dominates comes out as that key's V.  (Any other base rounds that probability to bf16 for P V and not
+// for the sum: a part in 10^3 of such a row.)
 struct Held {
   f32x16 c_init;
   float largest_sum;
@@ -991,6 +994,15 @@ __device__ __forceinline__ void stream_tile16(const uint8_t *kt, RowState<1> &st
     }
   }
   if constexpr (HOLD) {
+    // K fragments on their way: two steps ahead of the MFMAs (left to itself the compiler waits for each pair at its use:
+    // 976 against 952 us at the four requests)
+    __builtin_amdgcn_sched_group_barrier(kSgDsRead, 4, 0);
+#pragma unroll
+    for (int i = 0; i < 12; ++i) {
+      __builtin_amdgcn_sched_group_barrier(kSgMfma, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(kSgMfma, 4, 0);
     block_probs<1, true>(s0, 1.f, off, p0, sum0);
     st.l_run[0] += sum0[0];
     pv(0, p0);
@@ -1048,22 +1060,6 @@ __device__ __forceinline__ void stream_tile16(const uint8_t *kt, RowState<1> &st
   if (raise0 || raise1) st.base[0] = (st.m_run[0] == -INFINITY) ? 0.f : st.m_run[0];  // base == running maximum
   st.l_run[0] += sum1[0];
   pv(1, p1);
-}
-
-// Before a wavefront's first tile of the HOLD form: its base, the row maximum over the tile's first key block rounded up to
-// an integer (the weights that later combine the chunks are then exact powers of two).
-__device__ __forceinline__ void stream_tile16_first(const uint8_t *kt, RowState<1> &st, int koff0, Held &held) {
-  f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int t = 0; t < 8; ++t)
-    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(kt + (koff0 ^ (32 * t))), st.qf[0][t], s, 0, 0, 0);
-  float m = s[0];
-#pragma unroll
-  for (int j = 1; j < 16; ++j) m = fmaxf(m, s[j]);
-  m = ceilf(xhalf_max(m));
-  st.m_run[0] = m, st.base[0] = m;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) held.c_init[j] = -m;
 }
 
 // The second attempt's form of the tile (see stream_tile_lean): one key block after the other, not unrolled.
@@ -1246,16 +1242,23 @@ __device__ __forceinline__ bool stream16_chunk(const AttnParams &p, uint8_t *lds
   Held held;
   held.largest_sum = 0.f;
   int step = 0;
+  auto next_tile = [&]() __attribute__((always_inline)) {   // the step's tile is in LDS, the one NST - 1 on requested
+    wait_later<IPW, NST - 2>(min(n_steps - 1, step + NST - 2) - step);
+    __builtin_amdgcn_s_barrier();
+    if (step + NST - 1 < n_steps) issue(step + NST - 1);
+    return lds + (step % NST) * kStepBytes + ks * G::kTile;
+  };
   if constexpr (!GENERAL) {  // the steps all of whose tiles are full prefix tiles, in a loop of their own
+    if (kHold && n_full_steps > 0) {
+      const uint8_t *kt = next_tile();
+      if (active) stream_tile16<MASK_NONE, true>(kt, st, koff0, voff, lh, 0, 0, give_up);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) held.c_init[j] = -st.base[0];
+      ++step;
+    }
     for (; step < n_full_steps; ++step) {
-      wait_later<IPW, NST - 2>(min(n_steps - 1, step + NST - 2) - step);
-      __builtin_amdgcn_s_barrier();
-      if (step + NST - 1 < n_steps) issue(step + NST - 1);
-      if (active) {
-        const uint8_t *kt = lds + (step % NST) * kStepBytes + ks * G::kTile;
-        if (kHold && step == 0) stream_tile16_first(kt, st, koff0, held);
-        stream_tile16<MASK_NONE, true, kHold>(kt, st, koff0, voff, lh, 0, 0, give_up, &held);
-      }
+      const uint8_t *kt = next_tile();
+      if (active) stream_tile16<MASK_NONE, true, kHold>(kt, st, koff0, voff, lh, 0, 0, give_up, &held);
     }
   }
   int row_vis = 0;  // nested form: chain tokens the row's branch sees
@@ -1300,6 +1303,8 @@ __device__ __forceinline__ bool stream16_chunk(const AttnParams &p, uint8_t *lds
   }
   wait_vmcnt<0>();  // no direct load may still be on its way to LDS when the workgroup gives its LDS back
   if constexpr (!GENERAL) {
+    // (A sum that is no number does not raise the flag for certain: the maximum may drop it, and the build lets the compiler
+    // assume there are none.  Finite Q and K give one only where scores leave the range of fp32.)
     if (kHold && !(held.largest_sum <= kTrigger)) *(volatile int32_t *)give_up = 1;
     __syncthreads();  // every wavefront's flag store has landed before anyone reads the flag
     if (__builtin_expect(*(volatile int32_t *)give_up != 0, 0)) return false;

@@ -112,3 +112,32 @@ def test_many_requests(oracle, requests, kv):
         check_full(oracle, case, TOL_LOWP, split)
     check_nested(oracle, case, 70, TOL_LOWP, None, 128)
     check_tree(oracle, case, 2, 2, 9, TOL_LOWP, 128)
+
+
+def sink_inputs(case):
+    """Rows whose first key's score lies 19 to 22 nats above N(0, 2), the scores of the others."""
+    inp = W.make_attention_inputs(case)
+    rng = np.random.default_rng(case.seed)
+    u = rng.choice([-1.0, 1.0], size=(case.Hkv, case.D)) / np.sqrt(case.D)
+    q = rng.standard_normal((case.B, case.gamma, case.L, case.Hkv, case.Hq // case.Hkv, case.D))
+    q -= (q * u[:, None]).sum(-1, keepdims=True) * u[:, None]
+    q += np.sqrt(case.D) * rng.uniform(0.95, 1.1, size=q.shape[:-1] + (1,)) * u[:, None]
+    inp["q"] = W.encode(q.reshape(inp["q"].shape).astype(np.float32), "bf16")
+    inp["k_cache"][0, :, 0] = W.encode((20.0 * u).astype(np.float32), "bf16")
+    return inp
+
+
+@pytest.mark.parametrize("split", [0, 192])
+@pytest.mark.parametrize("kernel_shape", [6, 7])
+def test_first_key_holds_the_row(oracle, kernel_shape, split, monkeypatch):
+    """A first token that draws all attention: as the maximum of the first tile its probability is 2^0, which bf16 holds, so
+    the output is its V to fp32 accuracy.  The other 760 keys weigh 760 e^(1 - 19) = 1.2e-5 together, and their scores and
+    probabilities are right to a part in a hundred (Q times the score scale and the probabilities rounded to bf16)."""
+    from gpu_util import row_errors, run_attention
+    from test_gpu_attention import oracle_attention
+    monkeypatch.setattr("gpu_util.KERNEL_SHAPE", kernel_shape)
+    case = make_case("bf16", (700,), 3, 20, 16, 2, False, seed=420, out="f32")
+    inp = sink_inputs(case)
+    got, _ = run_attention(case, inp, split)
+    ref, _ = oracle_attention(oracle, case, inp)
+    assert row_errors(got, ref).max() <= 1e-5
