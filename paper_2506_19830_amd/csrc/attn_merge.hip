@@ -6,9 +6,9 @@
 //     M = max_s m_s,   w_s = 2^(m_s - M),   O = sum_s w_s O_s / sum_s w_s l_s,
 //     lse = ln2 * (M + log2 sum_s w_s l_s).
 // More than eight chunks: one wavefront owns one output row, lane s < n_s loads
-// (m_s, l_s), the maximum and the denominator are wavefront shuffle reductions,
-// the weights are then broadcast lane by lane while each lane accumulates its
-// D / 64 output columns.  Up to eight: D / 4 threads own a row (below).
+// (m_s, l_s), the maximum and the denominator are reductions over the lanes on
+// the vector ALU, the weights are then read lane by lane into scalar registers
+// while each lane accumulates its D / 64 output columns.  Up to eight: D / 4 threads own a row (below).
 #include "la_internal.hpp"
 
 namespace la {
@@ -42,12 +42,19 @@ __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, row_rotate<1>(v));
   return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
 }
+// (the halves and the rows first, then inside the rows: the order of a butterfly from lane ^ 32 down to lane ^ 1)
 __device__ __forceinline__ float wave_sum(float v) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  const auto halves = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const uint32_t h0 = halves[0], h1 = halves[1];
+  const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, h0) + __builtin_bit_cast(float, h1));
+  const auto rows = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+  const uint32_t r0 = rows[0], r1 = rows[1];
+  v = __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
   v += row_rotate<8>(v);
   v += row_rotate<4>(v);
   v += row_rotate<2>(v);
-  v += row_rotate<1>(v);
-  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+  return v + row_rotate<1>(v);
 }
 
 // kGroup: partial rows requested before the first is used.  Bound by the latency of the loads and what hangs on them:
