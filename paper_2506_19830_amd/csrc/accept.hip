@@ -1479,7 +1479,9 @@ __global__ __launch_bounds__(kWarpThreads) void accept_warp_kernel(const AcceptP
     if (!listed) zw = kept_mass<BF16>(row, p.V, mx_over_t, p.inv_temp, key_min, red, &s_slot);
   }
   if (tid == 0) {
-    p.warp_key[rw] = key_min;
+    // a row that keeps everything (the histogram's floor, 0) has the key of -inf: the keys below it decode to NaNs, which no
+    // logit compares above, and the kernels behind this one compare values
+    p.warp_key[rw] = max(key_min, order_key(-INFINITY));
     p.warp_z[rw] = zw;
   }
 }

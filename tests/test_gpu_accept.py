@@ -379,3 +379,24 @@ def test_accept_random_shapes(oracle, idx):
     case = random_accept_case(idx)
     print(f"  top_k={case.top_k} top_p={case.top_p} point_mass={case.point_mass}", flush=True)
     check(oracle, case)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_top_p_that_keeps_a_tail_of_tiny_masses(oracle, dtype):
+    """One token 28.5 above 299999 equal ones, which weigh 1.3e-7 of the row together, more than 1 - top_p = 6e-8: all are
+    kept, though none of them reaches the 2^-41 that the mass histogram counts in (it then keeps everything, by its lowest
+    key).  Drafts of the heavy token are accepted, drafts of the others rejected, and a draw can fall on the others."""
+    from gpu_util import compare_accept, run_accept
+    NB, K, V = 8, 2, 300000
+    case = W.AcceptCase("tail", NB, K, V, dtype, temperature=1.0, top_p=0.99999994, point_mass=True)
+    t = np.zeros((NB, K + 1, V), np.float32)
+    t[:, :, -1] = 28.5   # (last, so that a running sum meets the small masses first)
+    tok = np.full((NB, K), V - 1, np.int32)
+    tok[::2, 1] = 77
+    inp = {"target_logits": W.encode(t, dtype), "draft_logits": None, "draft_tokens": tok,
+           "u_accept": np.full((NB, K), 0.5, np.float32),
+           "u_sample": np.array([0.0, 1e-9, 2e-8, 5e-8, 9e-8, 1.2e-7, 0.3, 0.99999994], np.float32)}
+    got = run_accept(case, inp)
+    ref = oracle.spec_accept(**inp, logits_dtype=dtype, temperature=1.0, top_p=float(np.float32(0.99999994)))
+    assert set(ref["accepted_len"]) == {1, 2} and (ref["next_token"] < V - 1).sum() >= 5
+    assert compare_accept(got, ref) == (0, 0, 0), (got["next_token"], ref["next_token"])
