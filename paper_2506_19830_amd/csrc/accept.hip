@@ -1974,8 +1974,9 @@ __global__ __launch_bounds__(T) void accept_pick_kernel(const AcceptParams p) {
       }
       p.next_token[nb] = tok >= 0 ? tok : last;
     }
-    break;
+    return;
   }
+  if (tid == 0) p.next_token[nb] = 0;   // (a target row without a finite logit: any token, but an index all the same)
 }
 
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }

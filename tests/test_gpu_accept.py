@@ -400,3 +400,14 @@ def test_top_p_that_keeps_a_tail_of_tiny_masses(oracle, dtype):
     ref = oracle.spec_accept(**inp, logits_dtype=dtype, temperature=1.0, top_p=float(np.float32(0.99999994)))
     assert set(ref["accepted_len"]) == {1, 2} and (ref["next_token"] < V - 1).sum() >= 5
     assert compare_accept(got, ref) == (0, 0, 0), (got["next_token"], ref["next_token"])
+
+
+@pytest.mark.parametrize("V", [700, 40000])
+def test_a_row_without_a_finite_logit_writes_an_index(V):
+    """Undefined by contract (every row keeps a finite logit), but what is written is a token."""
+    from gpu_util import run_accept
+    case = W.AcceptCase("no_mass", 4, 2, V, "bf16")
+    inp = W.make_accept_inputs(case)
+    inp["target_logits"][:] = 0xFF80
+    got = run_accept(case, inp)
+    assert (got["next_token"] >= 0).all() and (got["next_token"] < V).all()
