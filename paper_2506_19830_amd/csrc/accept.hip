@@ -1431,7 +1431,7 @@ __device__ __forceinline__ bool warp_top_p_segments(const AcceptParams &p, int r
 
 template <bool BF16>
 __global__ __launch_bounds__(kWarpThreads) void accept_warp_kernel(const AcceptParams p) {
-  __shared__ double mass[kHist * kRep];               // the count histogram shares this storage
+  __shared__ alignas(16) double mass[kHist * kRep];   // the count histogram and the lists share this storage (16-byte accesses)
   uint32_t *cnt = (uint32_t *)mass;
   __shared__ uint32_t s_pick;
   __shared__ double s_above, s_slot;
