@@ -65,6 +65,13 @@ LA_API la_status la_calibrate_issue(int32_t mix, int32_t mix_second, int32_t wav
 LA_API la_status la_selftest_exp64(const double *y, double *out, size_t n, void *hip_stream);
 
 /* ------------------------------------------------------------------------- *
+ *  Self-test hook: whether la_spec_accept would look the fp64 masses of this
+ *  call's logits up in a table (1) or evaluate an exponential per token (0).
+ *  Host only.
+ * ------------------------------------------------------------------------- */
+LA_API la_status la_selftest_accept_table(const la_accept_desc *desc, int32_t *has_table);
+
+/* ------------------------------------------------------------------------- *
  *  Self-test hook for the streaming kernel shapes of an fp8 cache.  Their
  *  unmasked tiles never move the base their probabilities are formed against
  *  (Section 3.2's verification pass needs no such thing; it is this

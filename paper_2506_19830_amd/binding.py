@@ -32,7 +32,8 @@ EXPORTED_SYMBOLS = (
 )
 # what libla_verify_bench.so exports on top of those (la_verify_bench.h)
 BENCH_SYMBOLS = (
-    "la_calibrate_mfma", "la_calibrate_mfma_data", "la_calibrate_read", "la_calibrate_issue", "la_selftest_exp64", "la_selftest_second_attempt", "la_check_block_tables", "la_check_draft_tokens",
+    "la_calibrate_mfma", "la_calibrate_mfma_data", "la_calibrate_read", "la_calibrate_issue", "la_selftest_exp64",
+    "la_selftest_accept_table", "la_selftest_second_attempt", "la_check_block_tables", "la_check_draft_tokens",
     "la_profile_enable", "la_profile_select",
     "la_profile_collect", "la_profile_num_kernels", "la_profile_get", "la_profile_reset",
 )
@@ -357,6 +358,17 @@ def la_selftest_exp64(y, out) -> None:
     st = load("bench").la_selftest_exp64(_ptr(y), _ptr(out), ctypes.c_size_t(out.numel()), _stream())
     if st:
         raise LaError(st, "la_selftest_exp64")
+
+
+def la_selftest_accept_table(desc: la_accept_desc) -> bool:
+    """Whether ``la_spec_accept`` looks the masses of this call's logits up in a table (host only)."""
+    lib = load("bench")
+    out = ctypes.c_int32(-1)
+    lib.la_selftest_accept_table.restype = ctypes.c_int
+    st = lib.la_selftest_accept_table(ctypes.byref(desc), ctypes.byref(out))
+    if st:
+        raise LaError(st, "la_selftest_accept_table")
+    return bool(out.value)
 
 
 def la_selftest_second_attempt(on: bool) -> None:

@@ -194,13 +194,15 @@ __device__ __forceinline__ double mass64(float x, double mx_over_t, double inv_t
 //
 // The masses of such a row are in units of e^0, not of e^(max/T): nothing but their quotients leaves the call, and with
 // |max| / T up to 300 no sum overflows and a token that vanishes weighs e^-445 of the row at most.  A row beyond that keeps
-// the maximum as its unit and the exponential per token (mass_unit).  T below 0.11, where table entries leave the range
-// of a double, fp32 logits, and calls of a few slices, whose workspace has no room for it, have no table.
+// the maximum as its unit and the exponential per token (mass_unit).  fp32 logits, calls of a few slices, whose workspace has
+// no room for it, and temperatures below 0.11 have no table: its largest entry is e^(64/T), which leaves the range of a
+// double at T = 0.0902; at 0.11 it is e^582.
 // ---------------------------------------------------------------------------------------------
 constexpr int kTabLo = 115 * 128;               // bit pattern of 2^-12
 constexpr int kTabHalf = 18 * 128;              // up to 2^6
 constexpr int kTab = 2 * kTabHalf + 2;          // a zero behind the positive values, the negative ones, a zero behind those
 constexpr float kTabMaxExponent = 300.f;
+constexpr float kTabMinTemperature = 0.11f;     // (as the descriptor holds it)
 
 __device__ __forceinline__ double table_entry(int i, double inv_temp) {
   const int neg = i > kTabHalf, j = i - neg * (kTabHalf + 1);
@@ -2075,7 +2077,7 @@ void accept_carve_workspace(AcceptParams &p, void *ws) {
     p.heads = at + slices * (kThreads / 64) * kAmb * sizeof(Doubt);
     p.amb_n = (uint32_t *)(p.heads + (size_t)p.NB * sizeof(BranchHead));
     // the table ends the space, out of the way of both kinds of lists (64 slices leave 64 KiB behind the lists in doubt)
-    const bool tab = p.bf16 && slices >= 64 && p.inv_temp <= 1.0 / 0.11;
+    const bool tab = p.bf16 && slices >= 64 && p.inv_temp <= 1.0 / (double)kTabMinTemperature;
     p.exp_tab = tab ? (double *)(at + lists_bytes(p.NB, p.n_fine) - kTab * sizeof(double)) : nullptr;
     // the candidate segments of a call with top-p alone share the space: equal parts, 16-byte aligned, none if too small
     const size_t groups = (size_t)p.NB * (p.K + 1) * ((p.n_fine + rowz_group(p) - 1) / rowz_group(p));

@@ -76,6 +76,22 @@ la_status la_selftest_exp64(const double *y, double *out, size_t n, void *hip_st
   return launch_exp64_probe(y, out, n, (hipStream_t)hip_stream) == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
 }
 
+la_status la_selftest_accept_table(const la_accept_desc *desc, int32_t *has_table) {
+  size_t bytes = 0;
+  if (!has_table) return LA_ERR_INVALID_ARG;
+  const la_status st = la_spec_accept_workspace(desc, &bytes);   // validates the descriptor
+  if (st != LA_OK) return st;
+  AcceptParams p{};
+  p.bf16 = desc->logits_dtype == LA_BF16;
+  accept_workspace_bytes(desc->num_branches, desc->num_draft, desc->vocab, p.bf16, &p.n_chunks, &p.n_fine);
+  p.NB = desc->num_branches, p.K = desc->num_draft, p.V = desc->vocab;
+  p.inv_temp = 1.0 / (double)desc->temperature;
+  p.top_k = desc->top_k, p.top_p = desc->top_p;
+  accept_carve_workspace(p, (void *)(uintptr_t)256);   // (addresses only: nothing is read or written)
+  *has_table = p.exp_tab != nullptr;
+  return LA_OK;
+}
+
 la_status la_selftest_second_attempt(int on) {
   g_force_second_attempt = on != 0;
   return LA_OK;

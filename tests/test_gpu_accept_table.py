@@ -48,11 +48,39 @@ def make(case, kind):
                                                      (1.5, 30, 0.9)])
 def test_masses(oracle, V, kind, temperature, top_k, top_p):
     """14 branches of five slices: a table; the last slice nearly empty."""
-    if kind == "beyond" and temperature < 0.5:
-        pytest.skip("one token holds all but e^-100 of every row: what is left of a residual is rounding on every side")
     for point_mass in (False, True):
         case = W.AcceptCase(f"tab_{kind}", 14, 2, V, "bf16", temperature=temperature, top_k=top_k, top_p=top_p,
                             point_mass=point_mass, peak=6.0, seed=700 + V % 2)
+        inp = make(case, kind)
+        if kind == "beyond" and temperature < 0.5 and not point_mass:
+            # one token holds all but e^-100 of every row: what is left of a residual is rounding on every side.  So the
+            # drafts are accepted and the draw is from the bonus row.
+            t = W._decode_for_sampling(inp["target_logits"], "bf16")
+            inp["draft_tokens"] = t[:, :2].argmax(-1).astype(np.int32)
+            inp["u_accept"][:] = 0.0
+        check_inputs(oracle, case, inp)
+
+
+def has_table(case):
+    from paper_2506_19830_amd import binding as B
+    return B.la_selftest_accept_table(B.make_accept_desc(num_branches=case.NB, num_draft=case.K, vocab=case.V,
+                                                         logits_dtype=case.logits_dtype, temperature=case.temperature,
+                                                         top_k=case.top_k, top_p=case.top_p))
+
+
+COLDEST = float(np.float32(0.11))
+
+
+@pytest.mark.parametrize("temperature,table", [(COLDEST, True), (float(np.nextafter(np.float32(0.11), np.float32(0))), False),
+                                               (0.125, True)])
+@pytest.mark.parametrize("kind", ["plain", "tiny", "edges", "negative", "masked"])
+def test_coldest_table(oracle, kind, temperature, table):
+    """Temperatures around the lowest one with a table: entries up to e^+-582, and rows whose maximum is 300 T or more, which
+    keep it as their unit (8200 logits of deviation 3 reach 11, or 100 T; shifted by 100 and 400 they are beyond)."""
+    for point_mass, top_p in ((False, 1.0), (True, 0.9)):
+        case = W.AcceptCase(f"tab_cold_{kind}", 14, 2, 8200, "bf16", temperature=temperature, top_p=top_p,
+                            point_mass=point_mass, peak=6.0, seed=710)
+        assert has_table(case) == table
         check_inputs(oracle, case, make(case, kind))
 
 
@@ -61,6 +89,7 @@ def test_smallest_calls_with_a_table(oracle, NB, V):
     """64 slices in all, and one less; odd numbers of slices per branch."""
     for top_p in (1.0, 0.9):
         case = W.AcceptCase("tab_small", NB, 2, V, "bf16", temperature=0.7, top_p=top_p, seed=800 + NB)
+        assert has_table(case) == (NB * ((V + 2047) // 2048) >= 64)
         check_inputs(oracle, case, make(case, "plain"))
 
 
