@@ -85,6 +85,16 @@ LA_API la_status la_selftest_accept_table(const la_accept_desc *desc, int32_t *h
 LA_API la_status la_selftest_second_attempt(int on);
 
 /* ------------------------------------------------------------------------- *
+ *  Self-test hook for the planner of the head-dimension-128 kernels.  It
+ *  passes over numbers of chunks that cannot give another plan than one it
+ *  has modelled, and stops where a lower bound of the modelled time says that
+ *  none behind can win.  With on != 0 it models every number of chunks up to
+ *  its limit, so that a test can compare the plans.  Process-wide, host side
+ *  only; 0 restores the normal behaviour.
+ * ------------------------------------------------------------------------- */
+LA_API la_status la_selftest_exhaustive_plans(int on);
+
+/* ------------------------------------------------------------------------- *
  *  Index checks (debug aid).  The compute calls trust the indices the caller
  *  hands them -- cache block ids and drafted token ids are not range-checked
  *  on the device -- and a checked build of an application can run these two

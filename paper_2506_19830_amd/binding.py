@@ -33,7 +33,7 @@ EXPORTED_SYMBOLS = (
 # what libla_verify_bench.so exports on top of those (la_verify_bench.h)
 BENCH_SYMBOLS = (
     "la_calibrate_mfma", "la_calibrate_mfma_data", "la_calibrate_read", "la_calibrate_issue", "la_selftest_exp64",
-    "la_selftest_accept_table", "la_selftest_second_attempt", "la_check_block_tables", "la_check_draft_tokens",
+    "la_selftest_accept_table", "la_selftest_second_attempt", "la_selftest_exhaustive_plans", "la_check_block_tables", "la_check_draft_tokens",
     "la_profile_enable", "la_profile_select",
     "la_profile_collect", "la_profile_num_kernels", "la_profile_get", "la_profile_reset",
 )
@@ -379,6 +379,16 @@ def la_selftest_second_attempt(on: bool) -> None:
     st = lib.la_selftest_second_attempt(int(bool(on)))
     if st:
         raise LaError(st, "la_selftest_second_attempt")
+
+
+def la_selftest_exhaustive_plans(on: bool) -> None:
+    """Make the planner model every number of chunks up to its limit in the calls that follow."""
+    lib = load("bench")
+    lib.la_selftest_exhaustive_plans.restype = ctypes.c_int
+    lib.la_selftest_exhaustive_plans.argtypes = [ctypes.c_int]
+    st = lib.la_selftest_exhaustive_plans(int(bool(on)))
+    if st:
+        raise LaError(st, "la_selftest_exhaustive_plans")
 
 
 def la_check_block_tables(desc: la_attn_desc, block_tables, prefix_lens_host: Sequence[int], num_cache_blocks: int,

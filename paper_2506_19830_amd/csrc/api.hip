@@ -278,6 +278,7 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, Attn
   double best_cost = 0.0;
   int best_len = 0, best_shape = -1, best_short = 0;
   const int64_t T = (max_p + 63) / 64;
+  const bool exhaustive = selftest_exhaustive_plans && selftest_exhaustive_plans();   // (a test's search without shortcuts)
   for (int shape = 0; shape < num_shapes(); ++shape) {
     if (d->kernel_shape > 0 && shape != d->kernel_shape - 1) continue;
     const ShapeInfo si = shape_info(shape);
@@ -297,6 +298,7 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, Attn
       const int64_t tiles = T > 0 ? (T + n - 1) / n : 1;
       n_next = tiles > 1 ? (int)((T + tiles - 2) / (tiles - 1)) : n + 1;
       if (d->num_requests > 1 && n < 9 && n_next > 9) n_next = 9;
+      if (exhaustive) n_next = n + 1;
       int64_t len = 64 * tiles;
       if (len > longest) len = longest;
       if (d->kv_split_tokens) len = d->kv_split_tokens;
@@ -309,13 +311,15 @@ la_status make_plan(const la_attn_desc *d, const int32_t *prefix_lens_host, Attn
       // requests, dealt out: every workgroup) starts workgroups and the merge reads more partials the more chunks there
       // are.  Once that alone costs the best plan so far, no later count can win.
       const double starts = d->num_requests == 1 ? (double)rounds : (double)(base_wgs * units) / (double)slots;
-      if (best_shape >= 0 && (merge_us + margin * (starts * si.t_fixed + shared_us)) * (1.0 - 1e-9) >= best_cost) break;
+      if (!exhaustive && best_shape >= 0 &&
+          (merge_us + margin * (starts * si.t_fixed + shared_us)) * (1.0 - 1e-9) >= best_cost)
+        break;
       const int64_t n_max = attn_num_chunks((int)max_p, (int)len);
       const int64_t wg_tiles = (T + last_short + n_max - 1) / n_max;  // of the longest request
       const int64_t wg_steps = (wg_tiles * 64 + si.step_keys - 1) / si.step_keys;
       double busy_us = (double)rounds * ((double)wg_steps * t_step + si.t_fixed);
       bool model = d->num_requests > 1 && rounds > 1 && n <= 8 && units <= 64;
-      if (model && best_shape >= 0 && base_wgs * units <= 2 * slots) {
+      if (!exhaustive && model && best_shape >= 0 && base_wgs * units <= 2 * slots) {
         // Dealing the workgroups out costs microseconds of host time per candidate, and every call plans: not where even
         // a bound of the result from below (the mean over the slots; `rounds` of the shortest workgroups on one slot; the
         // longest one) leaves the best plan so far in place.  (Below twice the slots, where neither this candidate's cost

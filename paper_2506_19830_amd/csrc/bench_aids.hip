@@ -18,7 +18,7 @@ struct ProfileRecord {
 };
 // process-wide state of the timing aid (not thread-safe, as its header says)
 bool g_profile_on = false;
-int g_force_second_attempt = 0;
+int g_force_second_attempt = 0, g_exhaustive_plans = 0;
 uint32_t g_profile_mask = 0xffffffffu;      // slots that are timed
 int g_profile_stride = 1;                   // of their launches, every stride-th one
 int64_t g_seen[SLOT_COUNT];                 // launches of a slot seen while enabled
@@ -64,6 +64,7 @@ void profile_after(int slot, hipStream_t stream, void *start) {
 }
 
 int selftest_force_second_attempt() { return g_force_second_attempt; }
+int selftest_exhaustive_plans() { return g_exhaustive_plans; }
 
 }  // namespace la
 
@@ -94,6 +95,11 @@ la_status la_selftest_accept_table(const la_accept_desc *desc, int32_t *has_tabl
 
 la_status la_selftest_second_attempt(int on) {
   g_force_second_attempt = on != 0;
+  return LA_OK;
+}
+
+la_status la_selftest_exhaustive_plans(int on) {
+  g_exhaustive_plans = on != 0;
   return LA_OK;
 }
 

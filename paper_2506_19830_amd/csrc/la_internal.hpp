@@ -195,6 +195,8 @@ __attribute__((weak)) void *profile_before(int slot, hipStream_t stream);       
 __attribute__((weak)) void profile_after(int slot, hipStream_t stream, void *start);
 // self-test hook of the benchmark library: nonzero = the fp8 streaming kernels run their second attempt everywhere
 __attribute__((weak)) int selftest_force_second_attempt();
+// self-test hook of the benchmark library: nonzero = the planner looks at every number of chunks up to its limit
+__attribute__((weak)) int selftest_exhaustive_plans();
 
 struct ProfileScope {
   int slot;
