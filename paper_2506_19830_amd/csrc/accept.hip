@@ -2090,11 +2090,9 @@ size_t accept_workspace_bytes(int NB, int K, int V, bool bf16, int *n_chunks_out
   b += align_up((size_t)NB * sizeof(int32_t));                             // n_acc
   b += align_up((size_t)NB * 2 * n_fine * sizeof(double));                 // zsum
   b += align_up((size_t)NB * 2 * n_fine * sizeof(double));                 // rsum
-  b += align_up((size_t)NB * 2 * sizeof(float));                           // (not used any more)
   b += lists_bytes(NB, n_fine);                                            // lists (tokens in doubt / candidates)
   b += align_up((size_t)NB * (K + 1) * sizeof(uint32_t));                  // warp_key
   b += align_up((size_t)NB * (K + 1) * sizeof(double));                    // warp_z
-  b += align_up((size_t)NB * (K + 1) * sizeof(float));                     // (not used any more)
   b += align_up((size_t)NB * (K + 1) * n_fine * sizeof(double));           // warp_zs
   return b;
 }
@@ -2109,7 +2107,6 @@ void accept_carve_workspace(AcceptParams &p, void *ws) {
   at += align_up((size_t)p.NB * 2 * p.n_fine * sizeof(double));
   p.rsum = (double *)at;
   at += align_up((size_t)p.NB * 2 * p.n_fine * sizeof(double));
-  at += align_up((size_t)p.NB * 2 * sizeof(float));
   {
     const size_t slices = (size_t)p.NB * p.n_fine;
     p.amb = at;
@@ -2130,7 +2127,7 @@ void accept_carve_workspace(AcceptParams &p, void *ws) {
   p.warp_key = warp ? (uint32_t *)at : nullptr;
   at += align_up((size_t)p.NB * (p.K + 1) * sizeof(uint32_t));
   p.warp_z = warp ? (double *)at : nullptr;
-  at += align_up((size_t)p.NB * (p.K + 1) * sizeof(double)) + align_up((size_t)p.NB * (p.K + 1) * sizeof(float));
+  at += align_up((size_t)p.NB * (p.K + 1) * sizeof(double));
   p.warp_zs = warp ? (double *)at : nullptr;
 }
 
