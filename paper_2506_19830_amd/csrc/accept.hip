@@ -1811,20 +1811,23 @@ struct Crossing {
 
 // ---------------------------------------------------------------------------------------------
 // pick: grid NB.  Bound by its chain of loads, barriers and scans, one workgroup per branch.  T lanes: 512, four tokens of the
-// chosen slice each, from 16 slices on (32 branches of 152064: 9.3 us; 256 lanes, of eight tokens, 11.8, 1024 lanes 10.7);
-// 256 where the rows are short and many.
+// chosen slice each (32 branches of 152064: 9.3 us; 256 lanes, of eight tokens, 11.8, 1024 lanes 10.7; 8 branches of one
+// slice, whole call: 15.6 against 16.1 us).  Where the branches are more than two to a CU, wavefronts are what it waits for:
+// 256 lanes and room for 256 slices' sums (1024 branches of one slice, whole call: 32 against 36 us; 4096: 91 against 103; 256:
+// 19.9 against 19.3; of 16 slices, 256 branches 34.3 against 33.5, 1024 88.7 against 93.0).
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ double residual(double pm, double qm) {
 #pragma clang fp contract(off)
   return pm - qm;
 }
 
-template <bool BF16, int T>
+constexpr int kPickMany = 512;   // branches up to which it runs 512 lanes
+template <bool BF16, int T, int kMost>
 __global__ __launch_bounds__(T) void accept_pick_kernel(const AcceptParams p) {
-  constexpr int kW = T / 64, kOwn = kFine / T, kTerms = kMaxFine / T;   // (a lane's slices: tid * kTerms + j)
-  constexpr int kLists = kThreads / 64;               // lists of a slice
-  __shared__ double buf0[kMaxFine], buf1[kMaxFine];   // slice sums of the residual and of p
-  __shared__ uint32_t s_amb[kMaxFine];                // tokens in doubt per slice, a byte per list
+  constexpr int kW = T / 64, kOwn = kFine / T, kTerms = kMost / T;   // (a lane's slices: tid * kTerms + j)
+  constexpr int kLists = kThreads / 64;         // lists of a slice
+  __shared__ double buf0[kMost], buf1[kMost];   // slice sums of the residual and of p
+  __shared__ uint32_t s_amb[kMost];             // tokens in doubt per slice, a byte per list
   __shared__ double s_sum[2][kW], s_tot[kW], s_before;
   __shared__ int s_flags[kW], s_slice;
   const int nb = blockIdx.x, tid = threadIdx.x;
@@ -2069,10 +2072,10 @@ hipError_t launch_typed(const AcceptParams &p, hipStream_t stream) {
   }
   {
     ProfileScope scope(SLOT_ACCEPT_PICK, stream);
-    if (p.n_fine >= 16)
-      hipLaunchKernelGGL((accept_pick_kernel<BF16, 512>), dim3(p.NB), dim3(512), 0, stream, p);
+    if (p.NB <= kPickMany || p.n_fine > 256)
+      hipLaunchKernelGGL((accept_pick_kernel<BF16, 512, kMaxFine>), dim3(p.NB), dim3(512), 0, stream, p);
     else
-      hipLaunchKernelGGL((accept_pick_kernel<BF16, 256>), dim3(p.NB), dim3(256), 0, stream, p);
+      hipLaunchKernelGGL((accept_pick_kernel<BF16, 256, 256>), dim3(p.NB), dim3(256), 0, stream, p);
     return hipGetLastError();
   }
 }

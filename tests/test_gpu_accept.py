@@ -411,3 +411,11 @@ def test_a_row_without_a_finite_logit_writes_an_index(V):
     inp["target_logits"][:] = 0xFF80
     got = run_accept(case, inp)
     assert (got["next_token"] >= 0).all() and (got["next_token"] < V).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("NB,V", [(512, 2049), (513, 2049), (513, 700), (600, 9000)])
+def test_many_branches(oracle, NB, V, dtype):
+    """Around the number of branches from which the last kernel runs fewer lanes per branch: one slice, a slice and a token,
+    several."""
+    check(oracle, W.AcceptCase("many", NB, 1, V, dtype, target_std=2.0, seed=60))
