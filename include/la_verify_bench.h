@@ -66,13 +66,20 @@ LA_API la_status la_selftest_exp64(const double *y, double *out, size_t n, void 
 
 /* ------------------------------------------------------------------------- *
  *  Self-test hook: whether la_spec_accept would look the fp64 masses of this
- *  call's logits up in a table (1) or evaluate an exponential per token (0).
+ *  call's logits up in a table (1) or evaluate an exponential per token (0);
+ *  draft_logits: whether the call has any.  row_candidates (or NULL): how many
+ *  candidate tokens of a target row a call with top-p alone can hold in all.
  *  Host only.
+ *  la_selftest_force_table(1): every call that can have a table has one, also
+ *  where it is not worth its cost, so that small calls test it.  Process-wide,
+ *  host side only; 0 restores the normal behaviour.
  * ------------------------------------------------------------------------- */
-LA_API la_status la_selftest_accept_table(const la_accept_desc *desc, int32_t *has_table);
+LA_API la_status la_selftest_accept_table(const la_accept_desc *desc, int32_t draft_logits, int32_t *has_table,
+                                          int32_t *row_candidates);
+LA_API la_status la_selftest_force_table(int on);
 
 /* ------------------------------------------------------------------------- *
- *  Self-test hook for the streaming kernel shapes of an fp8 cache.  Their
+ *  Self-test hook for the streaming kernel shapes.  Their
  *  unmasked tiles never move the base their probabilities are formed against
  *  (Section 3.2's verification pass needs no such thing; it is this
  *  implementation's way to keep the accumulators of O in place); a workgroup

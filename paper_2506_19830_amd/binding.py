@@ -372,7 +372,7 @@ def la_selftest_accept_table(desc: la_accept_desc) -> bool:
 
 
 def la_selftest_second_attempt(on: bool) -> None:
-    """Make every workgroup of the fp8 streaming shapes take its second (general-form) attempt in the calls that follow."""
+    """Make every workgroup of the streaming shapes take its second (general-form) attempt in the calls that follow."""
     lib = load("bench")
     lib.la_selftest_second_attempt.restype = ctypes.c_int
     lib.la_selftest_second_attempt.argtypes = [ctypes.c_int]

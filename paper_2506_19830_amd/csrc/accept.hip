@@ -16,7 +16,7 @@
 //           whose residual max(0, p-q) is positive beyond doubt; tokens in doubt are listed.
 //   pick    grid NB: the normalisers, each slice's residual mass (its listed tokens settled),
 //           the slice in which the running sum first exceeds u_sample * total, then the lane
-//           inside it (its tokens evaluated again, eight per lane), then the token.
+//           inside it (its tokens evaluated again, four or eight per lane), then the token.
 //   warp    (only with top-k / top-p) one workgroup per target row: the smallest logit the row keeps and the
 //           mass of the kept tokens.  Both filters are predicates on a token's value (keep v iff fewer than k
 //           tokens are larger; keep v iff the mass of the larger kept tokens is below top_p * Z_k), so equal
@@ -48,7 +48,7 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) uint16_t u16x2;
 
 constexpr int kThreads = 256;
-constexpr int kFinePer = 8;                 // tokens per lane in the fp64 kernels (load_fine reads eight)
+constexpr int kFinePer = 8;                 // tokens per lane in the fp64 kernels (FineWords holds eight)
 constexpr int kFine = kThreads * kFinePer;  // 2048 tokens per fine slice
 constexpr int kMaxFine = 1024;   // fine slices per row the fp64 kernels can stage in LDS (vocab <= 2M)
 
@@ -1691,7 +1691,7 @@ __global__ __launch_bounds__(kSampleSlices<TAB> * kThreads, (TAB ? 6 : 1)) void 
   const float margin = head.margin(p);
   const float threshold = (float)(((double)head.mt - (double)head.mq) * (double)p.inv_temp_log2 +
                                   (double)__builtin_amdgcn_logf(head.zt / head.zq));
-  // no bounds test per token: load_fine gives -inf past V, whose mass is exactly 0, and the eight masses of a lane can
+  // no bounds test per token: places past V read as -inf, whose mass is exactly 0, and the eight masses of a lane can
   // then be evaluated side by side instead of one dependent chain after the other
   if (p.warp_key) wt.keep(x_min);   // (comparing values is comparing keys)
   double a[kFinePer], b[kFinePer];
@@ -1774,7 +1774,7 @@ __device__ __forceinline__ double sum_of_waves(const double *v) {
 
 // Where a running sum over the workgroup's values crosses thr = u * total: v is a lane's (non-negative) value, lanes in
 // order.  Every lane gets the total, its own exclusive prefix, the first lane whose running sum exceeds thr (the last lane
-// with a value if rounding hides it; -1 without any).  One barrier inside, one expected before the next call.
+// with a value if rounding hides it; -1 without any).  Two barriers inside, one expected before the next call.
 template <int kW>
 struct Crossing {
   double total, excl, thr;

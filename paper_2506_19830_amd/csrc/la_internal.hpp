@@ -50,7 +50,7 @@ struct AttnParams {
   int q_type, kv_type, br_type;  // la_dtype of Q, of the prefix cache, of the branch / chain / pool K and V
   float scale_log2; // softmax_scale * log2(e)
   union {
-    int force_again;  // streaming shapes (fp8): start with the give-up flag raised, so that every workgroup also runs its
+    int force_again;  // streaming shapes: start with the give-up flag raised, so that every workgroup also runs its
                       // second attempt (a self-test hook of the benchmark library; 0 otherwise)
     int first_wg;     // general kernel: number of the launch's first workgroup (calls too large for one launch)
   };
@@ -144,9 +144,11 @@ struct AcceptParams {
   // workspace
   float *stats;                // [rows = NB*(2K+1), n_chunks, 2]  (exact max, sum 2^((x-max)*log2e/T))
   int32_t *n_acc;              // [NB]
-  double *zsum;                // [NB, 2, n_fine]  fp64 slice sums of exp(z - max) of the target and the draft resampling row
+  // (slice sums and listed masses are in their row's unit, e^0 where its logits are looked up in the table, else e^(max/T):
+  // mass_unit in accept.hip; warp_z and the heads' masses are in units of e^(max/T))
+  double *zsum;                // [NB, 2, n_fine]  fp64 slice sums of the masses of the target and the draft resampling row
   double *rsum;                // [NB, 2, n_fine]  the same over the tokens whose residual is positive beyond doubt
-  uint8_t *amb;                // [NB, n_fine, 4, 48] masses of the tokens in doubt
+  uint8_t *amb;                // [NB, n_fine, 4, 48] masses of the tokens in doubt, or of groups of them
   uint32_t *amb_n;             // [NB, n_fine] their number, a byte per wavefront of the slice's workgroup
   uint8_t *heads;              // [NB] row maxima and fp32 masses of the resampling rows
   double *exp_tab;             // exp(x / T) of the bf16 logits, or null (see accept.hip)
@@ -157,7 +159,7 @@ struct AcceptParams {
   float top_p;
   uint32_t *warp_key;          // [NB*(K+1)] order-preserving key of the smallest logit a row keeps
   double *warp_z;              // [NB*(K+1)] sum exp((x - max)/T) over the kept tokens
-  double *warp_zs;             // [NB*(K+1), n_fine] fp64 slice sums of exp((x - max)/T) of every target row (top-p alone)
+  double *warp_zs;             // [NB*(K+1), n_fine] fp64 slice sums of the masses of every target row (top-p alone)
 };
 
 size_t accept_workspace_bytes(int NB, int K, int V, bool bf16, int *n_chunks_out, int *n_fine_out);
