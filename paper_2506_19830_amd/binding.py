@@ -33,7 +33,7 @@ EXPORTED_SYMBOLS = (
 # what libla_verify_bench.so exports on top of those (la_verify_bench.h)
 BENCH_SYMBOLS = (
     "la_calibrate_mfma", "la_calibrate_mfma_data", "la_calibrate_read", "la_calibrate_issue", "la_selftest_exp64",
-    "la_selftest_accept_table", "la_selftest_second_attempt", "la_selftest_exhaustive_plans", "la_check_block_tables", "la_check_draft_tokens",
+    "la_selftest_accept_table", "la_selftest_force_table", "la_selftest_second_attempt", "la_selftest_exhaustive_plans", "la_check_block_tables", "la_check_draft_tokens",
     "la_profile_enable", "la_profile_select",
     "la_profile_collect", "la_profile_num_kernels", "la_profile_get", "la_profile_reset",
 )
@@ -360,15 +360,27 @@ def la_selftest_exp64(y, out) -> None:
         raise LaError(st, "la_selftest_exp64")
 
 
-def la_selftest_accept_table(desc: la_accept_desc) -> bool:
-    """Whether ``la_spec_accept`` looks the masses of this call's logits up in a table (host only)."""
+def la_selftest_force_table(on: bool) -> None:
+    """Give every accept call that can have a table of masses one, also where it is not worth its cost."""
     lib = load("bench")
-    out = ctypes.c_int32(-1)
+    lib.la_selftest_force_table.restype = ctypes.c_int
+    lib.la_selftest_force_table.argtypes = [ctypes.c_int]
+    st = lib.la_selftest_force_table(int(bool(on)))
+    if st:
+        raise LaError(st, "la_selftest_force_table")
+
+
+def la_selftest_accept_table(desc: la_accept_desc, draft_logits: bool = True) -> Tuple[bool, int]:
+    """Whether ``la_spec_accept`` looks the masses of this call's logits up in a table, and how many candidate tokens of a target
+    row it can hold with top-p alone (host only)."""
+    lib = load("bench")
+    out, cand = ctypes.c_int32(-1), ctypes.c_int32(-1)
     lib.la_selftest_accept_table.restype = ctypes.c_int
-    st = lib.la_selftest_accept_table(ctypes.byref(desc), ctypes.byref(out))
+    st = lib.la_selftest_accept_table(ctypes.byref(desc), ctypes.c_int32(int(draft_logits)), ctypes.byref(out),
+                                      ctypes.byref(cand))
     if st:
         raise LaError(st, "la_selftest_accept_table")
-    return bool(out.value)
+    return bool(out.value), cand.value
 
 
 def la_selftest_second_attempt(on: bool) -> None:

@@ -194,9 +194,9 @@ __device__ __forceinline__ double mass64(float x, double mx_over_t, double inv_t
 //
 // The masses of such a row are in units of e^0, not of e^(max/T): nothing but their quotients leaves the call, and with
 // |max| / T up to 300 no sum overflows and a token that vanishes weighs e^-445 of the row at most.  A row beyond that keeps
-// the maximum as its unit and the exponential per token (mass_unit).  fp32 logits, calls of a few slices, whose workspace has
-// no room for it, and temperatures below 0.11 have no table: its largest entry is e^(64/T), which leaves the range of a
-// double at T = 0.0902; at 0.11 it is e^582.
+// the maximum as its unit and the exponential per token (mass_unit).  fp32 logits, calls of less than 64 slices, whose
+// workspace has no room for it, and temperatures below 0.11 have no table: its largest entry is e^(64/T), which leaves the
+// range of a double at T = 0.0902; at 0.11 it is e^582.  Nor do calls that it would cost more than it gives (worth_a_table).
 // ---------------------------------------------------------------------------------------------
 constexpr int kTabLo = 115 * 128;               // bit pattern of 2^-12
 constexpr int kTabHalf = 18 * 128;              // up to 2^6
@@ -1092,15 +1092,18 @@ __host__ __device__ inline int rowz_group(const AcceptParams &p) {
 struct CandHeader {
   uint32_t n, pad[3];   // tokens at or above the bound (more than fit: the segment is not complete)
 };
-template <bool BF16>
+// A row's space is shared out by slices, so that a last group of few of them does not take a whole group's part.
 __device__ __forceinline__ uint8_t *cand_segment(const AcceptParams &p, int rw, int group) {
-  return p.cand + ((size_t)rw * ((p.n_fine + rowz_group(p) - 1) / rowz_group(p)) + group) * p.cand_bytes;
+  return p.cand + (size_t)rw * p.cand_row + (size_t)((uint32_t)group * (uint32_t)p.cand_seg);
 }
-constexpr int kCandLds = 1024;      // most keys of a segment
-constexpr int kCandLdsTab = 1792;   // ... of twice the slices (four workgroups' tables and lists fit a CU's LDS)
+// Most keys of a segment in the workgroup's LDS: 1792 of bf16 logits (with a table, four workgroups' tables and lists fit a CU's
+// LDS), 1024 of fp32 ones.  Of bf16 logits of deviation 3 at T 1.0 and top_p 0.95 one in eight is listed, at 0.98 one in five.
+// Rows whose lists are complete but fall short (deviation 2, top_p 0.9: one in five as well) pay the counting before the long
+// way (V = 8192: 79 -> 82 us).
 template <bool BF16>
-__device__ __forceinline__ int cand_capacity(const AcceptParams &p) {
-  return min(BF16 && p.exp_tab ? kCandLdsTab : kCandLds, (p.cand_bytes - (int)sizeof(CandHeader)) / (BF16 ? 2 : 4));
+constexpr int kCandLds = BF16 ? 1792 : 1024;
+__device__ __forceinline__ int cand_capacity(const AcceptParams &p, int group) {
+  return (group + 1) * rowz_group(p) < p.n_fine ? p.cand_cap : p.cand_cap_last;
 }
 
 template <bool BF16, bool TAB>
@@ -1109,7 +1112,7 @@ __global__ __launch_bounds__(RowzShape<TAB>::kT, (TAB ? 6 : 1)) void accept_rowz
   typedef typename std::conditional<BF16, uint16_t, uint32_t>::type key_t;
   __shared__ double red[Sh::kPer][Sh::kT / 64];
   __shared__ int s_cnt[Sh::kT / 64];
-  __shared__ alignas(4) key_t s_list[(TAB ? kCandLdsTab : kCandLds) + 2];   // (bf16: the second half of the last word)
+  __shared__ alignas(4) key_t s_list[kCandLds<BF16> + 2];   // (bf16: the second half of the last word)
   __shared__ alignas(16) double s_tab[TAB ? kTab : 2];
   const int rw = blockIdx.y, tid = threadIdx.x;
   // slices c0 .. c0 + kPer - 1 of this half of the workgroup
@@ -1170,15 +1173,15 @@ __global__ __launch_bounds__(RowzShape<TAB>::kT, (TAB ? 6 : 1)) void accept_rowz
     const double *r = red[ht] + tid / kThreads * (kThreads / 64);
     p.warp_zs[(size_t)rw * p.n_fine + c0 + ht] = (r[0] + r[1]) + (r[2] + r[3]);
   }
-  if (p.cand_bytes) {   // (uniform)
+  if (p.cand_row) {   // (uniform)
     // in rounds, one listed token per lane and round, its logit read once more (few, and just loaded: a test per token in
     // straight code took 4 us of the kernel's 18); through LDS, then in whole words to the segment
-    uint8_t *seg = cand_segment<BF16>(p, rw, blockIdx.x);
+    uint8_t *seg = cand_segment(p, rw, blockIdx.x);
     int total = 0;
 #pragma unroll
     for (int i = 0; i < Sh::kT / 64; ++i) total += s_cnt[i];
     if (tid == 0) ((CandHeader *)seg)->n = (uint32_t)total;
-    if (total > cand_capacity<BF16>(p)) return;   // (uniform)
+    if (total > cand_capacity(p, blockIdx.x)) return;   // (uniform)
     int at = incl - own;
     for (int i = 0; i < wave; ++i) at += s_cnt[i];
     for (; marks; marks &= marks - 1, ++at) {
@@ -1188,7 +1191,7 @@ __global__ __launch_bounds__(RowzShape<TAB>::kT, (TAB ? 6 : 1)) void accept_rowz
       s_list[at] = (key_t)(BF16 ? key >> 16 : key);
     }
     __syncthreads();
-    uint32_t *to = (uint32_t *)(seg + sizeof(CandHeader));   // (the segment ends on a multiple of 16 bytes)
+    uint32_t *to = (uint32_t *)(seg + sizeof(CandHeader));   // (room for a multiple of 16 bytes)
     const int words = BF16 ? (total + 1) / 2 : total;
     for (int i = tid; i < words; i += Sh::kT) to[i] = ((const uint32_t *)s_list)[i];
   }
@@ -1210,12 +1213,13 @@ constexpr int kCandPer = 8;                        // keys per lane
 constexpr int kCandMax = kCandPer * kWarpThreads;  // (the LDS list holds as many)
 
 // The form for bf16 rows.  m: the row maximum; zk: the row's mass; keys0: the first 16 bytes a lane reads of its wavefront's
-// first segment, requested before the segments' counts were known; s_n: the counts.  false: the listed tokens span more
-// values than there are bins, or fall short of the target (the same decision in every lane).
+// first segment, requested before the segments' counts were known; s_n: the counts.  BINS_OUTSIDE: the listed tokens span more
+// values than there are bins; BINS_SHORT: they fall short of the target (the same decision in every lane).
+enum BinsResult { BINS_DONE, BINS_OUTSIDE, BINS_SHORT };
 constexpr int kBinPer = 4;                       // values per lane
 constexpr int kBins = kBinPer * kWarpThreads;    // 32 octaves; the counts share the list's storage
 
-__device__ __forceinline__ bool warp_top_p_bins(const AcceptParams &p, int rw, float m, double zk, u32x4 keys0, const int *s_n,
+__device__ __forceinline__ BinsResult warp_top_p_bins(const AcceptParams &p, int rw, float m, double zk, u32x4 keys0, const int *s_n,
                                                 int n_g, uint32_t *bins, uint32_t *key_min_out, double *z_out) {
   constexpr int kW = kWarpThreads / 64;
   __shared__ int s_outside, s_at[kW];
@@ -1226,9 +1230,9 @@ __device__ __forceinline__ bool warp_top_p_bins(const AcceptParams &p, int rw, f
   *(u32x4 *)(bins + tid * kBinPer) = (u32x4){0, 0, 0, 0};
   __syncthreads();
   for (int g = wave; g < n_g; g += kW) {
-    const u32x4 *keys = (const u32x4 *)(cand_segment<true>(p, rw, g) + sizeof(CandHeader));
+    const u32x4 *keys = (const u32x4 *)(cand_segment(p, rw, g) + sizeof(CandHeader));
     const int cnt = s_n[g];
-    for (int i = lane; i * 8 < cnt; i += 64) {   // eight keys to a load (a segment ends on a multiple of 16 bytes)
+    for (int i = lane; i * 8 < cnt; i += 64) {   // eight keys to a load (a segment holds a multiple of 16 bytes)
       const u32x4 w = g == wave && i == lane ? keys0 : keys[i];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -1242,7 +1246,7 @@ __device__ __forceinline__ bool warp_top_p_bins(const AcceptParams &p, int rw, f
     }
   }
   __syncthreads();
-  if (s_outside) return false;
+  if (s_outside) return BINS_OUTSIDE;
   const double o_t = mass_unit(p, m);
   const u32x4 n_of = *(const u32x4 *)(bins + tid * kBinPer);
   auto key_of = [&](int bin) {   // (the sixteen low bits of a widened bf16 value's key)
@@ -1288,10 +1292,10 @@ __device__ __forceinline__ bool warp_top_p_bins(const AcceptParams &p, int rw, f
 #pragma unroll
   for (int w = 0; w < kW; ++w)
     if (bin == INT_MAX && s_at[w] != INT_MAX) bin = s_at[w], z = s_at_mass[w];
-  if (bin == INT_MAX) return false;
+  if (bin == INT_MAX) return BINS_SHORT;
   *key_min_out = key_of(bin);
   *z_out = z * unit_over_max(p, m);
-  return true;
+  return BINS_DONE;
 }
 
 template <bool BF16>
@@ -1303,16 +1307,16 @@ __device__ __forceinline__ bool warp_top_p_segments(const AcceptParams &p, int r
   __shared__ uint32_t s_low[kW];
   __shared__ double s_sum[2][3][kW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int n_g = (p.n_fine + rowz_group(p) - 1) / rowz_group(p), cap = cand_capacity<BF16>(p);
+  const int n_g = (p.n_fine + rowz_group(p) - 1) / rowz_group(p);
   // zk from the row's fine-slice sums, in a fixed order: slice t in lane t, a butterfly per wavefront, the wavefronts
   // in order
   u32x4 keys0 = {0, 0, 0, 0};
-  if (BF16 && wave < n_g && (int)sizeof(CandHeader) + (lane + 1) * 16 <= p.cand_bytes)
-    keys0 = ((const u32x4 *)(cand_segment<BF16>(p, rw, wave) + sizeof(CandHeader)))[lane];
+  if (BF16 && wave < n_g && lane * 8 < cand_capacity(p, wave))
+    keys0 = ((const u32x4 *)(cand_segment(p, rw, wave) + sizeof(CandHeader)))[lane];
   double acc = 0.0;
   for (int t = tid; t < p.n_fine; t += kWarpThreads) acc += p.warp_zs[(size_t)rw * p.n_fine + t];
   // where each segment's keys go in the list (n_g <= kMaxGroups <= the workgroup)
-  const int own = tid < n_g ? (int)((const CandHeader *)cand_segment<BF16>(p, rw, tid))->n : 0;
+  const int own = tid < n_g ? (int)((const CandHeader *)cand_segment(p, rw, tid))->n : 0;
   float m = -INFINITY;   // the row maximum
   for (int c = lane; c < p.n_chunks; c += 64) m = fmaxf(m, p.stats[((size_t)rw * p.n_chunks + c) * 2]);
   acc = wave_sum(acc);
@@ -1320,7 +1324,7 @@ __device__ __forceinline__ bool warp_top_p_segments(const AcceptParams &p, int r
   m = wave_max_dpp(m);
   *row_max_out = m;
   const double o_t = mass_unit(p, m);   // the masses here are in the unit of the slice sums
-  const bool bad = own > cap;
+  const bool bad = tid < n_g && own > cand_capacity(p, tid);
   int incl = own;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -1345,12 +1349,13 @@ __device__ __forceinline__ bool warp_top_p_segments(const AcceptParams &p, int r
   __syncthreads();
   if (s_bad || n < 1) return false;
   if constexpr (BF16) {
-    if (warp_top_p_bins(p, rw, m, zk, keys0, s_n, n_g, list, key_min_out, z_out)) return true;
+    const BinsResult r = warp_top_p_bins(p, rw, m, zk, keys0, s_n, n_g, list, key_min_out, z_out);
+    if (r != BINS_OUTSIDE) return r == BINS_DONE;
     __syncthreads();
   }
   if (n > kCandMax) return false;
   for (int g = wave; g < n_g; g += kW) {
-    const uint8_t *keys = cand_segment<BF16>(p, rw, g) + sizeof(CandHeader);
+    const uint8_t *keys = cand_segment(p, rw, g) + sizeof(CandHeader);
     const int off = s_off[g], cnt = s_off[g + 1] - off;
     for (int i = lane; i < cnt; i += 64) {
       if constexpr (BF16) {   // (the sixteen low bits of a widened bf16 value's key)
@@ -1450,7 +1455,7 @@ __global__ __launch_bounds__(kWarpThreads) void accept_warp_kernel(const AcceptP
   if (p.top_k > 0 && p.top_k < p.V && p.top_k <= kSmallK)   // the candidate list lives in the histogram's storage
     done = warp_small_k<BF16>(p, row, cnt, cnt + kCand, mass + kCand, &m, &key_min, &zw);
   const bool use_k = p.top_k > 0 && p.top_k < p.V;
-  if (!done && !use_k && p.top_p < 1.0f && p.cand_bytes) {   // (the candidate lists live in the histogram's storage)
+  if (!done && !use_k && p.top_p < 1.0f && p.cand_row) {   // (the candidate lists live in the histogram's storage)
     done = warp_top_p_segments<BF16>(p, rw, red, cnt, &m, &key_min, &zw);
     __syncthreads();
   }
@@ -2100,6 +2105,20 @@ size_t accept_workspace_bytes(int NB, int K, int V, bool bf16, int *n_chunks_out
   return b;
 }
 
+// Is a table worth its copy to every workgroup's LDS?  With top-p alone, whose rowz kernel takes all target rows, six slices to
+// a workgroup: from 2048 slices in all on, rows of at least six (V = 152064, whole call, with and without: 600 slices 31.8 and
+// 29.7 us, 1200 32.7 and 33.0, 2400 35.2 and 36.5, 9450 50.8 and 55.8; V = 12000: 2400 slices 38.1 and 41.3; V = 6000, half of
+// every workgroup empty: 2400 56.5 and 53.2, 9600 141 and 135).  In calls just large enough to hold one it would also take a
+// seventh of the candidates' space, and rows whose candidates do not fit take the long way (V = 65536, two branches, K 8, T 1.0,
+// top_p 0.9: 128 against 32 us).  Otherwise the sample kernel alone, two slices to a workgroup: with draft rows from 1200 slices
+// on, of long rows (V = 152064: 600 slices 19.2 and 18.6 us, 1200 22.6 and 23.0, 4800 43.3 and 44.9; V = 32000: 2400 31.7 and 31.3;
+// V = 512, 4096 branches 89.4 and 75.6).  Without draft rows it is even at best.
+static bool worth_a_table(const AcceptParams &p) {
+  const size_t slices = (size_t)p.NB * p.n_fine;
+  if (p.top_p < 1.0f && !(p.top_k > 0 && p.top_k < p.V)) return slices * (p.K + 1) >= 2048 && p.n_fine >= 6;
+  return p.draft && slices >= 1200 && p.n_fine >= 32;
+}
+
 void accept_carve_workspace(AcceptParams &p, void *ws) {
   uint8_t *at = (uint8_t *)ws;
   p.stats = (float *)at;
@@ -2116,14 +2135,23 @@ void accept_carve_workspace(AcceptParams &p, void *ws) {
     p.heads = at + slices * (kThreads / 64) * kAmb * sizeof(Doubt);
     p.amb_n = (uint32_t *)(p.heads + (size_t)p.NB * sizeof(BranchHead));
     // the table ends the space, out of the way of both kinds of lists (64 slices leave 64 KiB behind the lists in doubt)
-    const bool tab = p.bf16 && slices >= 64 && p.inv_temp <= 1.0 / (double)kTabMinTemperature;
+    const bool room = p.bf16 && slices >= 64 && p.inv_temp <= 1.0 / (double)kTabMinTemperature;
+    const bool tab = room && (worth_a_table(p) || (selftest_force_table && selftest_force_table()));
     p.exp_tab = tab ? (double *)(at + lists_bytes(p.NB, p.n_fine) - kTab * sizeof(double)) : nullptr;
-    // the candidate segments of a call with top-p alone share the space: equal parts, 16-byte aligned, none if too small
-    const size_t groups = (size_t)p.NB * (p.K + 1) * ((p.n_fine + rowz_group(p) - 1) / rowz_group(p));
+    // the candidate segments of a call with top-p alone share the space: rows equally, a row's by its slices; none if they are
+    // too small (or one of a single slice could not hold its header)
     const size_t space = slices * kThreads * 2 * sizeof(double) - (tab ? kTab * sizeof(double) : 0);
-    const size_t bytes = (space / groups) & ~(size_t)15;
     p.cand = at;
-    p.cand_bytes = bytes >= 64 ? (int)bytes : 0;
+    p.cand_row = (int)((space / ((size_t)p.NB * (p.K + 1))) & ~(size_t)15);
+    const int groups = (p.n_fine + rowz_group(p) - 1) / rowz_group(p);
+    p.cand_seg = groups > 1 ? (int)((int64_t)p.cand_row * rowz_group(p) / p.n_fine) & ~15 : p.cand_row;
+    const int last = p.cand_row - (groups - 1) * p.cand_seg, lds = p.bf16 ? kCandLds<true> : kCandLds<false>;
+    auto keys = [&](int bytes) {
+      const int fit = (bytes - (int)sizeof(CandHeader)) / (p.bf16 ? 2 : 4);
+      return fit < lds ? fit : lds;
+    };
+    p.cand_cap = keys(p.cand_seg), p.cand_cap_last = keys(last);
+    if (p.cand_row / p.n_fine < 16 || p.cand_seg < 64) p.cand_row = 0;
   }
   at += lists_bytes(p.NB, p.n_fine);
   const bool warp = (p.top_k > 0 && p.top_k < p.V) || p.top_p < 1.0f;
@@ -2145,6 +2173,10 @@ hipError_t launch_exp64_probe(const double *y, double *out, size_t n, hipStream_
   hipLaunchKernelGGL(exp64_probe_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, y, out,
                      n);
   return hipGetLastError();
+}
+
+int accept_row_candidates(const AcceptParams &p) {
+  return p.cand_row ? (p.n_fine - 1) / rowz_group(p) * p.cand_cap + p.cand_cap_last : 0;
 }
 
 hipError_t launch_accept(const AcceptParams &p, hipStream_t stream) {

@@ -18,7 +18,7 @@ struct ProfileRecord {
 };
 // process-wide state of the timing aid (not thread-safe, as its header says)
 bool g_profile_on = false;
-int g_force_second_attempt = 0, g_exhaustive_plans = 0;
+int g_force_second_attempt = 0, g_exhaustive_plans = 0, g_force_table = 0;
 uint32_t g_profile_mask = 0xffffffffu;      // slots that are timed
 int g_profile_stride = 1;                   // of their launches, every stride-th one
 int64_t g_seen[SLOT_COUNT];                 // launches of a slot seen while enabled
@@ -64,6 +64,7 @@ void profile_after(int slot, hipStream_t stream, void *start) {
 }
 
 int selftest_force_second_attempt() { return g_force_second_attempt; }
+int selftest_force_table() { return g_force_table; }
 int selftest_exhaustive_plans() { return g_exhaustive_plans; }
 
 }  // namespace la
@@ -77,7 +78,12 @@ la_status la_selftest_exp64(const double *y, double *out, size_t n, void *hip_st
   return launch_exp64_probe(y, out, n, (hipStream_t)hip_stream) == hipSuccess ? LA_OK : LA_ERR_LAUNCH;
 }
 
-la_status la_selftest_accept_table(const la_accept_desc *desc, int32_t *has_table) {
+la_status la_selftest_force_table(int on) {
+  g_force_table = on != 0;
+  return LA_OK;
+}
+
+la_status la_selftest_accept_table(const la_accept_desc *desc, int32_t draft_logits, int32_t *has_table, int32_t *row_candidates) {
   size_t bytes = 0;
   if (!has_table) return LA_ERR_INVALID_ARG;
   const la_status st = la_spec_accept_workspace(desc, &bytes);   // validates the descriptor
@@ -88,8 +94,10 @@ la_status la_selftest_accept_table(const la_accept_desc *desc, int32_t *has_tabl
   p.NB = desc->num_branches, p.K = desc->num_draft, p.V = desc->vocab;
   p.inv_temp = 1.0 / (double)desc->temperature;
   p.top_k = desc->top_k, p.top_p = desc->top_p;
+  p.draft = draft_logits ? &p : nullptr;   // (whether there are any is all that is asked)
   accept_carve_workspace(p, (void *)(uintptr_t)256);   // (addresses only: nothing is read or written)
   *has_table = p.exp_tab != nullptr;
+  if (row_candidates) *row_candidates = accept_row_candidates(p);
   return LA_OK;
 }
 

@@ -153,7 +153,9 @@ struct AcceptParams {
   uint8_t *heads;              // [NB] row maxima and fp32 masses of the resampling rows
   double *exp_tab;             // exp(x / T) of the bf16 logits, or null (see accept.hip)
   uint8_t *cand;               // top-p alone: candidate segments of every target row, in the space of the lists above
-  int cand_bytes;              // size of one segment (0: none)
+  int cand_row;                // bytes of a row's segments (0: none)
+  int cand_seg;                // bytes of one (the last has what is left)
+  int cand_cap, cand_cap_last; // keys that one holds, and the last one
   // top-k / top-p warping of the target rows (off: top_k == 0 and top_p >= 1)
   int top_k;
   float top_p;
@@ -164,6 +166,8 @@ struct AcceptParams {
 
 size_t accept_workspace_bytes(int NB, int K, int V, bool bf16, int *n_chunks_out, int *n_fine_out);
 void accept_carve_workspace(AcceptParams &p, void *ws);
+// top-p alone: candidates of a carved call's target row that its segments hold in all (self-test hook)
+int accept_row_candidates(const AcceptParams &p);
 hipError_t launch_accept(const AcceptParams &p, hipStream_t stream);
 // out[i] = the accept path's own fp64 exponential of y[i] (self-test hook)
 hipError_t launch_exp64_probe(const double *y, double *out, size_t n, hipStream_t stream);
@@ -195,8 +199,10 @@ hipError_t launch_kv_commit(const CommitParams &p, int src_bytes, bool quantise,
 // ----------------------------------------------------------------------------
 __attribute__((weak)) void *profile_before(int slot, hipStream_t stream);            // start event, or null
 __attribute__((weak)) void profile_after(int slot, hipStream_t stream, void *start);
-// self-test hook of the benchmark library: nonzero = the fp8 streaming kernels run their second attempt everywhere
+// self-test hook of the benchmark library: nonzero = the streaming kernels run their second attempt everywhere
 __attribute__((weak)) int selftest_force_second_attempt();
+// self-test hook of the benchmark library: nonzero = every accept call that can have a table of masses has one
+__attribute__((weak)) int selftest_force_table();
 // self-test hook of the benchmark library: nonzero = the planner looks at every number of chunks up to its limit
 __attribute__((weak)) int selftest_exhaustive_plans();
 

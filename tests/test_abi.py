@@ -447,3 +447,36 @@ def test_plan_search_misses_nothing():
         B.select_library("product")
     assert sum(not isinstance(x, str) for x in full) > 3000
     assert fast == full
+
+
+@pytest.mark.parametrize("NB,K,V,T,top_k,top_p,draft,table", [
+    (32, 8, 152064, 1.0, 0, 1.0, True, True), (15, 8, 152064, 1.0, 0, 1.0, True, False),      # 1200 slices of a row
+    (16, 8, 152064, 1.0, 0, 1.0, True, True), (2000, 1, 32000, 1.0, 0, 1.0, True, False),     # rows of 32 slices
+    (32, 8, 152064, 1.0, 0, 1.0, False, False), (6, 8, 152064, 0.6, 0, 0.95, False, True),
+    (3, 8, 152064, 0.6, 0, 0.95, False, False), (400, 8, 10240, 0.6, 0, 0.95, False, False),  # 2048 slices; rows of six
+    (32, 8, 152064, 0.6, 20, 0.95, False, False), (32, 8, 152064, 0.1, 0, 1.0, True, False),
+    (600, 8, 10241, 0.6, 0, 0.95, True, True),
+])
+def test_calls_with_a_table_of_masses(NB, K, V, T, top_k, top_p, draft, table):
+    """Which accept calls look their masses up: where the table is worth its copy to every workgroup."""
+    for dtype in ("bf16", "f32"):
+        desc = B.make_accept_desc(num_branches=NB, num_draft=K, vocab=V, logits_dtype=dtype, temperature=T, top_k=top_k,
+                                  top_p=top_p)
+        assert B.la_selftest_accept_table(desc, draft)[0] == (table and dtype == "bf16")
+
+
+def test_room_for_top_p_candidates():
+    """A target row's candidate segments share the row's part of the workspace, 4096 / (K + 1) bytes per 2048 tokens and call
+    branch; the table of masses, where a call has one, takes no more than a sixteenth of it, and short last groups of slices
+    waste nothing: a row that a call without a table could hold is not sent the long way."""
+    rng = np.random.default_rng(5)
+    for _ in range(2000):
+        NB, K = int(rng.integers(1, 65)), int(rng.choice([1, 2, 3, 4, 6, 8, 12, 20]))
+        V = int(np.exp(rng.uniform(np.log(100), np.log(300000))))
+        dtype = str(rng.choice(["bf16", "f32"]))
+        desc = B.make_accept_desc(num_branches=NB, num_draft=K, vocab=V, logits_dtype=dtype, temperature=0.8, top_k=0, top_p=0.9)
+        table, room = B.la_selftest_accept_table(desc, False)
+        slices = (V + 2047) // 2048
+        key = 2 if dtype == "bf16" else 4
+        most = min(1024, (16384 // (K + 1) // 16 * 16 - 16) // key) / 4                   # per slice
+        assert room >= (15 / 16 if table else 0.97) * most * slices - 16, (NB, K, V, dtype, table, room, most * slices)

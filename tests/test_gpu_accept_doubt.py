@@ -5,7 +5,7 @@ import pytest
 
 from paper_2506_19830_amd import workloads as W
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("accept_tables")]
 
 # vocabularies around a wavefront's 512 tokens, a 2048-token slice, rows without 16-byte alignment
 VOCABS = (64, 513, 2048, 2049, 6000, 20003)

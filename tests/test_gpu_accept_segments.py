@@ -4,7 +4,7 @@ import pytest
 from paper_2506_19830_amd import workloads as W
 from test_gpu_accept import check
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("accept_tables")]
 
 CASES = [
     # vocabularies around a fine slice (2048) and a segment's group of four, aligned and odd rows

@@ -6,7 +6,7 @@ import pytest
 from paper_2506_19830_amd import workloads as W
 from test_gpu_accept import check_inputs
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("accept_tables")]
 
 
 def rows(kind, x, rng):
@@ -65,7 +65,7 @@ def has_table(case):
     from paper_2506_19830_amd import binding as B
     return B.la_selftest_accept_table(B.make_accept_desc(num_branches=case.NB, num_draft=case.K, vocab=case.V,
                                                          logits_dtype=case.logits_dtype, temperature=case.temperature,
-                                                         top_k=case.top_k, top_p=case.top_p))
+                                                         top_k=case.top_k, top_p=case.top_p))[0]
 
 
 COLDEST = float(np.float32(0.11))
@@ -74,22 +74,22 @@ COLDEST = float(np.float32(0.11))
 @pytest.mark.parametrize("temperature,table", [(COLDEST, True), (float(np.nextafter(np.float32(0.11), np.float32(0))), False),
                                                (0.125, True)])
 @pytest.mark.parametrize("kind", ["plain", "tiny", "edges", "negative", "masked"])
-def test_coldest_table(oracle, kind, temperature, table):
+def test_coldest_table(oracle, accept_tables, kind, temperature, table):
     """Temperatures around the lowest one with a table: entries up to e^+-582, and rows whose maximum is 300 T or more, which
     keep it as their unit (8200 logits of deviation 3 reach 11, or 100 T; shifted by 100 and 400 they are beyond)."""
     for point_mass, top_p in ((False, 1.0), (True, 0.9)):
         case = W.AcceptCase(f"tab_cold_{kind}", 14, 2, 8200, "bf16", temperature=temperature, top_p=top_p,
                             point_mass=point_mass, peak=6.0, seed=710)
-        assert has_table(case) == table
+        assert has_table(case) == (table and accept_tables == "table")
         check_inputs(oracle, case, make(case, kind))
 
 
 @pytest.mark.parametrize("NB,V", [(63, 2048), (64, 2048), (1, 131071), (1, 129023), (13, 10000), (2, 65535)])
-def test_smallest_calls_with_a_table(oracle, NB, V):
+def test_smallest_calls_with_a_table(oracle, accept_tables, NB, V):
     """64 slices in all, and one less; odd numbers of slices per branch."""
     for top_p in (1.0, 0.9):
         case = W.AcceptCase("tab_small", NB, 2, V, "bf16", temperature=0.7, top_p=top_p, seed=800 + NB)
-        assert has_table(case) == (NB * ((V + 2047) // 2048) >= 64)
+        assert has_table(case) == (accept_tables == "table" and NB * ((V + 2047) // 2048) >= 64)
         check_inputs(oracle, case, make(case, "plain"))
 
 
