@@ -1103,7 +1103,7 @@ __device__ __forceinline__ uint8_t *cand_segment(const AcceptParams &p, int rw, 
 template <bool BF16>
 constexpr int kCandLds = BF16 ? 1792 : 1024;
 __device__ __forceinline__ int cand_capacity(const AcceptParams &p, int group) {
-  return (group + 1) * rowz_group(p) < p.n_fine ? p.cand_cap : p.cand_cap_last;
+  return group + 1 < p.cand_groups ? p.cand_cap : p.cand_cap_last;
 }
 
 template <bool BF16, bool TAB>
@@ -1307,7 +1307,7 @@ __device__ __forceinline__ bool warp_top_p_segments(const AcceptParams &p, int r
   __shared__ uint32_t s_low[kW];
   __shared__ double s_sum[2][3][kW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int n_g = (p.n_fine + rowz_group(p) - 1) / rowz_group(p);
+  const int n_g = p.cand_groups;
   // zk from the row's fine-slice sums, in a fixed order: slice t in lane t, a butterfly per wavefront, the wavefronts
   // in order
   u32x4 keys0 = {0, 0, 0, 0};
@@ -2054,7 +2054,7 @@ hipError_t launch_typed(const AcceptParams &p, hipStream_t stream) {
   if (p.warp_key) {
     ProfileScope scope(SLOT_ACCEPT_WARP, stream);
     if (p.top_p < 1.0f && !(p.top_k > 0 && p.top_k < p.V)) {   // top-p alone needs every target row's whole mass
-      const dim3 grid((p.n_fine + rowz_group(p) - 1) / rowz_group(p), p.NB * (p.K + 1));
+      const dim3 grid(p.cand_groups, p.NB * (p.K + 1));
       if (BF16 && p.exp_tab)
         hipLaunchKernelGGL((accept_rowz_kernel<BF16, BF16>), grid, dim3(RowzShape<true>::kT), 0, stream, p);
       else
@@ -2143,7 +2143,7 @@ void accept_carve_workspace(AcceptParams &p, void *ws) {
     const size_t space = slices * kThreads * 2 * sizeof(double) - (tab ? kTab * sizeof(double) : 0);
     p.cand = at;
     p.cand_row = (int)((space / ((size_t)p.NB * (p.K + 1))) & ~(size_t)15);
-    const int groups = (p.n_fine + rowz_group(p) - 1) / rowz_group(p);
+    const int groups = p.cand_groups = (p.n_fine + rowz_group(p) - 1) / rowz_group(p);
     p.cand_seg = groups > 1 ? (int)((int64_t)p.cand_row * rowz_group(p) / p.n_fine) & ~15 : p.cand_row;
     const int last = p.cand_row - (groups - 1) * p.cand_seg, lds = p.bf16 ? kCandLds<true> : kCandLds<false>;
     auto keys = [&](int bytes) {
@@ -2176,7 +2176,7 @@ hipError_t launch_exp64_probe(const double *y, double *out, size_t n, hipStream_
 }
 
 int accept_row_candidates(const AcceptParams &p) {
-  return p.cand_row ? (p.n_fine - 1) / rowz_group(p) * p.cand_cap + p.cand_cap_last : 0;
+  return p.cand_row ? (p.cand_groups - 1) * p.cand_cap + p.cand_cap_last : 0;
 }
 
 hipError_t launch_accept(const AcceptParams &p, hipStream_t stream) {

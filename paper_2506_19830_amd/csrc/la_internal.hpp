@@ -154,6 +154,7 @@ struct AcceptParams {
   double *exp_tab;             // exp(x / T) of the bf16 logits, or null (see accept.hip)
   uint8_t *cand;               // top-p alone: candidate segments of every target row, in the space of the lists above
   int cand_row;                // bytes of a row's segments (0: none)
+  int cand_groups;             // segments of a row
   int cand_seg;                // bytes of one (the last has what is left)
   int cand_cap, cand_cap_last; // keys that one holds, and the last one
   // top-k / top-p warping of the target rows (off: top_k == 0 and top_p >= 1)
