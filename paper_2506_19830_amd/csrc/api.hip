@@ -63,6 +63,7 @@ ShapeInfo shape_info(int shape) {
       s.t_step = s.tile_m == 64 ? 3.1 : s.tile_m == 128 ? 2.3 : 3.0;
       s.t_step_shared = s.tile_m == 64 ? 2.15 : s.tile_m == 128 ? 2.05 : 2.2;
     } else {
+      // (1.8: fitted to a tile with branches; the present one is 4 to 5 % faster)
       s.t_step = s.t_step_shared = s.tile_m == 256 ? 1.8 : 2.45;
     }
     // (the 256-row bf16 shape: eight row blocks' Q into registers and a branch-private tile per wavefront at the end)
